@@ -4,6 +4,7 @@
 // Everything is checked before the first launch; nothing is allocated or synchronised here.
 #include <algorithm>
 #include <atomic>
+#include <cstdint>
 #include <cstring>
 
 #include "tp_internal.h"
@@ -163,21 +164,36 @@ struct Plan {
     // (0 = not trimmed); the tail covers rows [m_main, m).
     int64_t m_main;
     int tail_tile_id, tail_tiles_m, tail_tiles_n, tail_split;
+    size_t need;               // bytes of workspace the call asks for (at least what the plan uses)
 };
 
-// Measured costs in shader cycles.  One 64-deep K tile of one workgroup: the four-wave stream kernel
-// (256 x 256) takes 2500 - 2900 against 2048 of pure MFMA issue; the eight-wave kernel's half and
-// quarter tiles move more bytes per flop and take ~2200 and ~1400.  On top of that every C tile has
-// a fixed cost: the epilogue alone for the stream kernel (its K tiles keep flowing across C tiles),
-// epilogue plus pipeline refill for the others.
-double k_tile_cycles(int bm, int bn) { return bm * bn == 65536 ? 2730.0 : (bm * bn == 32768 ? 2220.0 : 1410.0); }
-double c_tile_cycles(int bm, int bn) { return bm * bn == 65536 ? 12000.0 : 20000.0; }
+// Costs in shader cycles, by macro-tile area (256 x 256; half; quarter).  k_tile: one 64-deep K tile of one
+// workgroup with the chip full; on a chip that is not, a K tile takes (1 - spare) of that plus spare in proportion
+// to the workgroups (clock and L2 are shared).  c_tile: what a C tile costs besides (epilogue, filling the
+// pipeline).  plane: cycles x 1667 per element and plane of a K split; launch: the fix-up launch; trim: a tail launch.
+struct Costs { double k_tile[3], c_tile[3], spare, plane, launch, trim; };
+// What the kernels take, fitted to a sweep of tiles and splits over eight shapes (0.1 .. 275 GFLOP, all three forms;
+// times in us, one round of 256 workgroups): a K tile 1.5 / 0.9 / 0.53 full and 0.95 / 0.6 / 0.36 alone (half tiles
+// are charged 10 % more: over many rounds their extra traffic costs clock).  The pick
+// is within 1.5 % of the best of the sweep in 23 of 24 products, within 9 % in all.
+constexpr Costs kRunCosts{{2730.0, 1800.0, 1000.0}, {20000.0, 14000.0, 10000.0}, 0.3, 4.0, 10000.0, 40000.0};
+// What the workspace query has always been computed from.  Callers size and keep workspaces by it, so it goes on
+// deciding how many bytes a call needs (and which calls are refused); the plan that runs stays within them.
+constexpr Costs kQueryCosts{{2730.0, 2220.0, 1410.0}, {12000.0, 20000.0, 20000.0}, 0.0, 8.0, 12000.0, 15000.0};
 
-// Pick the macro-tile and the split of K so that the launch fills whole waves of the 256 CUs.
-// Cost model: (waves of workgroups) x (K tiles per workgroup) x (tile area), plus the fp32
-// round trip of the partials when K is split.
+int area_class(int bm, int bn) { return bm * bn == 65536 ? 0 : (bm * bn == 32768 ? 1 : 2); }
+
+size_t ws_bytes_for(const Plan& p, int64_t m, int64_t n) {
+    if (p.m_main > 0)              // the main launch never splits K; the tail may
+        return p.tail_split > 1 ? (size_t)p.tail_split * (size_t)(m - p.m_main) * (size_t)n * sizeof(float) : 0;
+    return p.split_k > 1 ? (size_t)p.split_k * (size_t)p.groups * (size_t)m * (size_t)n * sizeof(float) : 0;
+}
+
+// Pick the macro-tile and the split of K so that the launch fills whole rounds of the 256 CUs, with at most `limit`
+// bytes of partial planes: rounds of workgroups x (K tiles per workgroup x cost + fixed cost), plus the fp32 round
+// trip of the partials when K is split.
 // groups > 1: that many products of the same extents share one launch (tiles_m, tiles_n stay per product).
-Plan plan_whole(const Opts& o, int64_t m, int64_t n, int64_t k, int n_steps, int groups, double* cost_out) {
+Plan plan_whole(const Costs& cs, const Opts& o, int64_t m, int64_t n, int64_t k, int n_steps, int groups, size_t limit, double* cost_out) {
     const int64_t T = (int64_t)n_steps * ((k + 63) / 64);
     Plan best{};
     double best_cost = 1e300;
@@ -189,36 +205,34 @@ Plan plan_whole(const Opts& o, int64_t m, int64_t n, int64_t k, int n_steps, int
         tile_shape(tile_ids[ti], &bm, &bn);
         const int64_t tm = (m + bm - 1) / bm, tn = (n + bn - 1) / bn;
         const int64_t tiles = tm * tn * groups;
-        const double tile_cycles = k_tile_cycles(bm, bn);
-        const double per_tile = c_tile_cycles(bm, bn);
+        const int cls = area_class(bm, bn);
         for (int z = 1; z <= 8; ++z) {
             if (forced_split && z != forced_split) continue;
             if (z > T) break;
-            const int64_t waves = (tiles * z + kCUs - 1) / kCUs;
-            const double main_cost = (double)waves * ((double)((T + z - 1) / z) * tile_cycles + per_tile);
-            // partials: z fp32 planes written and read back at ~1.6 KB/clk, plus one more launch
-            const double fix = z > 1 ? ((double)m * n * 8.0 * z / 1667.0 + 12000.0) * groups : 0.0;
+            Plan c{tile_ids[ti], bm, bn, (int)tm, (int)tn, z, 4, groups, 0, 0, 0, 0, 0, 0};
+            if (ws_bytes_for(c, m, n) > limit) break;
+            const int64_t full = tiles * z / kCUs, rem = tiles * z % kCUs;
+            const double k_cost = (double)((T + z - 1) / z) * cs.k_tile[cls], last = 1.0 - cs.spare + cs.spare * (double)rem / kCUs;
+            const double main_cost = (double)full * (k_cost + cs.c_tile[cls]) + (rem ? k_cost * last + cs.c_tile[cls] : 0.0);
+            const double fix = z > 1 ? ((double)m * n * cs.plane * z / 1667.0 + cs.launch) * groups : 0.0;
             const double cost = main_cost + fix;
             if (cost < best_cost) {
                 best_cost = cost;
-                best = Plan{tile_ids[ti], bm, bn, (int)tm, (int)tn, z, 4, groups, 0, 0, 0, 0, 0};
+                best = c;
             }
         }
     }
     if (best.tile_id == 0) {           // overrides left nothing admissible: fall back to the safe default
-        best = Plan{TILE_256x256, 256, 256, (int)((m + 255) / 256), (int)((n + 255) / 256), 1, 4, groups, 0, 0, 0, 0, 0};
+        best = Plan{TILE_256x256, 256, 256, (int)((m + 255) / 256), (int)((n + 255) / 256), 1, 4, groups, 0, 0, 0, 0, 0, 0};
     }
     best.group_m = o.group > 0 ? o.group : 4;
     if (cost_out) *cost_out = best_cost;
     return best;
 }
 
-// cycles of one C tile of the given shape over T K tiles (the cost model's unit, see plan_whole)
-double tile_cost(int bm, int bn, int64_t T) { return (double)T * k_tile_cycles(bm, bn) + c_tile_cycles(bm, bn); }
-
-Plan make_plan(const Opts& o, int64_t m, int64_t n, int64_t k, int n_steps, int groups = 1) {
+Plan plan_by(const Costs& cs, const Opts& o, int64_t m, int64_t n, int64_t k, int n_steps, int groups, size_t limit) {
     double whole_cost = 0.0;
-    Plan best = plan_whole(o, m, n, k, n_steps, groups, &whole_cost);
+    Plan best = plan_whole(cs, o, m, n, k, n_steps, groups, limit, &whole_cost);
     if (groups != 1 || !o.trim || o.split > 1) return best;
     const int64_t T = (int64_t)n_steps * ((k + 63) / 64);
     const int tile_ids[4] = {TILE_256x256, TILE_128x256, TILE_256x128, TILE_128x128};
@@ -235,15 +249,23 @@ Plan make_plan(const Opts& o, int64_t m, int64_t n, int64_t k, int n_steps, int 
         if (tail_rows_tiles >= tm) continue;
         const int64_t m_main = (tm - tail_rows_tiles) * bm;
         double tail_cost = 0.0;
-        const Plan tail = plan_whole(o, m - m_main, n, k, n_steps, 1, &tail_cost);
-        const double cost = (double)((tiles - rem) / kCUs) * tile_cost(bm, bn, T) + tail_cost + 15000.0;   // + one more launch
+        const Plan tail = plan_whole(cs, o, m - m_main, n, k, n_steps, 1, limit, &tail_cost);
+        const int cls = area_class(bm, bn);
+        const double cost = (double)((tiles - rem) / kCUs) * ((double)T * cs.k_tile[cls] + cs.c_tile[cls]) + tail_cost + cs.trim;
         if (cost < best_cost) {
             best_cost = cost;
             best = Plan{tile_ids[ti], bm, bn, (int)(tm - tail_rows_tiles), (int)tn, 1, best.group_m, 1,
-                        m_main, tail.tile_id, tail.tiles_m, tail.tiles_n, tail.split_k};
+                        m_main, tail.tile_id, tail.tiles_m, tail.tiles_n, tail.split_k, 0};
         }
     }
     return best;
+}
+
+Plan make_plan(const Opts& o, int64_t m, int64_t n, int64_t k, int n_steps, int groups = 1) {
+    const size_t need = ws_bytes_for(plan_by(kQueryCosts, o, m, n, k, n_steps, groups, SIZE_MAX), m, n);
+    Plan p = plan_by(kRunCosts, o, m, n, k, n_steps, groups, need);
+    p.need = need;
+    return p;
 }
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -261,12 +283,6 @@ int check_oblk(const tp_oblk_t& b, int64_t cols, bool f32_only) {
     if (!aligned16(b.ptr) || (b.ld & 7) || (cols & 7)) return TP_ERR_ALIGN;
     if (b.ld < cols) return TP_ERR_SHAPE;
     return TP_OK;
-}
-
-size_t ws_bytes_for(const Plan& p, int64_t m, int64_t n) {
-    if (p.m_main > 0)              // the main launch never splits K; the tail may
-        return p.tail_split > 1 ? (size_t)p.tail_split * (size_t)(m - p.m_main) * (size_t)n * sizeof(float) : 0;
-    return p.split_k > 1 ? (size_t)p.split_k * (size_t)p.groups * (size_t)m * (size_t)n * sizeof(float) : 0;
 }
 
 struct Product {                 // one validated GEMM ready to launch
@@ -297,10 +313,20 @@ bool w4_eligible(int form, const GemmArgs& a) {
 }
 
 int run_one(const Opts& o, int form, int tile_id, int split_k, const GemmArgs& a, hipStream_t stream) {
-    // 256 x 256 tiles run on the four-wave stream kernel unless the eight-wave one is asked for
-    if (tile_id == TILE_256x256 && !o.eight_wave && w4_eligible(form, a)) tile_id = TILE_256x256_W4;
+    // 256 x 256 tiles run on the four-wave stream kernel unless the eight-wave one is asked for, smaller ones on
+    // the four-wave kernel with a ring of stages; the eight-wave kernel keeps what their 32-bit offsets cannot reach
+    const bool four_wave = !o.eight_wave && w4_eligible(form, a);
+    if (four_wave) {
+        switch (tile_id) {
+            case TILE_256x256: tile_id = TILE_256x256_W4; break;
+            case TILE_128x256: tile_id = TILE_128x256_MS; break;
+            case TILE_256x128: tile_id = TILE_256x128_MS; break;
+            case TILE_128x128: tile_id = TILE_128x128_MS; break;
+            default: break;
+        }
+    }
     GemmArgs la = a;
-    la.rotate = o.rotate < 0 ? (tile_id != TILE_256x256_W4) : o.rotate;
+    la.rotate = o.rotate < 0 ? !four_wave : o.rotate;
     if (launch_gemm(form, tile_id, la, stream) != hipSuccess) return TP_ERR_HIP;
     if (split_k > 1) {
         const int groups = a.n_groups > 1 ? a.n_groups : 1;
@@ -411,8 +437,8 @@ int linear_fwd(const tp_grid_t* grid, const tp_dims_t* dims, int n_steps, const 
     }
     Plan p = make_plan(o, s.m, s.n, s.k, n_steps);
     if (use_static_scratch) {
-        if (ws_bytes_for(p, s.m, s.n) > kStaticScratchBytes) return TP_ERR_SCRATCH;
-    } else if (!ws_ok(ws_bytes_for(p, s.m, s.n), workspace, workspace_bytes)) {
+        if (p.need > kStaticScratchBytes) return TP_ERR_SCRATCH;
+    } else if (!ws_ok(p.need, workspace, workspace_bytes)) {
         return TP_ERR_WORKSPACE;
     }
     if (int e = check_device()) return e;
@@ -467,14 +493,14 @@ size_t tp_linear_workspace_size_ex(const tp_grid_t* grid, const tp_dims_t* dims,
         if (build_partials(grid, dims, pass, &ps) != TP_OK) return 0;
         size_t worst = 0;               // any number of products 1 .. n_steps may be asked for
         for (int groups = 1; groups <= ps.n_steps; ++groups)
-            worst = std::max(worst, ws_bytes_for(make_plan(o, ps.m, ps.n, ps.k, 1, groups), ps.m, ps.n));
+            worst = std::max(worst, make_plan(o, ps.m, ps.n, ps.k, 1, groups).need);
         return worst;
     }
     Share s;
     if (build_share(grid, dims, pass, &s) != TP_OK) return 0;
     size_t worst = 0;                   // any prefix 1 .. n_steps of the steps may be asked for
     for (int steps = 1; steps <= s.n_steps; ++steps)
-        worst = std::max(worst, ws_bytes_for(make_plan(o, s.m, s.n, s.k, steps), s.m, s.n));
+        worst = std::max(worst, make_plan(o, s.m, s.n, s.k, steps).need);
     Share sf;                           // the bias gradient of tp_linear_bwd sums the forward block's columns in two passes
     if (pass != TP_PASS_FWD && build_share(grid, dims, TP_PASS_FWD, &sf) == TP_OK)
         worst = std::max(worst, colsum_ws_bytes(sf.m, sf.n));
@@ -584,8 +610,8 @@ int tp_linear_bwd_ex(const tp_grid_t* grid, const tp_dims_t* dims, int n_steps_d
         pw.form = FORM_TN; pw.plan = p;
     }
     size_t need = 0;
-    if (px.active) need = std::max(need, ws_bytes_for(px.plan, sx.m, sx.n));
-    if (pw.active) need = std::max(need, ws_bytes_for(pw.plan, sw.m, sw.n));
+    if (px.active) need = std::max(need, px.plan.need);
+    if (pw.active) need = std::max(need, pw.plan.need);
     if (!ws_ok(need, workspace, workspace_bytes)) return TP_ERR_WORKSPACE;
     if (want_da || px.active || pw.active)
         if (int e = check_device()) return e;
@@ -692,8 +718,8 @@ int tp_linear_bwd_partials_ex(const tp_grid_t* grid, const tp_dims_t* dims, int 
         for (int j = i + 1; j < n_ranges; ++j)
             if (overlap(ranges[i], ranges[j])) return TP_ERR_SHAPE;
     size_t need = 0;
-    if (px.active) need = std::max(need, ws_bytes_for(px.plan, sx.m, sx.n));
-    if (pw.active) need = std::max(need, ws_bytes_for(pw.plan, sw.m, sw.n));
+    if (px.active) need = std::max(need, px.plan.need);
+    if (pw.active) need = std::max(need, pw.plan.need);
     if (!ws_ok(need, workspace, workspace_bytes)) return TP_ERR_WORKSPACE;
     if (int e = check_device()) return e;
     if (px.active) if (int e = run_product(o, px, workspace, stream)) return e;

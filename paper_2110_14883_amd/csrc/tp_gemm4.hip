@@ -20,55 +20,11 @@
 //     boundary;
 //   * tile order and epilogue (bias / GeLU / GeLU' in registers, then through a wave-private LDS patch so
 //     that stores are whole 128-byte row segments) are those of the eight-wave kernel.
-#include <utility>
-
-#include "tp_device.h"
+#include "tp_stream.h"
 
 namespace tpl {
 
 namespace {
-
-template <class F, int... I>
-__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, I...>) {
-    (f(std::integral_constant<int, I>{}), ...);
-}
-template <int N, class F>
-__device__ __forceinline__ void static_for(F&& f) {
-    static_for_impl(f, std::make_integer_sequence<int, N>{});
-}
-
-// a value every lane agrees on, pinned to a scalar register (keeps the cursor arithmetic on the scalar unit)
-__device__ __forceinline__ int uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
-__device__ __forceinline__ const uint16_t* uni_ptr(const void* q) {
-    const uint64_t v = reinterpret_cast<uint64_t>(q);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
-    return reinterpret_cast<const uint16_t*>(((uint64_t)hi << 32) | lo);
-}
-
-// LDS access by 32-bit byte address.  The kernel has no static LDS, so its dynamic LDS starts at
-// address 0 and an address is the offset into it.
-typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4_t;
-typedef __attribute__((ext_vector_type(4))) short i16x4_t;
-typedef __attribute__((address_space(3))) i16x4_t lds_i16x4_t;
-typedef __attribute__((address_space(3))) bf16x8_t lds_bf16x8_t;
-__device__ __forceinline__ bf16x8_t lds_load_frag(uint32_t addr) { return *reinterpret_cast<const lds_bf16x8_t*>(addr); }
-__device__ __forceinline__ bf16x4_t lds_load_tr(uint32_t addr) {
-    return __builtin_bit_cast(bf16x4_t, __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<lds_i16x4_t*>(addr)));
-}
-
-// One direct-to-LDS load: each lane's 16 bytes go from global memory straight into LDS, lane l at
-// byte lds_base + 16 l (lds_base: wave-uniform, travels in M0), without touching the vector registers.
-// Out-of-range lanes write zeros.  The compiler does not see this load: whoever reads the data waits
-// for it with wait_vm() and a barrier.
-__device__ __forceinline__ void dtl_load16(u32x4_t rsrc_words, uint32_t voff, uint32_t lds_base) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-                 :: "s"(lds_base), "v"(voff), "s"(rsrc_words) : "memory");
-}
-template <int N> __device__ __forceinline__ void wait_vm() {      // at most N vector-memory operations outstanding
-    static_assert(N >= 0 && N < 64);
-    __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
-}
 
 constexpr int W4_THREADS = 256;
 constexpr int W4_BM = 256, W4_BN = 256;
@@ -316,150 +272,6 @@ void tp_gemm4_kernel(const GemmArgs p) {
         });
     };
 
-    // ------------------------------------------------------------------ epilogue of the compute cursor's C tile
-    // acc[i][j][e]: row m = 32 i + lane%32, columns n = 32 j + 8 (e/4) + 4 (lane/32) + e%4.
-    // No branch depends on a lane: every global access goes through a buffer descriptor that starts at
-    // the first row of this wave's 128 x 128 block and ends with the last row of the matrix, so rows
-    // below a ragged edge are dropped by the range check, and a lane whose columns lie beyond N carries
-    // an out-of-range offset.  One slab = 32 rows x 128 columns passes through the wave's LDS patch so
-    // that stores are whole row segments.
-    auto epilogue = [&]() __attribute__((always_inline)) {
-        const int m_sub = c.m0 + wm * 128, n_sub = c.n0 + wn * 128;
-        const int r = lr;
-        const bool partial = Z > 1;          // split K: raw fp32 partials, the fix-up kernel runs the epilogue
-        constexpr bool use_bias = EPI == EPI_BIAS || EPI == EPI_BIAS_GELU;
-        constexpr bool use_gelu = EPI == EPI_BIAS_GELU;
-        constexpr bool use_dg = EPI == EPI_MUL_DGELU;
-        const bool use_pre = !use_dg && p.pre != nullptr;
-        const int rows_left = p.M - m_sub;
-        // rows m_sub .. M - 1 of a matrix with leading dimension ld (elements of es bytes), N columns
-        auto block_rsrc = [&](const void* base, int64_t ld, int es) __attribute__((always_inline)) {
-            const int64_t nrec = rows_left > 0 ? ((int64_t)(rows_left - 1) * ld + p.N) * es : 0;
-            return make_rsrc(uni_ptr(static_cast<const char*>(base) + (int64_t)m_sub * ld * es), nrec);
-        };
-        u32x2_t bias_v[TN][4];
-        if constexpr (use_bias) {
-            const __amdgpu_buffer_rsrc_t rs_bias = make_rsrc(uni_ptr(p.bias), (int64_t)p.N * 2);
-#pragma unroll
-            for (int j = 0; j < TN; ++j)
-#pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    const u32x2_t b = __builtin_amdgcn_raw_buffer_load_b64(rs_bias, (n_sub + 32 * j + 8 * g + 4 * ch) * 2, 0, 0);
-                    bias_v[j][g] = b;
-                }
-        }
-        __amdgpu_buffer_rsrc_t rs_dg;
-        uint32_t dg_lane = 0;
-        if constexpr (use_dg) {
-            rs_dg = block_rsrc(p.dg, p.lddg, 2);
-            dg_lane = (uint32_t)((r * (int)p.lddg + n_sub + 4 * ch) * 2);   // columns past N: the next row's values or zeros, never stored
-        }
-        // The accumulators stay where the MFMAs keep them (the accumulator half of the register file) and
-        // are fetched four at a time, where they are used: left to itself the compiler copies all 256 out
-        // at once, which cannot fit beside the staging registers.
-        auto raw4 = [&](int i, int j, int g, float (&v)[4]) __attribute__((always_inline)) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(v[e]) : "a"(acc[i][j][4 * g + e]));
-        };
-        auto preact4 = [&](int i, int j, int g, float (&v)[4]) __attribute__((always_inline)) {
-            raw4(i, j, g, v);
-            if constexpr (use_bias) {
-                const u32x2_t b = bias_v[j][g];
-                v[0] += bf16_lo(b[0]); v[1] += bf16_hi(b[0]); v[2] += bf16_lo(b[1]); v[3] += bf16_hi(b[1]);
-            }
-        };
-        u32x2_t dg_v[TN][4];
-        auto load_dg = [&](int i) __attribute__((always_inline)) {
-            if constexpr (use_dg) {
-#pragma unroll
-                for (int j = 0; j < TN; ++j)
-#pragma unroll
-                    for (int g = 0; g < 4; ++g)
-                        dg_v[j][g] = __builtin_amdgcn_raw_buffer_load_b64(rs_dg, dg_lane + (uint32_t)(((32 * i) * (int)p.lddg + 32 * j + 8 * g) * 2), 0, 0);
-            }
-        };
-        auto final4 = [&](int i, int j, int g, float (&v)[4]) __attribute__((always_inline)) {
-            preact4(i, j, g, v);
-            if constexpr (use_gelu) {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] = gelu_f(v[e]);
-            }
-            if constexpr (use_dg) {
-                const u32x2_t a = dg_v[j][g];
-                v[0] *= dgelu_f(bf16_lo(a[0])); v[1] *= dgelu_f(bf16_hi(a[0]));
-                v[2] *= dgelu_f(bf16_lo(a[1])); v[3] *= dgelu_f(bf16_hi(a[1]));
-            }
-        };
-        // bf16 slab of 32 rows x 128 columns: rows of 256 bytes in the patch; a lane writes 8 bytes and
-        // reads back 16 (chunk index XOR row keeps both conflict-free), stores are 256-byte row segments:
-        // lane l stores columns 8 (l % 16) .. + 7 of rows l / 16 + 4 it
-        auto slab_bf16 = [&](int i, auto value4, __amdgpu_buffer_rsrc_t rs, int ld) __attribute__((always_inline)) {
-            const uint32_t lane = (n_sub + 8 * (l & 15)) < p.N ? (uint32_t)(((l >> 4) * ld + n_sub + 8 * (l & 15)) * 2) : OOB_OFFSET;
-#pragma unroll
-            for (int j = 0; j < TN; ++j)
-#pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    float x[4];
-                    value4(i, j, g, x);
-                    const u32x2_t v = {pack_bf16(x[0], x[1]), pack_bf16(x[2], x[3])};
-                    *reinterpret_cast<u32x2_t*>(eps + r * 256 + (((4 * j + g) ^ (r & 15)) << 4) + 8 * ch) = v;
-                }
-#pragma unroll
-            for (int it = 0; it < 8; ++it) {
-                const int rr = it * 4 + (l >> 4), cc = l & 15;
-                const u32x4_t v = *reinterpret_cast<const u32x4_t*>(eps + rr * 256 + ((cc ^ (rr & 15)) << 4));
-                __builtin_amdgcn_raw_buffer_store_b128(v, rs, (int)(lane + (uint32_t)((32 * i + 4 * it) * ld * 2)), 0, 0);
-            }
-        };
-        // fp32 slab, one 32-column block at a time: rows of 128 bytes; lane l stores columns
-        // 4 (l % 8) .. + 3 of rows l / 8 + 8 it
-        auto slab_f32 = [&](int i, auto value4, __amdgpu_buffer_rsrc_t rs, int ld) __attribute__((always_inline)) {
-#pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                const int n = n_sub + 32 * j + 4 * (l & 7);
-                const uint32_t lane = n < p.N ? (uint32_t)(((l >> 3) * ld + n) * 4) : OOB_OFFSET;
-#pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    float x[4];
-                    value4(i, j, g, x);
-                    const f32x4_t v = {x[0], x[1], x[2], x[3]};
-                    *reinterpret_cast<f32x4_t*>(eps + r * 128 + (((2 * g + ch) ^ ((r >> 1) & 7)) << 4)) = v;
-                }
-#pragma unroll
-                for (int it = 0; it < 4; ++it) {
-                    const int rr = it * 8 + (l >> 3), cc = l & 7;
-                    const u32x4_t v = *reinterpret_cast<const u32x4_t*>(eps + rr * 128 + ((cc ^ ((rr >> 1) & 7)) << 4));
-                    __builtin_amdgcn_raw_buffer_store_b128(v, rs, (int)(lane + (uint32_t)((32 * i + 8 * it) * ld * 4)), 0, 0);
-                }
-            }
-        };
-        // (the last MFMA's result is read by hand-placed instructions: give it the 19 cycles it needs)
-        asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7" ::: "memory");
-        if (partial) {
-            const __amdgpu_buffer_rsrc_t rs_ws = block_rsrc(p.ws + ((int64_t)c.z * p.n_groups + c.g) * p.M * p.N, (int64_t)p.N, 4);
-#pragma unroll
-            for (int i = 0; i < TM; ++i) {
-                slab_f32(i, raw4, rs_ws, p.N);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        } else {
-            const int ldo = (int)p.ldos[c.g];
-            const __amdgpu_buffer_rsrc_t rs_out = block_rsrc(p.outs[c.g], ldo, F32_OUT ? 4 : 2);
-            __amdgpu_buffer_rsrc_t rs_pre;
-            if constexpr (!use_dg) rs_pre = block_rsrc(p.pre, p.ldp, 2);
-#pragma unroll
-            for (int i = 0; i < TM; ++i) {
-                load_dg(i);
-                if constexpr (!use_dg) {
-                    if (use_pre) slab_bf16(i, preact4, rs_pre, (int)p.ldp);
-                }
-                if constexpr (F32_OUT) slab_f32(i, final4, rs_out, ldo);
-                else                   slab_bf16(i, final4, rs_out, ldo);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        }
-    };
-
     // ------------------------------------------------------------------ the stream
     start(f, (int)blockIdx.x);
     if (f.left == 0) return;
@@ -487,7 +299,7 @@ void tp_gemm4_kernel(const GemmArgs p) {
             k_tile(S0{});
             k_tile(S1{});
         }
-        epilogue();
+        store_c_block<TM, TN, EPI, F32_OUT, true>(p, acc, c.m0 + wm * 128, c.n0 + wn * 128, c.z, c.g, eps);
         start(c, c.v + grid);
         if (c.left == 0) break;
     }

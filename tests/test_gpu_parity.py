@@ -663,3 +663,15 @@ def test_config5_gathered_full_size_sampled():
     g = T.Grid(T.MODE_3D_GATHERED, p=c.grid.p, ri=c.grid.ri, rj=c.grid.rj, rk=c.grid.rk)
     mp = T.tp_block_map(g, c.dims, 0)
     _gathered3d(g, c.dims, rows=S.sample_rows(11, mp["m"], 128), w_rows=S.sample_rows(12, mp["k"], 64), label=c.name)
+
+
+@pytest.mark.parametrize("tile", [2, 3, 4])
+@pytest.mark.parametrize("m,k,n", [(1, 8, 8), (127, 64, 264), (129, 328, 248), (300, 712, 520)])
+def test_ring_kernel_edges(tile, m, k, n):
+    """The kernel with a ring of LDS stages at the edges of its tiles: one row, one K tile, fewer K tiles than
+    stages (so that fetches past the end must be harmless), ragged extents of every kind; two steps, both
+    directions, whole and with K split."""
+    grid, dims = T.Grid(T.MODE_2D, q=2, ri=1, rj=0), (2 * m, 2 * k, 2 * n)
+    for split in (1, 2):
+        with overrides(tile=tile, split=split):
+            run_share(grid, dims, y_dtype="f32", dx_dtype="bf16", use_own_slot=False, label=f"tile {tile} split {split} {m}x{k}x{n}")
