@@ -15,7 +15,7 @@ CSRC = os.path.join(PKG_DIR, "csrc")
 OBJ_DIR = os.path.join(CSRC, "_build")
 LIB_PATH = os.path.join(PKG_DIR, "libtplinear.so")
 PROBE_LIB_PATH = os.path.join(PKG_DIR, "libtpprobe.so")      # bench-only measurement aid (tp_probe.hip)
-SOURCES = ["tp_kernels.hip", "tp_gemm4.hip", "tp_gemm_ms.hip", "tp_api.cpp"]
+SOURCES = ["tp_kernels.hip", "tp_gemm4.hip", "tp_gemm_ms.hip", "tp_small.hip", "tp_api.cpp"]
 PROBE_SOURCE = "tp_probe.hip"
 HEADERS = [os.path.join(ROOT, "include", "tp_linear.h"), os.path.join(ROOT, "include", "tp_probe.h"), os.path.join(CSRC, "tp_internal.h"), os.path.join(CSRC, "tp_device.h"), os.path.join(CSRC, "tp_stream.h")]
 

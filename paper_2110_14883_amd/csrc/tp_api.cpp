@@ -230,9 +230,11 @@ Plan plan_whole(const Costs& cs, const Opts& o, int64_t m, int64_t n, int64_t k,
     return best;
 }
 
-Plan plan_by(const Costs& cs, const Opts& o, int64_t m, int64_t n, int64_t k, int n_steps, int groups, size_t limit) {
+Plan plan_by(const Costs& cs, const Opts& o, int64_t m, int64_t n, int64_t k, int n_steps, int groups, size_t limit,
+             double* cost_out = nullptr) {
     double whole_cost = 0.0;
     Plan best = plan_whole(cs, o, m, n, k, n_steps, groups, limit, &whole_cost);
+    if (cost_out) *cost_out = whole_cost;
     if (groups != 1 || !o.trim || o.split > 1) return best;
     const int64_t T = (int64_t)n_steps * ((k + 63) / 64);
     const int tile_ids[4] = {TILE_256x256, TILE_128x256, TILE_256x128, TILE_128x128};
@@ -254,6 +256,7 @@ Plan plan_by(const Costs& cs, const Opts& o, int64_t m, int64_t n, int64_t k, in
         const double cost = (double)((tiles - rem) / kCUs) * ((double)T * cs.k_tile[cls] + cs.c_tile[cls]) + tail_cost + cs.trim;
         if (cost < best_cost) {
             best_cost = cost;
+            if (cost_out) *cost_out = cost;
             best = Plan{tile_ids[ti], bm, bn, (int)(tm - tail_rows_tiles), (int)tn, 1, best.group_m, 1,
                         m_main, tail.tile_id, tail.tiles_m, tail.tiles_n, tail.split_k, 0};
         }
@@ -261,9 +264,29 @@ Plan plan_by(const Costs& cs, const Opts& o, int64_t m, int64_t n, int64_t k, in
     return best;
 }
 
-Plan make_plan(const Opts& o, int64_t m, int64_t n, int64_t k, int n_steps, int groups = 1) {
+// The same for the kernel that splits K over the waves of a workgroup (no partial planes, one launch): `wgs`
+// workgroups, T chunks of 64 k each.  Fitted to 22 shapes, each form, up to 512 workgroups and 64 chunks (replayed
+// graphs): 3 us per launch, then per round of 256 workgroups 0.6 - 1.2 us and 0.11 - 0.25 us a chunk.  Measured on
+// both sides: 128 x 2048 x 512, 2 steps, forward 6.7 us against 14.0 (128 x 128, split 4 and fix-up); 300 x 328 x 136, 2
+// steps 4.4 / 4.8 / 5.2 us against 10.0 / 9.4 / 8.2; beyond, the larger tiles' reuse of operands wins: 64 x 4096 x 4096
+// 16.5 us against 15.3, 1024 x 256 x 1024 dX 10.1 against 6.5.
+double small_cost(int form, int bm, int64_t wgs, int64_t T) {
+    if (wgs > 2 * kCUs || T > 64) return 1e300;
+    const double chunk = form == FORM_TN ? 200.0 : (form == FORM_NN ? (bm == 16 ? 255.0 : 345.0) : (bm == 16 ? 310.0 : 455.0));
+    const double round = form == FORM_TN ? 2200.0 : 1100.0;
+    return 5500.0 + (double)((wgs + kCUs - 1) / kCUs) * (round + chunk * (double)T);
+}
+
+Plan make_plan(const Opts& o, int form, int64_t m, int64_t n, int64_t k, int n_steps, int groups = 1) {
     const size_t need = ws_bytes_for(plan_by(kQueryCosts, o, m, n, k, n_steps, groups, SIZE_MAX), m, n);
-    Plan p = plan_by(kRunCosts, o, m, n, k, n_steps, groups, need);
+    double cost = 0.0;
+    Plan p = plan_by(kRunCosts, o, m, n, k, n_steps, groups, need, &cost);
+    if (!o.tile && !o.split) {
+        const int bm = m <= 16 && form != FORM_TN ? 16 : 32;
+        const int64_t tm = (m + bm - 1) / bm, tn = (n + 31) / 32;
+        if (1.1 * small_cost(form, bm, tm * tn * groups, (int64_t)n_steps * ((k + 63) / 64)) < cost)
+            p = Plan{bm == 16 ? TILE_16x32_SMALL : TILE_32x32_SMALL, bm, 32, (int)tm, (int)tn, 1, o.group > 0 ? o.group : 4, groups, 0, 0, 0, 0, 0, 0};
+    }
     p.need = need;
     return p;
 }
@@ -316,6 +339,16 @@ int run_one(const Opts& o, int form, int tile_id, int split_k, const GemmArgs& a
     // 256 x 256 tiles run on the four-wave stream kernel unless the eight-wave one is asked for, smaller ones on
     // the four-wave kernel with a ring of stages; the eight-wave kernel keeps what their 32-bit offsets cannot reach
     const bool four_wave = !o.eight_wave && w4_eligible(form, a);
+    GemmArgs la = a;
+    if (!four_wave && (tile_id == TILE_32x32_SMALL || tile_id == TILE_16x32_SMALL)) {
+        const int groups = a.n_groups > 1 ? a.n_groups : 1;
+        tile_id = TILE_128x128;
+        la.tiles_m = (a.M + 127) / 128; la.tiles_n = (a.N + 127) / 128;
+        if (groups > 1) {
+            la.group_tiles = a.group_along_n ? la.tiles_n : la.tiles_m;
+            (a.group_along_n ? la.tiles_n : la.tiles_m) *= groups;
+        }
+    }
     if (four_wave) {
         switch (tile_id) {
             case TILE_256x256: tile_id = TILE_256x256_W4; break;
@@ -325,7 +358,6 @@ int run_one(const Opts& o, int form, int tile_id, int split_k, const GemmArgs& a
             default: break;
         }
     }
-    GemmArgs la = a;
     la.rotate = o.rotate < 0 ? !four_wave : o.rotate;
     if (launch_gemm(form, tile_id, la, stream) != hipSuccess) return TP_ERR_HIP;
     if (split_k > 1) {
@@ -435,7 +467,7 @@ int linear_fwd(const tp_grid_t* grid, const tp_dims_t* dims, int n_steps, const 
         if (int e = check_oblk(preact, s.n, false)) return e;
         if (preact.dtype != TP_BF16) return TP_ERR_DTYPE;
     }
-    Plan p = make_plan(o, s.m, s.n, s.k, n_steps);
+    Plan p = make_plan(o, FORM_NN, s.m, s.n, s.k, n_steps);
     if (use_static_scratch) {
         if (p.need > kStaticScratchBytes) return TP_ERR_SCRATCH;
     } else if (!ws_ok(p.need, workspace, workspace_bytes)) {
@@ -493,14 +525,14 @@ size_t tp_linear_workspace_size_ex(const tp_grid_t* grid, const tp_dims_t* dims,
         if (build_partials(grid, dims, pass, &ps) != TP_OK) return 0;
         size_t worst = 0;               // any number of products 1 .. n_steps may be asked for
         for (int groups = 1; groups <= ps.n_steps; ++groups)
-            worst = std::max(worst, make_plan(o, ps.m, ps.n, ps.k, 1, groups).need);
+            worst = std::max(worst, make_plan(o, pass == TP_PASS_DX_PARTIALS ? FORM_NT : FORM_TN, ps.m, ps.n, ps.k, 1, groups).need);
         return worst;
     }
     Share s;
     if (build_share(grid, dims, pass, &s) != TP_OK) return 0;
     size_t worst = 0;                   // any prefix 1 .. n_steps of the steps may be asked for
     for (int steps = 1; steps <= s.n_steps; ++steps)
-        worst = std::max(worst, make_plan(o, s.m, s.n, s.k, steps).need);
+        worst = std::max(worst, make_plan(o, pass == TP_PASS_FWD ? FORM_NN : (pass == TP_PASS_DX ? FORM_NT : FORM_TN), s.m, s.n, s.k, steps).need);
     Share sf;                           // the bias gradient of tp_linear_bwd sums the forward block's columns in two passes
     if (pass != TP_PASS_FWD && build_share(grid, dims, TP_PASS_FWD, &sf) == TP_OK)
         worst = std::max(worst, colsum_ws_bytes(sf.m, sf.n));
@@ -573,7 +605,7 @@ int tp_linear_bwd_ex(const tp_grid_t* grid, const tp_dims_t* dims, int n_steps_d
             if (dgelu_preact) return TP_ERR_MODE;
             if (dx.dtype != TP_F32) return TP_ERR_DTYPE;
         }
-        Plan p = make_plan(o, sx.m, sx.n, sx.k, n_steps_dx);
+        Plan p = make_plan(o, FORM_NT, sx.m, sx.n, sx.k, n_steps_dx);
         fill_common(o, px.args, p, sx.m, sx.n, sx.k, n_steps_dx);
         for (int k = 0; k < n_steps_dx; ++k) {
             const tp_cblk_t& a = (k == own_slot_dx) ? own_blk : da_row_blocks[k];
@@ -596,7 +628,7 @@ int tp_linear_bwd_ex(const tp_grid_t* grid, const tp_dims_t* dims, int n_steps_d
         if (!x_blocks_dw || !da_col_blocks) return TP_ERR_NULL;
         if (n_steps_dw < 1 || n_steps_dw > sw.n_steps) return TP_ERR_SHAPE;
         if (own_slot_dw >= n_steps_dw) return TP_ERR_SHAPE;
-        Plan p = make_plan(o, sw.m, sw.n, sw.k, n_steps_dw);
+        Plan p = make_plan(o, FORM_TN, sw.m, sw.n, sw.k, n_steps_dw);
         fill_common(o, pw.args, p, sw.m, sw.n, sw.k, n_steps_dw);
         for (int k = 0; k < n_steps_dw; ++k) {
             const tp_cblk_t& b = (k == own_slot_dw) ? own_blk : da_col_blocks[k];
@@ -681,7 +713,7 @@ int tp_linear_bwd_partials_ex(const tp_grid_t* grid, const tp_dims_t* dims, int 
     Product px{}; px.active = n_dx > 0;
     if (px.active) {
         if (!w_blocks_dx || !dx_partials) return TP_ERR_NULL;
-        Plan p = make_plan(o, sx.m, sx.n, sx.k, 1, n_dx);
+        Plan p = make_plan(o, FORM_NT, sx.m, sx.n, sx.k, 1, n_dx);
         fill_common(o, px.args, p, sx.m, sx.n, sx.k, 1);
         for (int k = 0; k < n_dx; ++k) {
             if (int e = check_cblk(w_blocks_dx[k], sx.k)) return e;    // W block [H_blk][F_blk]: n x k
@@ -699,7 +731,7 @@ int tp_linear_bwd_partials_ex(const tp_grid_t* grid, const tp_dims_t* dims, int 
     Product pw{}; pw.active = n_dw > 0;
     if (pw.active) {
         if (!x_blocks_dw || !dw_partials) return TP_ERR_NULL;
-        Plan p = make_plan(o, sw.m, sw.n, sw.k, 1, n_dw);
+        Plan p = make_plan(o, FORM_TN, sw.m, sw.n, sw.k, 1, n_dw);
         fill_common(o, pw.args, p, sw.m, sw.n, sw.k, 1);
         for (int k = 0; k < n_dw; ++k) {
             if (int e = check_cblk(x_blocks_dw[k], sw.m)) return e;    // X block [M_blk][H_blk]: k x m

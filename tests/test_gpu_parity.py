@@ -675,3 +675,13 @@ def test_ring_kernel_edges(tile, m, k, n):
     for split in (1, 2):
         with overrides(tile=tile, split=split):
             run_share(grid, dims, y_dtype="f32", dx_dtype="bf16", use_own_slot=False, label=f"tile {tile} split {split} {m}x{k}x{n}")
+
+
+@pytest.mark.parametrize("m,k,n", [(1, 8, 8), (16, 72, 40), (17, 64, 264), (33, 200, 96), (100, 1096, 104)])
+def test_workgroup_split_kernel_edges(m, k, n):
+    """Products small enough for the kernel that splits K over the waves of one workgroup, at the edges of its
+    tiles (16 or 32 rows, 32 columns), with fewer chunks of K than waves and with several rounds of them, ragged in
+    every extent; two steps, both directions, fused epilogues."""
+    for seed, (y, dx) in enumerate((("f32", "bf16"), ("bf16", "f32"))):
+        run_share(T.Grid(T.MODE_2D, q=2, ri=1, rj=0), (2 * m, 2 * k, 2 * n), y_dtype=y, dx_dtype=dx, want_db=True,
+                  seed=S.BASE_SEED + seed, label=f"{m}x{k}x{n}")
