@@ -650,13 +650,14 @@ int tp_linear_bwd_ex(const tp_grid_t* grid, const tp_dims_t* dims, int n_steps_d
 
     // ---- launches (stream order: dA, db, dX, dW)
     if (want_da) {
-        if (launch_dgelu(dy_own->ptr, dy_own->ld, preact_own->ptr, preact_own->ld, da_own_out.ptr, da_own_out.ld,
-                         sf.m, sf.n, stream) != hipSuccess) return TP_ERR_HIP;
-        // (two passes over row slabs when the workspace holds the slab sums, else one workgroup per 64 columns)
+        // (the column sums take two passes over row slabs when the workspace holds the slab sums, else one)
         float* const cws = (workspace && aligned16(workspace) && workspace_bytes >= colsum_ws_bytes(sf.m, sf.n))
                                ? static_cast<float*>(workspace) : nullptr;
-        if (db_f32 && launch_colsum(da_own_out.ptr, da_own_out.ld, sf.m, sf.n, static_cast<float*>(db_f32), cws, stream) != hipSuccess)
-            return TP_ERR_HIP;
+        const hipError_t e = db_f32 ? launch_dgelu_colsum(dy_own->ptr, dy_own->ld, preact_own->ptr, preact_own->ld, da_own_out.ptr,
+                                                          da_own_out.ld, sf.m, sf.n, static_cast<float*>(db_f32), cws, stream)
+                                    : launch_dgelu(dy_own->ptr, dy_own->ld, preact_own->ptr, preact_own->ld, da_own_out.ptr,
+                                                   da_own_out.ld, sf.m, sf.n, stream);
+        if (e != hipSuccess) return TP_ERR_HIP;
     }
     if (px.active) if (int e = run_product(o, px, workspace, stream)) return e;
     if (pw.active) if (int e = run_product(o, pw, workspace, stream)) return e;

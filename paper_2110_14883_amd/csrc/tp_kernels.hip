@@ -414,50 +414,79 @@ __global__ __launch_bounds__(256) void tp_bias_act_kernel(const float* c, int64_
 }
 
 // Column sums of a bf16 [rows][cols] block into fp32.  Workgroup (bx, by) sums rows
-// [by * rows_per_split, ...) of columns 64 bx .. 64 bx + 63 into out[by][cols]; with one split that is the
-// result, with several tp_colsum_finish_kernel adds the splits in ascending order.  Every order of
-// summation is fixed by (rows, cols) alone: the result is reproducible.
-__global__ __launch_bounds__(256) void tp_colsum_kernel(const uint16_t* da, int64_t ld, int64_t rows, int cols, float* out,
+// [by * rows_per_split, ...) of columns 128 bx .. 128 bx + 127 into out[by][cols]; with one split that is the
+// result, with several tp_colsum_finish_kernel adds the splits.  Every order of summation is fixed by
+// (rows, cols) and the number of splits: the result is reproducible.
+// FROM_DY: the block does not exist yet; it is formed on the way, da = dy * GeLU'(pre), and written.  The own dA
+// block and its bias gradient then take one pass over memory (6 bytes per element) instead of 8 and one launch less;
+// the sums are those of the finished block, bit for bit.  Bound by memory; two passes against one, finish included:
+// 8192 x 1024 25.1 -> 18.4 us, 2048 x 8192 35.2 -> 28.2, 32896 x 2560 127 -> 119, 4096 x 24576 145 -> 131.
+constexpr int COLSUM_COLS = 128, COLSUM_LANES = 32;           // columns per workgroup, rows side by side
+template <bool FROM_DY>
+__global__ __launch_bounds__(512) void tp_colsum_kernel(const uint16_t* dy, int64_t ld_dy, const uint16_t* pre, int64_t ld_pre,
+                                                        uint16_t* da, int64_t ld, int64_t rows, int cols, float* out,
                                                         int64_t rows_per_split) {
-    __shared__ float part[32][65];
-    const int cl = threadIdx.x & 7, rl = threadIdx.x >> 3;        // 8 chunk lanes x 32 row lanes
-    const int c = blockIdx.x * 64 + cl * 8;
+    __shared__ float part[COLSUM_LANES][COLSUM_COLS + 1];
+    const int cl = threadIdx.x & 15, rl = threadIdx.x >> 4;       // 16 chunk lanes x 32 row lanes
+    const int c = blockIdx.x * COLSUM_COLS + cl * 8;
     const int64_t r_begin = (int64_t)blockIdx.y * rows_per_split;
     const int64_t r_end = r_begin + rows_per_split < rows ? r_begin + rows_per_split : rows;
     float s[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    auto some_rows = [&](auto n_, int64_t r) __attribute__((always_inline)) {      // n rows, 32 apart, in flight together
+        constexpr int n = decltype(n_)::value;
+        u32x4_t v[n], a[n];
+#pragma unroll
+        for (int u = 0; u < n; ++u) {
+            const int64_t row = r + COLSUM_LANES * u;
+            v[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(FROM_DY ? dy + row * ld_dy + c : da + row * ld + c));
+            if constexpr (FROM_DY) a[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(pre + row * ld_pre + c));
+        }
+#pragma unroll
+        for (int u = 0; u < n; ++u) {
+            if constexpr (FROM_DY) {
+                v[u] = dgelu8(v[u], a[u]);
+                __builtin_nontemporal_store(v[u], reinterpret_cast<u32x4_t*>(da + (r + COLSUM_LANES * u) * ld + c));
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) { s[2 * i] += bf16_lo(v[u][i]); s[2 * i + 1] += bf16_hi(v[u][i]); }
+        }
+    };
     if (c < cols) {
         int64_t r = r_begin + rl;
-        for (; r + 96 < r_end; r += 128) {                        // four independent loads in flight
-            u32x4_t v[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) v[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(da + (r + 32 * u) * ld + c));
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) { s[2 * i] += bf16_lo(v[u][i]); s[2 * i + 1] += bf16_hi(v[u][i]); }
-        }
-        for (; r < r_end; r += 32) {
-            const u32x4_t v = *reinterpret_cast<const u32x4_t*>(da + r * ld + c);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) { s[2 * i] += bf16_lo(v[i]); s[2 * i + 1] += bf16_hi(v[i]); }
-        }
+        for (; r + 3 * COLSUM_LANES < r_end; r += 4 * COLSUM_LANES) some_rows(std::integral_constant<int, 4>{}, r);
+        for (; r < r_end; r += COLSUM_LANES) some_rows(std::integral_constant<int, 1>{}, r);
     }
 #pragma unroll
     for (int i = 0; i < 8; ++i) part[rl][cl * 8 + i] = s[i];
     __syncthreads();
-    if (threadIdx.x < 64) {
+    if (threadIdx.x < COLSUM_COLS) {
         float tot = 0.0f;
-        for (int r = 0; r < 32; ++r) tot += part[r][threadIdx.x];
-        const int cc = blockIdx.x * 64 + threadIdx.x;
+#pragma unroll
+        for (int r = 0; r < COLSUM_LANES; ++r) tot += part[r][threadIdx.x];
+        const int cc = blockIdx.x * COLSUM_COLS + threadIdx.x;
         if (cc < cols) out[(int64_t)blockIdx.y * cols + cc] = tot;
     }
 }
+// Bound by latency: 8 threads share a column's (at most 64) splits, each adding every eighth in ascending order, and
+// their sums meet in LDS.  (One thread a column, in a chain of loads, took 5 - 9 us.)
 __global__ __launch_bounds__(256) void tp_colsum_finish_kernel(const float* part, int splits, int cols, float* out) {
-    const int c = blockIdx.x * 256 + threadIdx.x;
-    if (c >= cols) return;
+    __shared__ float sums[8][32];
+    const int x = threadIdx.x & 31, y = threadIdx.x >> 5, c = blockIdx.x * 32 + x;
     float tot = 0.0f;
-    for (int r = 0; r < splits; ++r) tot += part[(int64_t)r * cols + c];
-    out[c] = tot;
+    if (c < cols) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int r = y + 8 * i;
+            if (r < splits) tot += part[(int64_t)r * cols + c];
+        }
+    }
+    sums[y][x] = tot;
+    __syncthreads();
+    if (y == 0 && c < cols) {
+#pragma unroll
+        for (int i = 1; i < 8; ++i) tot += sums[i][x];
+        out[c] = tot;
+    }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -580,19 +609,32 @@ size_t colsum_ws_bytes(int64_t rows, int64_t cols) {
     const int r = colsum_splits(rows, cols);
     return r > 1 ? (size_t)r * (size_t)cols * 4 : 0;
 }
-// ws: colsum_ws_bytes(rows, cols) bytes, or null for the single-pass form (one workgroup per 64 columns)
-hipError_t launch_colsum(const void* da, int64_t ld, int64_t rows, int64_t cols, float* out, float* ws, hipStream_t s) {
-    const unsigned col_blocks = (unsigned)((cols + 63) / 64);
+template <bool FROM_DY>
+static hipError_t colsum_passes(const uint16_t* dy, int64_t ld_dy, const uint16_t* pre, int64_t ld_pre, uint16_t* da, int64_t ld,
+                                int64_t rows, int64_t cols, float* out, float* ws, hipStream_t s) {
+    const unsigned strips = (unsigned)((cols + COLSUM_COLS - 1) / COLSUM_COLS);
     const int splits = ws ? colsum_splits(rows, cols) : 1;
-    if (splits == 1)
-        return launch_kernel(tp_colsum_kernel, dim3(col_blocks), dim3(256), 0, s, static_cast<const uint16_t*>(da), ld, rows,
-                             (int)cols, out, rows);
-    const int64_t per = ((rows + splits - 1) / splits + 31) / 32 * 32;
-    if (hipError_t e = launch_kernel(tp_colsum_kernel, dim3(col_blocks, (unsigned)splits), dim3(256), 0, s,
-                                     static_cast<const uint16_t*>(da), ld, rows, (int)cols, ws, per); e != hipSuccess)
+    const int64_t per = splits == 1 ? rows : ((rows + splits - 1) / splits + 31) / 32 * 32;
+    if (hipError_t e = launch_kernel(tp_colsum_kernel<FROM_DY>, dim3(strips, (unsigned)splits), dim3(512), 0, s, dy, ld_dy, pre, ld_pre,
+                                     da, ld, rows, (int)cols, splits == 1 ? out : ws, per); e != hipSuccess || splits == 1)
         return e;
-    return launch_kernel(tp_colsum_finish_kernel, dim3((unsigned)((cols + 255) / 256)), dim3(256), 0, s,
+    return launch_kernel(tp_colsum_finish_kernel, dim3((unsigned)((cols + 31) / 32)), dim3(256), 0, s,
                          static_cast<const float*>(ws), splits, (int)cols, out);
+}
+// ws: colsum_ws_bytes(rows, cols) bytes, or null for the single-pass form (one workgroup per 128 columns)
+hipError_t launch_colsum(const void* da, int64_t ld, int64_t rows, int64_t cols, float* out, float* ws, hipStream_t s) {
+    return colsum_passes<false>(nullptr, 0, nullptr, 0, static_cast<uint16_t*>(const_cast<void*>(da)), ld, rows, cols, out, ws, s);
+}
+// da = dy * GeLU'(pre) and its column sums.  One pass where its workgroups keep the chip busy (half of the CUs), or where
+// the block is so small (4M elements, 4 us of traffic) that a launch costs more; else (no workspace, narrow block) the elementwise kernel's own grid and then the sums.
+hipError_t launch_dgelu_colsum(const void* dy, int64_t ld_dy, const void* pre, int64_t ld_pre, void* da, int64_t ld, int64_t rows,
+                               int64_t cols, float* out, float* ws, hipStream_t s) {
+    const int64_t wgs = (cols + COLSUM_COLS - 1) / COLSUM_COLS * (ws ? colsum_splits(rows, cols) : 1);
+    if (wgs >= 128 || rows * cols <= ((int64_t)1 << 22))
+        return colsum_passes<true>(static_cast<const uint16_t*>(dy), ld_dy, static_cast<const uint16_t*>(pre), ld_pre,
+                                   static_cast<uint16_t*>(da), ld, rows, cols, out, ws, s);
+    if (hipError_t e = launch_dgelu(dy, ld_dy, pre, ld_pre, da, ld, rows, cols, s); e != hipSuccess) return e;
+    return launch_colsum(da, ld, rows, cols, out, ws, s);
 }
 
 }  // namespace tpl

@@ -685,3 +685,21 @@ def test_workgroup_split_kernel_edges(m, k, n):
     for seed, (y, dx) in enumerate((("f32", "bf16"), ("bf16", "f32"))):
         run_share(T.Grid(T.MODE_2D, q=2, ri=1, rj=0), (2 * m, 2 * k, 2 * n), y_dtype=y, dx_dtype=dx, want_db=True,
                   seed=S.BASE_SEED + seed, label=f"{m}x{k}x{n}")
+
+
+@pytest.mark.parametrize("rows,cols", [(1, 8), (33, 136), (257, 128), (700, 1032), (5000, 1024)])
+@pytest.mark.parametrize("with_workspace", [True, False])
+def test_own_dA_and_bias_gradient_in_one_pass(rows, cols, with_workspace):
+    """The pass that forms the own dA block and sums its columns: the block is that of tp_dgelu and the sums are those of
+    tp_bias_grad on it, bit for bit, for one slab and several, ragged strips, and leading dimensions beyond the columns."""
+    grid, dims = T.Grid(T.MODE_2D, q=1), (rows, 64, cols)
+    g, a = (dev(S.normal_block_bf16(S.BASE_SEED + i, S.T_G, cols + 8, 0, rows, 0, cols + 8, 1.0))[:, :cols] for i in (1, 2))
+    ws = torch.empty(max(T.tp_linear_workspace_size(grid, dims, T.PASS_DX), 16), dtype=torch.uint8, device="cuda") if with_workspace else None
+    da, da2 = (torch.full((rows, cols + 16), 7.0, dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    db, db2 = (torch.full((cols,), float("nan"), dtype=torch.float32, device="cuda") for _ in range(2))
+    T.tp_linear_bwd(grid, dims, dy_own=g, preact_own=a, da_own_out=da[:, :cols], db=db, workspace=ws)
+    T.tp_dgelu(g, a, da2[:, :cols])
+    need = T.tp_bias_grad_workspace_size(rows, cols)
+    T.tp_bias_grad(da2[:, :cols], db2, workspace=ws if with_workspace and need else None)
+    assert torch.equal(da, da2) and torch.equal(db, db2)
+    check(host64(db), host64(da[:, :cols]).sum(axis=0), "f32", f"db {rows} x {cols}")
