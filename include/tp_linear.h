@@ -85,11 +85,12 @@ typedef struct { void* ptr; int64_t ld; int dtype; } tp_oblk_t;
 /* Launch-plan options of one call (tuning and tests; NULL = all automatic).  The same options must be
  * given to the workspace query and to the call it sizes.
  *   tile   : macro-tile of C.  0 automatic; 1 = 256x256 (four-wave stream kernel); 2 = 128x256,
- *            3 = 256x128, 4 = 128x128 (eight-wave kernel); 5 = 256x256 on the eight-wave kernel.
+ *            3 = 256x128, 4 = 128x128 (four-wave kernel with a ring of stages); 5 = 256x256 on the
+ *            eight-wave kernel.
  *   split_k: workgroups sharing one C tile along K.  0 automatic, 1..8.
  *   group_m: height, in tile rows, of the groups of the tile order.  0 automatic, 1..64.
  *   rotate : rotate the K-tile order inside a step from C tile to C tile.  0 automatic (on for the
- *            eight-wave kernel, off for the four-wave one), 1 on, 2 off.
+ *            eight-wave kernel, off for the others), 1 on, 2 off.
  *   trim   : when the tiles are a little more than a whole number of rounds of the persistent
  *            workgroups, run the last tile rows as a second, smaller launch.  0 automatic (on), 1 on, 2 off. */
 typedef struct { int tile, split_k, group_m, rotate, trim; } tp_plan_opts_t;

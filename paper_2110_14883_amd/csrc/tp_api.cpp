@@ -265,16 +265,16 @@ Plan plan_by(const Costs& cs, const Opts& o, int64_t m, int64_t n, int64_t k, in
 }
 
 // The same for the kernel that splits K over the waves of a workgroup (no partial planes, one launch): `wgs`
-// workgroups, T chunks of 64 k each.  Fitted to 22 shapes, each form, up to 512 workgroups and 64 chunks (replayed
-// graphs): 3 us per launch, then per round of 256 workgroups 0.6 - 1.2 us and 0.11 - 0.25 us a chunk.  Measured on
-// both sides: 128 x 2048 x 512, 2 steps, forward 6.7 us against 14.0 (128 x 128, split 4 and fix-up); 300 x 328 x 136, 2
-// steps 4.4 / 4.8 / 5.2 us against 10.0 / 9.4 / 8.2; beyond, the larger tiles' reuse of operands wins: 64 x 4096 x 4096
-// 16.5 us against 15.3, 1024 x 256 x 1024 dX 10.1 against 6.5.
-double small_cost(int form, int bm, int64_t wgs, int64_t T) {
-    if (wgs > 2 * kCUs || T > 64) return 1e300;
-    const double chunk = form == FORM_TN ? 200.0 : (form == FORM_NN ? (bm == 16 ? 255.0 : 345.0) : (bm == 16 ? 310.0 : 455.0));
-    const double round = form == FORM_TN ? 2200.0 : 1100.0;
-    return 5500.0 + (double)((wgs + kCUs - 1) / kCUs) * (round + chunk * (double)T);
+// workgroups, T chunks of 64 k each.  Fitted to 22 shapes, each form, up to 512 workgroups and 64 (NN) or 256 chunks
+// (replayed graphs): 2 - 2.5 us per launch, then per round of 256 workgroups 1.6 - 1.9 us and 0.06 - 0.12 us a chunk.
+// Both sides: 128 x 2048 x 512, 2 steps, forward 5.2 us against 14.0 (128 x 128, split 4 and fix-up); 300 x 328 x 136, 2 steps
+// 4.7 / 4.4 / 4.3 us against 10.0 / 9.4 / 8.2; 64 x 4096 x 4096 dX 9.8 against 14.4.  Beyond, the larger tiles' reuse of
+// operands wins: 1024 x 256 x 1024 dX (1024 workgroups) 11.3 against 6.5, 16 x 16384 x 4096 forward 27.1 against 27.4.
+double small_cost(int form, int64_t wgs, int64_t T) {
+    if (wgs > 2 * kCUs || T > (form == FORM_NN ? 64 : 256)) return 1e300;
+    const double launch = form == FORM_NN ? 4500.0 : 3600.0, round = form == FORM_TN ? 3450.0 : 2900.0;
+    const double chunk = form == FORM_NN ? 220.0 : (form == FORM_NT ? 137.0 : 110.0);
+    return launch + (double)((wgs + kCUs - 1) / kCUs) * (round + chunk * (double)T);
 }
 
 Plan make_plan(const Opts& o, int form, int64_t m, int64_t n, int64_t k, int n_steps, int groups = 1) {
@@ -284,7 +284,7 @@ Plan make_plan(const Opts& o, int form, int64_t m, int64_t n, int64_t k, int n_s
     if (!o.tile && !o.split) {
         const int bm = m <= 16 && form != FORM_TN ? 16 : 32;
         const int64_t tm = (m + bm - 1) / bm, tn = (n + 31) / 32;
-        if (1.1 * small_cost(form, bm, tm * tn * groups, (int64_t)n_steps * ((k + 63) / 64)) < cost)
+        if (1.1 * small_cost(form, tm * tn * groups, (int64_t)n_steps * ((k + 63) / 64)) < cost)
             p = Plan{bm == 16 ? TILE_16x32_SMALL : TILE_32x32_SMALL, bm, 32, (int)tm, (int)tn, 1, o.group > 0 ? o.group : 4, groups, 0, 0, 0, 0, 0, 0};
     }
     p.need = need;

@@ -3,8 +3,8 @@
 // 3D schemes, C = sum_k A_k B_k over the steps, then bias + erf-GeLU; and the two backward
 // products).  bf16 operands, fp32 accumulation in MFMA 32x32x16 tiles.
 //
-// The eight-wave GEMM of this file serves the 128 x 256, 256 x 128 and 128 x 128 macro-tiles (and 256 x 256
-// on request), the rest of the file the split-K fix-up and the elementwise kernels.  One kernel template
+// The eight-wave GEMM of this file serves operands that the 32-bit offsets of the other GEMM kernels cannot reach (and
+// 256 x 256 tiles on request); the rest of the file holds the split-K fix-up and the elementwise kernels.  One kernel template
 // serves the three memory forms (NN forward, NT dX, TN dW):
 //   * persistent workgroups (one per CU) of 8 wave64 walk over the BM x BN tiles of C; a tile's
 //     accumulators stay in registers across ALL steps and all K tiles -- no partial C leaves the

@@ -3,20 +3,26 @@
 //
 //   * bound: latency (small products) or the stream of the weights (a handful of token rows), never MFMA.  So the
 //     macro-tile is small, 32 x 32 (16 x 32 for at most 16 rows), which gives every CU one, and K is split over the
-//     16 waves of the WORKGROUP: the partial sums meet in LDS, in a fixed order, and the epilogue follows in the
+//     eight waves of the WORKGROUP: the partial sums meet in LDS, in a fixed order, and the epilogue follows in the
 //     same launch -- no partial planes, no second kernel;
-//   * no LDS staging and no barrier in the K loop: a wave loads its own fragments, 2 chunks of 64 k (whole 128-byte
-//     lines of a contraction-contiguous operand) ahead of their
-//     MFMAs (16 x 16 x 32).  A contraction-contiguous operand comes as 16 bytes per lane, which is a fragment; of
-//     the other kind a lane takes 2 columns x 8 rows of k (dwords, a row of 16 lanes is 64 contiguous bytes) and
-//     byte permutes make two fragments of them, whose column c is column 2 c + i of the tile;
-//   * waves take the chunks in turn (wave w: w, w + 16, ...), across the steps of the sum.
+//   * waves take the chunks of 64 k in turn (wave w: w, w + 8, ...), across the steps of the sum, and work alone until
+//     the end: each has its own ring of LDS slots, filled by direct-to-LDS loads (16 bytes a lane: 8 lines or 16
+//     half lines an instruction) one or two chunks ahead, with no barrier in the K loop.  An operand that is not
+//     contraction-contiguous is transposed on the way out, by ds_read_b64_tr_b16.
+//     (Fragments loaded straight into registers, 16 bytes of a row or 4 bytes of 8 rows a lane, kept the address path
+//     busy four times as long: 16 x 4096 x 4096 dX 13.9 us against 8.0, 512 x 1024 x 1024 dX 12.5 against 7.5, forward
+//     10.7 against 8.8.)
 #include "tp_stream.h"
 
 namespace tpl {
 
 namespace {
-constexpr int SM_WAVES = 16, SM_THREADS = 64 * SM_WAVES, SM_BN = 32, SM_UNROLL = 2;
+constexpr int SM_WAVES = 8, SM_THREADS = 64 * SM_WAVES, SM_BN = 32, SM_B_BYTES = SM_BN * 128;
+template <int MT> struct SmShape {
+    static constexpr int BM = 16 * MT, SLOT = BM * 128 + SM_B_BYTES;      // one chunk of 64 k of both operands
+    static constexpr int NS = MT == 1 ? 3 : 2, LDS_BYTES = SM_WAVES * NS * SLOT;
+    static_assert(SM_WAVES * BM * SM_BN * 4 <= LDS_BYTES && LDS_BYTES <= 163840);
+};
 }
 
 // MT: 16-row blocks of the tile (1 or 2; 2 if A is not contraction-contiguous)
@@ -24,8 +30,10 @@ template <int MT, bool A_KC, bool B_KC>
 __global__ __launch_bounds__(SM_THREADS)
 void tp_small_kernel(const GemmArgs p, const Epilogue e) {
     static_assert(MT == 2 || (MT == 1 && A_KC));
-    constexpr int BM = 16 * MT;
-    __shared__ __attribute__((aligned(16))) char red[SM_WAVES * BM * SM_BN * 4];
+    using Sh = SmShape<MT>;
+    constexpr int BM = Sh::BM, NS = Sh::NS, A_BYTES = BM * 128;
+    constexpr int LA = A_BYTES / 1024, LB = SM_B_BYTES / 1024, LPC = LA + LB;    // loads of a chunk
+    extern __shared__ __attribute__((aligned(16))) char lds[];
     const int t = threadIdx.x, l = t & 63, c = l & 15, kg = l >> 4;
     const int w = uni(t >> 6);
     int tm, tn, z, g = 0;
@@ -37,90 +45,105 @@ void tp_small_kernel(const GemmArgs p, const Epilogue e) {
     g = uni(g);
     const int m0 = uni(tm * BM), n0 = uni(tn * SM_BN);
     const int KC = (p.K + 63) / 64, T = p.n_steps * KC;           // chunks of 64 k: of a step, in all
+    const uint32_t mine = (uint32_t)(w * NS * Sh::SLOT);
 
-    // Operand fragments of 32 k.  Descriptors start at the tile's first row (column) and end with the block:
-    // rows past a ragged edge, and rows of k past the last one, read as zero; the rest is masked per lane.
-    auto load_kc = [&](u32x4_t (&r)[2], int nb, const void* ptr, int ld, int rows, int row0, int k0) __attribute__((always_inline)) {
-        const __amdgpu_buffer_rsrc_t rs = make_rsrc(uni_ptr(static_cast<const uint16_t*>(ptr) + (int64_t)row0 * ld),
-                                                    ((int64_t)(rows - row0 - 1) * ld + p.K) * 2);
-        const int k = k0 + 8 * kg;
-        const uint32_t off = k < p.K ? (uint32_t)((c * ld + k) * 2) : OOB_OFFSET;
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-            if (i < nb) r[i] = buf_load16(rs, off + (uint32_t)(16 * i * ld * 2));
+    // Descriptors start at the tile's first row (column) and end with the block: rows past a ragged edge, and rows of
+    // k past the last one, read as zero; the rest is masked per lane.
+    //   contraction-contiguous: rows of 128 bytes, chunk q of row r at q ^ ((r >> 1) & 7); load n: rows 8 n + l / 8;
+    //   otherwise: 64 rows of k of 64 bytes (32 columns), chunk q of row k at q ^ 2 ((k >> 3) & 1), so that the two
+    //     groups of 4 rows x 16 columns of a half-wave's transposing read lie in different banks; load n: rows 16 n + l / 4.
+    auto load_kc = [&](auto n_loads, const void* ptr, int ld, int rows, int row0, int k0, bool live, uint32_t dst) __attribute__((always_inline)) {
+        const uint64_t base = reinterpret_cast<uint64_t>(static_cast<const uint16_t*>(ptr) + (int64_t)row0 * ld);
+        const int64_t nrec = live ? ((int64_t)(rows - row0 - 1) * ld + p.K) * 2 : 0;
+        const u32x4_t rw = {(uint32_t)uni((int)(uint32_t)base), (uint32_t)uni((int)((uint32_t)(base >> 32) & 0xffffu)),
+                            (uint32_t)uni((int)(uint32_t)nrec), 0x00020000u};
+        static_for<decltype(n_loads)::value>([&](auto n_) __attribute__((always_inline)) {
+            constexpr int n = decltype(n_)::value;
+            const int r = 8 * n + (l >> 3), k = k0 + (((l & 7) ^ ((r >> 1) & 7)) << 3);
+            dtl_load16(rw, k < p.K ? (uint32_t)((r * ld + k) * 2) : OOB_OFFSET, dst + n * 1024);
+        });
     };
-    auto load_xc = [&](uint32_t (&r)[8], const void* ptr, int ld, int X, int x0, int k0) __attribute__((always_inline)) {
-        const __amdgpu_buffer_rsrc_t rs = make_rsrc(uni_ptr(static_cast<const uint16_t*>(ptr) + x0),
-                                                    ((int64_t)(p.K - 1) * ld + (X - x0)) * 2);
-        const uint32_t off = x0 + 2 * c < X ? (uint32_t)(((k0 + 8 * kg) * ld + 2 * c) * 2) : OOB_OFFSET;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) r[j] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rs, (int)(off + (uint32_t)(j * ld * 2)), 0, 0);
+    auto load_xc = [&](const void* ptr, int ld, int X, int x0, int k0, bool live, uint32_t dst) __attribute__((always_inline)) {
+        const uint64_t base = reinterpret_cast<uint64_t>(static_cast<const uint16_t*>(ptr) + x0);
+        const int64_t nrec = live ? ((int64_t)(p.K - 1) * ld + (X - x0)) * 2 : 0;
+        const u32x4_t rw = {(uint32_t)uni((int)(uint32_t)base), (uint32_t)uni((int)((uint32_t)(base >> 32) & 0xffffu)),
+                            (uint32_t)uni((int)(uint32_t)nrec), 0x00020000u};
+        const int x = ((l & 3) ^ (2 * (l >> 5))) * 8;
+        const uint32_t off = x0 + x < X ? (uint32_t)(((k0 + (l >> 2)) * ld + x) * 2) : OOB_OFFSET;
+        static_for<4>([&](auto n_) __attribute__((always_inline)) {
+            constexpr int n = decltype(n_)::value;
+            dtl_load16(rw, off + (uint32_t)(32 * n * ld), dst + n * 1024);
+        });
     };
-    auto frag_xc = [&](const uint32_t (&r)[8], int i) __attribute__((always_inline)) {
-        const uint32_t sel = i ? 0x07060302u : 0x05040100u;
-        const u32x4_t v = {__builtin_amdgcn_perm(r[1], r[0], sel), __builtin_amdgcn_perm(r[3], r[2], sel),
-                           __builtin_amdgcn_perm(r[5], r[4], sel), __builtin_amdgcn_perm(r[7], r[6], sel)};
-        return __builtin_bit_cast(bf16x8_t, v);
+    int step = 0, kc = w;                                          // the next chunk to fetch, as (step, chunk of the step)
+    while (kc >= KC && step < p.n_steps) { kc -= KC; ++step; }
+    auto fetch = [&](auto slot) __attribute__((always_inline)) {   // (past the end: empty descriptors, zeros nobody uses)
+        const bool live = step < p.n_steps;
+        const int s = uni((live ? step : p.n_steps - 1) + g), k0 = uni(kc * 64);
+        const uint32_t dst = mine + decltype(slot)::value * Sh::SLOT;
+        if constexpr (A_KC) load_kc(std::integral_constant<int, LA>{}, p.a[s], uni(p.lda[s]), p.M, m0, k0, live, dst);
+        else                load_xc(p.a[s], uni(p.lda[s]), p.M, m0, k0, live, dst);
+        if constexpr (B_KC) load_kc(std::integral_constant<int, LB>{}, p.b[s], uni(p.ldb[s]), p.N, n0, k0, live, dst + A_BYTES);
+        else                load_xc(p.b[s], uni(p.ldb[s]), p.N, n0, k0, live, dst + A_BYTES);
+        kc += SM_WAVES;
+        while (kc >= KC && step < p.n_steps) { kc -= KC; ++step; }
+        if (step >= p.n_steps) kc = 0;
     };
-
+    // fragment (16 rows or columns, block i) x (32 k, half h)
+    auto frag = [&](auto kc_form, uint32_t at, int i, int h) __attribute__((always_inline)) {
+        if constexpr (decltype(kc_form)::value) {
+            const int r = 16 * i + c;
+            return lds_load_frag(at + r * 128 + (((4 * h + kg) ^ ((r >> 1) & 7)) << 4));
+        } else {
+            const int k = 32 * h + 8 * kg + (c >> 2);              // and k + 4
+            const uint32_t a = at + k * 64 + ((2 * i ^ 2 * (kg & 1)) << 4) + 8 * (l & 3);
+            const bf16x4_t lo = lds_load_tr(a), hi = lds_load_tr(a + 256);
+            return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+        }
+    };
     f32x4_t acc[MT][2];
 #pragma unroll
     for (int i = 0; i < MT; ++i) acc[i][0] = acc[i][1] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-    int step = 0, kc = w;                                          // chunk w, as (step, chunk of the step)
-    while (kc >= KC && step < p.n_steps) { kc -= KC; ++step; }
-    for (int u = w; u < T; u += SM_WAVES * SM_UNROLL) {
-        u32x4_t a_kc[2 * SM_UNROLL][2], b_kc[2 * SM_UNROLL][2];
-        uint32_t a_xc[2 * SM_UNROLL][8], b_xc[2 * SM_UNROLL][8];
+    auto one_chunk = [&](auto slot_) __attribute__((always_inline)) {
+        constexpr int slot = decltype(slot_)::value;
+        // the slot to refill was read one chunk ago: its fragments have arrived
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        fetch(std::integral_constant<int, (slot + NS - 1) % NS>{});
+        wait_vm<(NS - 1) * LPC>();                                 // this wave's own loads: no barrier
+        asm volatile("" ::: "memory");
+        const uint32_t at = mine + slot * Sh::SLOT;
 #pragma unroll
-        for (int n = 0; n < 2 * SM_UNROLL; ++n) {
-            // (a chunk past the end lies at K or beyond: every lane is masked, or past the descriptor's end)
-            const int s = uni((step < p.n_steps ? step : p.n_steps - 1) + g);
-            const int k0 = uni((step < p.n_steps ? kc : KC) * 64 + 32 * (n & 1));
-            const int lda = uni(p.lda[s]), ldb = uni(p.ldb[s]);
-            if constexpr (A_KC) load_kc(a_kc[n], MT, p.a[s], lda, p.M, m0, k0); else load_xc(a_xc[n], p.a[s], lda, p.M, m0, k0);
-            if constexpr (B_KC) load_kc(b_kc[n], 2, p.b[s], ldb, p.N, n0, k0);  else load_xc(b_xc[n], p.b[s], ldb, p.N, n0, k0);
-            if (n & 1) {
-                kc += SM_WAVES;
-                while (kc >= KC && step < p.n_steps) { kc -= KC; ++step; }
-            }
-        }
-#pragma unroll
-        for (int n = 0; n < 2 * SM_UNROLL; ++n) {
+        for (int h = 0; h < 2; ++h) {
             bf16x8_t fb[2];
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                if constexpr (B_KC) fb[j] = __builtin_bit_cast(bf16x8_t, b_kc[n][j]); else fb[j] = frag_xc(b_xc[n], j);
-            }
+            for (int j = 0; j < 2; ++j) fb[j] = frag(std::integral_constant<bool, B_KC>{}, at + A_BYTES, j, h);
 #pragma unroll
             for (int i = 0; i < MT; ++i) {
-                bf16x8_t fa;
-                if constexpr (A_KC) fa = __builtin_bit_cast(bf16x8_t, a_kc[n][i]); else fa = frag_xc(a_xc[n], i);
+                const bf16x8_t fa = frag(std::integral_constant<bool, A_KC>{}, at, i, h);
 #pragma unroll
                 for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j], fa, acc[i][j], 0, 0, 0);
             }
         }
-    }
+    };
+    static_for<NS - 1>([&](auto s_) __attribute__((always_inline)) { fetch(s_); });
+    for (int u = w; u < T; u += SM_WAVES * NS)                     // (a chunk past the end of the last round is zeros)
+        static_for<NS>([&](auto s_) __attribute__((always_inline)) { one_chunk(s_); });
 
-    // The operands are swapped (C^T = B^T A^T): a lane holds column block c's row of C.  acc[i][j][q]:
-    // row 16 i + c (A contraction-contiguous) or 2 c + i, column 16 j + 4 kg + q or 8 kg + 2 q + j.
+    // The operands are swapped (C^T = B^T A^T): acc[i][j][q] is row 16 i + c, column 16 j + 4 kg + q of the tile.
     // LDS: per wave BM rows of 128 bytes, 16-byte chunk n of row r at n ^ (r & 7).
-    char* const mine = red + w * (BM * SM_BN * 4);
+    wait_vm<0>();
+    __syncthreads();
 #pragma unroll
     for (int i = 0; i < MT; ++i) {
-        const int r = A_KC ? 16 * i + c : 2 * c + i;
+        const int r = 16 * i + c;
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int n = B_KC ? 4 * h + kg : 2 * kg + h;
-            f32x4_t v;
-            if constexpr (B_KC) v = acc[i][h];
-            else                v = f32x4_t{acc[i][0][2 * h], acc[i][1][2 * h], acc[i][0][2 * h + 1], acc[i][1][2 * h + 1]};
-            *reinterpret_cast<f32x4_t*>(mine + r * 128 + ((n ^ (r & 7)) << 4)) = v;
-        }
+        for (int j = 0; j < 2; ++j)
+            *reinterpret_cast<f32x4_t*>(lds + w * (BM * SM_BN * 4) + r * 128 + (((4 * j + kg) ^ (r & 7)) << 4)) = acc[i][j];
     }
     __syncthreads();
     if (t < BM * 8) {
         const int r = t >> 3, n = t & 7, row = m0 + r, col = n0 + 4 * n;
-        const char* const at = red + r * 128 + ((n ^ (r & 7)) << 4);
+        const char* const at = lds + r * 128 + ((n ^ (r & 7)) << 4);
         f32x4_t sum = *reinterpret_cast<const f32x4_t*>(at);
 #pragma unroll
         for (int i = 1; i < SM_WAVES; ++i) {
@@ -138,8 +161,19 @@ void tp_small_kernel(const GemmArgs p, const Epilogue e) {
 
 template <int MT, bool A_KC, bool B_KC>
 static hipError_t launch_small_one(const GemmArgs& a, hipStream_t s) {
+    static std::atomic<uint64_t> attr_done{0};
+    constexpr int lds_bytes = SmShape<MT>::LDS_BYTES;
+    int dev = 0;
+    if (hipError_t err = hipGetDevice(&dev); err != hipSuccess) return err;
+    const uint64_t bit = 1ull << (dev & 63);
+    if (!(attr_done.load(std::memory_order_relaxed) & bit)) {
+        hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(&tp_small_kernel<MT, A_KC, B_KC>),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
+        if (err != hipSuccess) return err;
+        attr_done.fetch_or(bit, std::memory_order_relaxed);
+    }
     const Epilogue e{a.out, a.ldo, a.out_f32, a.pre, a.ldp, a.bias, a.gelu, a.dg, a.lddg};
-    return launch_kernel(tp_small_kernel<MT, A_KC, B_KC>, dim3((unsigned)(a.tiles_m * a.tiles_n)), dim3(SM_THREADS), 0, s, a, e);
+    return launch_kernel(tp_small_kernel<MT, A_KC, B_KC>, dim3((unsigned)(a.tiles_m * a.tiles_n)), dim3(SM_THREADS), lds_bytes, s, a, e);
 }
 
 hipError_t launch_small(int form, int tile_id, const GemmArgs& a, hipStream_t s) {

@@ -703,3 +703,21 @@ def test_own_dA_and_bias_gradient_in_one_pass(rows, cols, with_workspace):
     T.tp_bias_grad(da2[:, :cols], db2, workspace=ws if with_workspace and need else None)
     assert torch.equal(da, da2) and torch.equal(db, db2)
     check(host64(db), host64(da[:, :cols]).sum(axis=0), "f32", f"db {rows} x {cols}")
+
+
+def test_small_product_with_a_leading_dimension_beyond_32_bit_offsets():
+    """A product small enough for the workgroup-split kernel whose weight rows lie so far apart that its 32-bit offsets
+    cannot reach the last one: it runs on the eight-wave kernel, against the same blocks packed tightly."""
+    m, k, n, ld = 24, 4096, 40, 1 << 18
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(11)
+    x = torch.randn((m, k), generator=gen, device="cuda").to(torch.bfloat16)
+    w = torch.randn((k, n), generator=gen, device="cuda").mul_(0.02).to(torch.bfloat16)
+    wide = torch.empty((k, ld), dtype=torch.bfloat16, device="cuda")[:, :n]
+    wide.copy_(w)
+    bias = torch.randn((n,), generator=gen, device="cuda").to(torch.bfloat16)
+    ref = O.share_fwd([host64(x)], [host64(w)], host64(bias))[1]
+    for weights in (w, wide):
+        y = torch.empty((m, n), dtype=torch.float32, device="cuda")
+        T.tp_linear_fwd(T.Grid(T.MODE_2D, q=1), (m, k, n), 1, [x], [weights], bias, T.EPI_BIAS_GELU, y, None, workspace_for(T.Grid(T.MODE_2D, q=1), (m, k, n)))
+        check(host64(y), ref, "f32", f"ld {weights.stride(0)}")
