@@ -243,6 +243,12 @@ void tp_gemm4_kernel(const GemmArgs p) {
     //     then the cursor moves on, and after the barrier operand A of the following K tile goes into the
     //     stage this body has just finished reading.  All four waves run the same schedule, so a slot with
     //     a load asks the CU's one address path for 4 KB (64 B/clk: two slots): loads every other slot.
+    //   In the NN form operand A comes late instead, a load every fourth slot: where its rows do not start on cache
+    //   lines, each of its loads asks for 16 lines and not 8 (four slots of the address path), and bunched loads hold up
+    //   the MFMAs behind them.  8192 x 4096, K = 12528: 728 -> 690 us (NN), K = 4880: 647 -> 625; aligned rows take the same.
+    constexpr bool A_LATE = A_KC && !B_KC;
+    using Late = std::integral_constant<bool, A_LATE>;
+    using Early = std::integral_constant<bool, !A_LATE>;
     auto k_tile = [&](auto S_) __attribute__((always_inline)) {
         constexpr int S = decltype(S_)::value;
         using SR = std::integral_constant<int, S>;          // stage read
@@ -263,8 +269,9 @@ void tp_gemm4_kernel(const GemmArgs p) {
             if constexpr (NR == 8)       { if constexpr (q % 2 == 0) read_n(std::integral_constant<int, q / 2>{}, KN{}, ST{}); }
             else if constexpr (NR == 12) { if constexpr (q % 4 != 3) read_n(std::integral_constant<int, q - q / 4>{}, KN{}, ST{}); }
             else                         read_n(std::integral_constant<int, q>{}, KN{}, ST{});
-            if constexpr ((s & 1) == 1 && s < 16) dtl1(std::false_type{}, std::integral_constant<int, s / 2>{}, SW{});
-            if constexpr ((s & 1) == 1 && s > 48) dtl1(std::true_type{}, std::integral_constant<int, (s - 49) / 2>{}, SR{});
+            if constexpr (A_LATE) { if constexpr ((s & 3) == 1 && s < 32) dtl1(Late{}, std::integral_constant<int, s / 4>{}, SW{}); }
+            else                  { if constexpr ((s & 1) == 1 && s < 16) dtl1(Late{}, std::integral_constant<int, s / 2>{}, SW{}); }
+            if constexpr ((s & 1) == 1 && s > 48) dtl1(Early{}, std::integral_constant<int, (s - 49) / 2>{}, SR{});
             if constexpr (s == 38) advance_fast();
             if constexpr (s == 40) { if (f_reopen) advance_slow(); }
             if constexpr (s == 42) prep_tile();
@@ -288,7 +295,7 @@ void tp_gemm4_kernel(const GemmArgs p) {
     advance_fast();
     if (f_reopen) advance_slow();
     prep_tile();
-    static_for<8>([&](auto n_) __attribute__((always_inline)) { dtl1(std::true_type{}, n_, S1{}); });
+    static_for<8>([&](auto n_) __attribute__((always_inline)) { dtl1(Early{}, n_, S1{}); });
     wait_vm<8>();
     __syncthreads();
     static_for<NR>([&](auto n_) __attribute__((always_inline)) { read_n(n_, S0{}, S0{}); });
