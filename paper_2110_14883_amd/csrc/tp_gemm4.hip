@@ -243,9 +243,11 @@ void tp_gemm4_kernel(const GemmArgs p) {
     //     then the cursor moves on, and after the barrier operand A of the following K tile goes into the
     //     stage this body has just finished reading.  All four waves run the same schedule, so a slot with
     //     a load asks the CU's one address path for 4 KB (64 B/clk: two slots): loads every other slot.
-    //   In the NN form operand A comes late instead, a load every fourth slot: where its rows do not start on cache
-    //   lines, each of its loads asks for 16 lines and not 8 (four slots of the address path), and bunched loads hold up
-    //   the MFMAs behind them.  8192 x 4096, K = 12528: 728 -> 690 us (NN), K = 4880: 647 -> 625; aligned rows take the same.
+    //   Where the rows of a contraction-contiguous operand do not start on cache lines, each of its loads asks for 16 lines
+    //   and not 8 (four slots of the address path), and bunched loads hold up the MFMAs behind them: in the NN form
+    //   operand A is the late one, and in both forms with such an A the late operand has a load every fourth slot.
+    //   8192 x 4096, K = 12528: 728 -> 690 us (NN); 19633 x 3424, K = 4880: 647 -> 625 (NN), 658 -> 640 (NT); aligned rows
+    //   gain up to 1 %.
     constexpr bool A_LATE = A_KC && !B_KC;
     using Late = std::integral_constant<bool, A_LATE>;
     using Early = std::integral_constant<bool, !A_LATE>;
@@ -269,7 +271,7 @@ void tp_gemm4_kernel(const GemmArgs p) {
             if constexpr (NR == 8)       { if constexpr (q % 2 == 0) read_n(std::integral_constant<int, q / 2>{}, KN{}, ST{}); }
             else if constexpr (NR == 12) { if constexpr (q % 4 != 3) read_n(std::integral_constant<int, q - q / 4>{}, KN{}, ST{}); }
             else                         read_n(std::integral_constant<int, q>{}, KN{}, ST{});
-            if constexpr (A_LATE) { if constexpr ((s & 3) == 1 && s < 32) dtl1(Late{}, std::integral_constant<int, s / 4>{}, SW{}); }
+            if constexpr (A_KC) { if constexpr ((s & 3) == 1 && s < 32) dtl1(Late{}, std::integral_constant<int, s / 4>{}, SW{}); }
             else                  { if constexpr ((s & 1) == 1 && s < 16) dtl1(Late{}, std::integral_constant<int, s / 2>{}, SW{}); }
             if constexpr ((s & 1) == 1 && s > 48) dtl1(Early{}, std::integral_constant<int, (s - 49) / 2>{}, SR{});
             if constexpr (s == 38) advance_fast();
