@@ -47,14 +47,18 @@ void tp_small_kernel(const GemmArgs p, const Epilogue e) {
     const int KC = (p.K + 63) / 64, T = p.n_steps * KC;           // chunks of 64 k: of a step, in all
     const uint32_t mine = (uint32_t)(w * NS * Sh::SLOT);
 
-    // Descriptors start at the tile's first row (column) and end with the block: rows past a ragged edge, and rows of
-    // k past the last one, read as zero; the rest is masked per lane.
+    // Descriptors start at the tile's first row (column).  A contraction-contiguous one ends with the tile's last row that
+    // exists: its size stays below OOB_OFFSET for every leading dimension, however many rows the matrix has.  The other kind
+    // ends with the block (the host refuses spans of 2 GiB).  So rows past a ragged edge, and rows of k past the last one,
+    // read as zero; the rest is masked per lane.
     //   contraction-contiguous: rows of 128 bytes, chunk q of row r at q ^ ((r >> 1) & 7); load n: rows 8 n + l / 8;
     //   otherwise: 64 rows of k of 64 bytes (32 columns), chunk q of row k at q ^ 2 ((k >> 3) & 1), so that the two
     //     groups of 4 rows x 16 columns of a half-wave's transposing read lie in different banks; load n: rows 16 n + l / 4.
     auto load_kc = [&](auto n_loads, const void* ptr, int ld, int rows, int row0, int k0, bool live, uint32_t dst) __attribute__((always_inline)) {
         const uint64_t base = reinterpret_cast<uint64_t>(static_cast<const uint16_t*>(ptr) + (int64_t)row0 * ld);
-        const int64_t nrec = live ? ((int64_t)(rows - row0 - 1) * ld + p.K) * 2 : 0;
+        constexpr int R = 8 * decltype(n_loads)::value;
+        const int have = rows - row0 < R ? rows - row0 : R;
+        const int64_t nrec = live ? ((int64_t)(have - 1) * ld + p.K) * 2 : 0;
         const u32x4_t rw = {(uint32_t)uni((int)(uint32_t)base), (uint32_t)uni((int)((uint32_t)(base >> 32) & 0xffffu)),
                             (uint32_t)uni((int)(uint32_t)nrec), 0x00020000u};
         static_for<decltype(n_loads)::value>([&](auto n_) __attribute__((always_inline)) {

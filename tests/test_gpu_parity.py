@@ -721,3 +721,31 @@ def test_small_product_with_a_leading_dimension_beyond_32_bit_offsets():
         y = torch.empty((m, n), dtype=torch.float32, device="cuda")
         T.tp_linear_fwd(T.Grid(T.MODE_2D, q=1), (m, k, n), 1, [x], [weights], bias, T.EPI_BIAS_GELU, y, None, workspace_for(T.Grid(T.MODE_2D, q=1), (m, k, n)))
         check(host64(y), ref, "f32", f"ld {weights.stride(0)}")
+
+
+@pytest.mark.parametrize("direction,m,n", [("fwd", 600, 72), ("fwd", 1100, 64), ("dx", 600, 72), ("dx", 1100, 64), ("dx", 72, 600), ("dx", 72, 1104)])
+def test_small_product_over_rows_gigabytes_apart(direction, m, n):
+    """A product small enough for the workgroup-split kernel whose operand rows span 2.5 or 4.6 GB (leading dimension 2^21),
+    with NaN wherever the operand is not: the result has the bits of the same blocks packed tightly.  K is no multiple of a
+    chunk, so lanes past its end are masked by an offset that must lie outside the descriptor."""
+    k, ld = 136, 1 << 21
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(12)
+    tall = torch.randn((max(m, n), k), generator=gen, device="cuda").to(torch.bfloat16)      # X or dA; W of the last cases
+    other = torch.randn((k, n) if direction == "fwd" else (min(m, n), k), generator=gen, device="cuda").mul_(0.02).to(torch.bfloat16)
+    wide = torch.full((max(m, n), ld), float("nan"), dtype=torch.bfloat16, device="cuda")[:, 8:8 + k]
+    wide.copy_(tall)
+    outs = []
+    for block in (tall, wide):
+        out = torch.full((m, n), 7.0, dtype=torch.float32, device="cuda")
+        if direction == "fwd":
+            grid, dims = T.Grid(T.MODE_2D, q=1), (m, k, n)
+            T.tp_linear_fwd(grid, dims, 1, [block], [other], None, T.EPI_NONE, out, None, workspace_for(grid, dims))
+        else:
+            grid, dims = T.Grid(T.MODE_2D, q=1), (m, n, k)
+            a, w = (block, other) if m > n else (other, block)
+            T.tp_linear_bwd(grid, dims, 1, 0, da_row_blocks=[a], w_blocks_dx=[w], dx=out, workspace=workspace_for(grid, dims))
+        outs.append(out)
+    a, w = (tall, other) if direction == "fwd" or m > n else (other, tall)
+    check(host64(outs[0]), host64(a) @ (host64(w) if direction == "fwd" else host64(w).T), "f32", f"{direction} {m} x {n}, packed")
+    assert torch.equal(outs[0], outs[1])
