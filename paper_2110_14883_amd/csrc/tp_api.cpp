@@ -277,8 +277,18 @@ double small_cost(int form, int64_t wgs, int64_t T) {
     return launch + (double)((wgs + kCUs - 1) / kCUs) * (round + chunk * (double)T);
 }
 
-Plan make_plan(const Opts& o, int form, int64_t m, int64_t n, int64_t k, int n_steps, int groups = 1) {
-    const size_t need = ws_bytes_for(plan_by(kQueryCosts, o, m, n, k, n_steps, groups, SIZE_MAX), m, n);
+// Bytes of workspace a call needs, and the plan the eight-wave kernel runs: its costs are those the query is made of.
+Plan query_plan(const Opts& o, int64_t m, int64_t n, int64_t k, int n_steps, int groups = 1) {
+    Plan p = plan_by(kQueryCosts, o, m, n, k, n_steps, groups, SIZE_MAX);
+    p.need = ws_bytes_for(p, m, n);
+    return p;
+}
+
+// four_wave: the product runs on the kernels of tp_gemm4.hip, tp_gemm_ms.hip and tp_small.hip
+Plan make_plan(const Opts& o, int form, int64_t m, int64_t n, int64_t k, int n_steps, int groups, bool four_wave) {
+    const Plan q = query_plan(o, m, n, k, n_steps, groups);
+    if (!four_wave) return q;
+    const size_t need = q.need;
     double cost = 0.0;
     Plan p = plan_by(kRunCosts, o, m, n, k, n_steps, groups, need, &cost);
     if (!o.tile && !o.split) {
@@ -310,10 +320,11 @@ int check_oblk(const tp_oblk_t& b, int64_t cols, bool f32_only) {
 
 struct Product {                 // one validated GEMM ready to launch
     int form; Plan plan; GemmArgs args; bool active;
+    bool four_wave;              // on the four-wave (and workgroup-split) kernels; else on the eight-wave one
 };
 
-// The four-wave stream kernel keeps one buffer descriptor per (C tile, step) and moves 32-bit lane
-// offsets along K: every offset it can form must stay below 2^31.
+// The four-wave kernels and the workgroup-split one keep one buffer descriptor per (C tile, step) and move
+// 32-bit lane offsets along K: every offset they can form must stay below 2^31.
 bool w4_eligible(int form, const GemmArgs& a) {
     const bool a_kc = form != FORM_TN, b_kc = form == FORM_NT;
     const int slots = a.n_groups > 1 ? a.n_groups : a.n_steps;
@@ -335,20 +346,10 @@ bool w4_eligible(int form, const GemmArgs& a) {
     return true;
 }
 
-int run_one(const Opts& o, int form, int tile_id, int split_k, const GemmArgs& a, hipStream_t stream) {
+int run_one(const Opts& o, int form, bool four_wave, int tile_id, int split_k, const GemmArgs& a, hipStream_t stream) {
     // 256 x 256 tiles run on the four-wave stream kernel unless the eight-wave one is asked for, smaller ones on
     // the four-wave kernel with a ring of stages; the eight-wave kernel keeps what their 32-bit offsets cannot reach
-    const bool four_wave = !o.eight_wave && w4_eligible(form, a);
     GemmArgs la = a;
-    if (!four_wave && (tile_id == TILE_32x32_SMALL || tile_id == TILE_16x32_SMALL)) {
-        const int groups = a.n_groups > 1 ? a.n_groups : 1;
-        tile_id = TILE_128x128;
-        la.tiles_m = (a.M + 127) / 128; la.tiles_n = (a.N + 127) / 128;
-        if (groups > 1) {
-            la.group_tiles = a.group_along_n ? la.tiles_n : la.tiles_m;
-            (a.group_along_n ? la.tiles_n : la.tiles_m) *= groups;
-        }
-    }
     if (four_wave) {
         switch (tile_id) {
             case TILE_256x256: tile_id = TILE_256x256_W4; break;
@@ -377,12 +378,12 @@ int run_product(const Opts& o, const Product& pr, void* workspace, hipStream_t s
     GemmArgs a = pr.args;
     a.ws = static_cast<float*>(workspace);
     const Plan& pl = pr.plan;
-    if (pl.m_main <= 0) return run_one(o, pr.form, pl.tile_id, pl.split_k, a, stream);
+    if (pl.m_main <= 0) return run_one(o, pr.form, pr.four_wave, pl.tile_id, pl.split_k, a, stream);
     // main launch: rows [0, m_main), a whole number of rounds
     const int64_t m = a.M, m0 = pl.m_main;
     GemmArgs mainp = a;
     mainp.M = (int32_t)m0;
-    if (int e = run_one(o, pr.form, pl.tile_id, 1, mainp, stream)) return e;
+    if (int e = run_one(o, pr.form, pr.four_wave, pl.tile_id, 1, mainp, stream)) return e;
     // tail launch: rows [m_main, m) through shifted pointers, with its own tile shape and K split
     GemmArgs tail = a;
     tail.M = (int32_t)(m - m0);
@@ -394,15 +395,29 @@ int run_product(const Opts& o, const Product& pr, void* workspace, hipStream_t s
     tail.out = static_cast<char*>(a.out) + m0 * a.ldo * (a.out_f32 ? 4 : 2);
     if (a.pre) tail.pre = static_cast<char*>(a.pre) + m0 * a.ldp * 2;
     if (a.dg) tail.dg = static_cast<const char*>(a.dg) + m0 * a.lddg * 2;
-    return run_one(o, pr.form, pl.tail_tile_id, pl.tail_split, tail, stream);
+    return run_one(o, pr.form, pr.four_wave, pl.tail_tile_id, pl.tail_split, tail, stream);
 }
 
-void fill_common(const Opts& o, GemmArgs& a, const Plan& p, int64_t m, int64_t n, int64_t k, int n_steps) {
+void fill_common(const Opts& o, GemmArgs& a, int64_t m, int64_t n, int64_t k, int n_steps) {
     std::memset(&a, 0, sizeof(a));
     a.M = (int32_t)m; a.N = (int32_t)n; a.K = (int32_t)k; a.n_steps = n_steps;
-    a.tiles_m = p.tiles_m; a.tiles_n = p.tiles_n; a.split_k = p.split_k; a.group_m = p.group_m;
     a.max_workgroups = kCUs;
     a.rotate = o.rotate;                       // (run_one resolves "automatic" once it knows the kernel)
+}
+
+// The plan of a product whose blocks, epilogue and groups are filled in.  The offsets that its strides ask for come first:
+// they decide which kernels can run it, and so whose costs count.
+void plan_product(const Opts& o, Product& pr) {
+    GemmArgs& a = pr.args;
+    const int groups = a.n_groups > 1 ? a.n_groups : 1;
+    pr.four_wave = !o.eight_wave && w4_eligible(pr.form, a);
+    pr.plan = make_plan(o, pr.form, a.M, a.N, a.K, a.n_steps, groups, pr.four_wave);
+    const Plan& p = pr.plan;
+    a.tiles_m = p.tiles_m; a.tiles_n = p.tiles_n; a.split_k = p.split_k; a.group_m = p.group_m;
+    if (a.n_groups > 0) {                      // the products of a grouped launch lie side by side along N or M
+        a.group_tiles = a.group_along_n ? p.tiles_n : p.tiles_m;
+        (a.group_along_n ? a.tiles_n : a.tiles_m) *= groups;
+    }
 }
 
 bool ws_ok(size_t need, const void* workspace, size_t bytes) {
@@ -467,20 +482,9 @@ int linear_fwd(const tp_grid_t* grid, const tp_dims_t* dims, int n_steps, const 
         if (int e = check_oblk(preact, s.n, false)) return e;
         if (preact.dtype != TP_BF16) return TP_ERR_DTYPE;
     }
-    Plan p = make_plan(o, FORM_NN, s.m, s.n, s.k, n_steps);
-    if (use_static_scratch) {
-        if (p.need > kStaticScratchBytes) return TP_ERR_SCRATCH;
-    } else if (!ws_ok(p.need, workspace, workspace_bytes)) {
-        return TP_ERR_WORKSPACE;
-    }
-    if (int e = check_device()) return e;
-    if (use_static_scratch) {
-        if (int e = static_scratch(&workspace)) return e;
-    }
-
     Product pr{};
-    pr.form = FORM_NN; pr.plan = p;
-    fill_common(o, pr.args, p, s.m, s.n, s.k, n_steps);
+    pr.form = FORM_NN;
+    fill_common(o, pr.args, s.m, s.n, s.k, n_steps);
     for (int k = 0; k < n_steps; ++k) {
         pr.args.a[k] = x_blocks[k].ptr; pr.args.lda[k] = (int32_t)x_blocks[k].ld;
         pr.args.b[k] = w_blocks[k].ptr; pr.args.ldb[k] = (int32_t)w_blocks[k].ld;
@@ -489,6 +493,16 @@ int linear_fwd(const tp_grid_t* grid, const tp_dims_t* dims, int n_steps, const 
     pr.args.pre = preact.ptr; pr.args.ldp = preact.ld;
     pr.args.bias = epi == TP_EPI_NONE ? nullptr : bias;
     pr.args.gelu = epi == TP_EPI_BIAS_GELU;
+    plan_product(o, pr);
+    if (use_static_scratch) {
+        if (pr.plan.need > kStaticScratchBytes) return TP_ERR_SCRATCH;
+    } else if (!ws_ok(pr.plan.need, workspace, workspace_bytes)) {
+        return TP_ERR_WORKSPACE;
+    }
+    if (int e = check_device()) return e;
+    if (use_static_scratch) {
+        if (int e = static_scratch(&workspace)) return e;
+    }
     return run_product(o, pr, workspace, static_cast<hipStream_t>(hip_stream));
 }
 
@@ -525,14 +539,14 @@ size_t tp_linear_workspace_size_ex(const tp_grid_t* grid, const tp_dims_t* dims,
         if (build_partials(grid, dims, pass, &ps) != TP_OK) return 0;
         size_t worst = 0;               // any number of products 1 .. n_steps may be asked for
         for (int groups = 1; groups <= ps.n_steps; ++groups)
-            worst = std::max(worst, make_plan(o, pass == TP_PASS_DX_PARTIALS ? FORM_NT : FORM_TN, ps.m, ps.n, ps.k, 1, groups).need);
+            worst = std::max(worst, query_plan(o, ps.m, ps.n, ps.k, 1, groups).need);
         return worst;
     }
     Share s;
     if (build_share(grid, dims, pass, &s) != TP_OK) return 0;
     size_t worst = 0;                   // any prefix 1 .. n_steps of the steps may be asked for
     for (int steps = 1; steps <= s.n_steps; ++steps)
-        worst = std::max(worst, make_plan(o, pass == TP_PASS_FWD ? FORM_NN : (pass == TP_PASS_DX ? FORM_NT : FORM_TN), s.m, s.n, s.k, steps).need);
+        worst = std::max(worst, query_plan(o, s.m, s.n, s.k, steps).need);
     Share sf;                           // the bias gradient of tp_linear_bwd sums the forward block's columns in two passes
     if (pass != TP_PASS_FWD && build_share(grid, dims, TP_PASS_FWD, &sf) == TP_OK)
         worst = std::max(worst, colsum_ws_bytes(sf.m, sf.n));
@@ -605,8 +619,7 @@ int tp_linear_bwd_ex(const tp_grid_t* grid, const tp_dims_t* dims, int n_steps_d
             if (dgelu_preact) return TP_ERR_MODE;
             if (dx.dtype != TP_F32) return TP_ERR_DTYPE;
         }
-        Plan p = make_plan(o, FORM_NT, sx.m, sx.n, sx.k, n_steps_dx);
-        fill_common(o, px.args, p, sx.m, sx.n, sx.k, n_steps_dx);
+        fill_common(o, px.args, sx.m, sx.n, sx.k, n_steps_dx);
         for (int k = 0; k < n_steps_dx; ++k) {
             const tp_cblk_t& a = (k == own_slot_dx) ? own_blk : da_row_blocks[k];
             if (int e = check_cblk(a, sx.k)) return e;
@@ -620,7 +633,8 @@ int tp_linear_bwd_ex(const tp_grid_t* grid, const tp_dims_t* dims, int n_steps_d
             px.args.dg = dgelu_preact->ptr; px.args.lddg = dgelu_preact->ld;
         }
         px.args.out = dx.ptr; px.args.ldo = dx.ld; px.args.out_f32 = dx.dtype == TP_F32;
-        px.form = FORM_NT; px.plan = p;
+        px.form = FORM_NT;
+        plan_product(o, px);
     }
     // ---- (3) dW
     Product pw{}; pw.active = dw.ptr != nullptr;
@@ -628,8 +642,7 @@ int tp_linear_bwd_ex(const tp_grid_t* grid, const tp_dims_t* dims, int n_steps_d
         if (!x_blocks_dw || !da_col_blocks) return TP_ERR_NULL;
         if (n_steps_dw < 1 || n_steps_dw > sw.n_steps) return TP_ERR_SHAPE;
         if (own_slot_dw >= n_steps_dw) return TP_ERR_SHAPE;
-        Plan p = make_plan(o, FORM_TN, sw.m, sw.n, sw.k, n_steps_dw);
-        fill_common(o, pw.args, p, sw.m, sw.n, sw.k, n_steps_dw);
+        fill_common(o, pw.args, sw.m, sw.n, sw.k, n_steps_dw);
         for (int k = 0; k < n_steps_dw; ++k) {
             const tp_cblk_t& b = (k == own_slot_dw) ? own_blk : da_col_blocks[k];
             if (int e = check_cblk(x_blocks_dw[k], sw.m)) return e;       // X block is [k = tokens][m = H_blk]
@@ -639,7 +652,8 @@ int tp_linear_bwd_ex(const tp_grid_t* grid, const tp_dims_t* dims, int n_steps_d
         }
         if (int e = check_oblk(dw, sw.n, true)) return e;
         pw.args.out = dw.ptr; pw.args.ldo = dw.ld; pw.args.out_f32 = 1;
-        pw.form = FORM_TN; pw.plan = p;
+        pw.form = FORM_TN;
+        plan_product(o, pw);
     }
     size_t need = 0;
     if (px.active) need = std::max(need, px.plan.need);
@@ -714,8 +728,7 @@ int tp_linear_bwd_partials_ex(const tp_grid_t* grid, const tp_dims_t* dims, int 
     Product px{}; px.active = n_dx > 0;
     if (px.active) {
         if (!w_blocks_dx || !dx_partials) return TP_ERR_NULL;
-        Plan p = make_plan(o, FORM_NT, sx.m, sx.n, sx.k, 1, n_dx);
-        fill_common(o, px.args, p, sx.m, sx.n, sx.k, 1);
+        fill_common(o, px.args, sx.m, sx.n, sx.k, 1);
         for (int k = 0; k < n_dx; ++k) {
             if (int e = check_cblk(w_blocks_dx[k], sx.k)) return e;    // W block [H_blk][F_blk]: n x k
             if (int e = check_oblk(dx_partials[k], sx.n, true)) return e;
@@ -725,15 +738,14 @@ int tp_linear_bwd_partials_ex(const tp_grid_t* grid, const tp_dims_t* dims, int 
             px.args.outs[k] = dx_partials[k].ptr; px.args.ldos[k] = dx_partials[k].ld;
         }
         px.args.out = dx_partials[0].ptr; px.args.ldo = dx_partials[0].ld; px.args.out_f32 = 1;
-        px.args.n_groups = n_dx; px.args.group_along_n = 1; px.args.group_tiles = p.tiles_n;
-        px.args.tiles_n = p.tiles_n * n_dx;                            // the products side by side along N
-        px.form = FORM_NT; px.plan = p;
+        px.args.n_groups = n_dx; px.args.group_along_n = 1;            // the products side by side along N
+        px.form = FORM_NT;
+        plan_product(o, px);
     }
     Product pw{}; pw.active = n_dw > 0;
     if (pw.active) {
         if (!x_blocks_dw || !dw_partials) return TP_ERR_NULL;
-        Plan p = make_plan(o, FORM_TN, sw.m, sw.n, sw.k, 1, n_dw);
-        fill_common(o, pw.args, p, sw.m, sw.n, sw.k, 1);
+        fill_common(o, pw.args, sw.m, sw.n, sw.k, 1);
         for (int k = 0; k < n_dw; ++k) {
             if (int e = check_cblk(x_blocks_dw[k], sw.m)) return e;    // X block [M_blk][H_blk]: k x m
             if (int e = check_oblk(dw_partials[k], sw.n, true)) return e;
@@ -743,9 +755,9 @@ int tp_linear_bwd_partials_ex(const tp_grid_t* grid, const tp_dims_t* dims, int 
             pw.args.outs[k] = dw_partials[k].ptr; pw.args.ldos[k] = dw_partials[k].ld;
         }
         pw.args.out = dw_partials[0].ptr; pw.args.ldo = dw_partials[0].ld; pw.args.out_f32 = 1;
-        pw.args.n_groups = n_dw; pw.args.group_along_n = 0; pw.args.group_tiles = p.tiles_m;
-        pw.args.tiles_m = p.tiles_m * n_dw;                            // the products stacked along M
-        pw.form = FORM_TN; pw.plan = p;
+        pw.args.n_groups = n_dw; pw.args.group_along_n = 0;            // the products stacked along M
+        pw.form = FORM_TN;
+        plan_product(o, pw);
     }
     for (int i = 0; i < n_ranges; ++i)
         for (int j = i + 1; j < n_ranges; ++j)

@@ -749,3 +749,74 @@ def test_small_product_over_rows_gigabytes_apart(direction, m, n):
     a, w = (tall, other) if direction == "fwd" or m > n else (other, tall)
     check(host64(outs[0]), host64(a) @ (host64(w) if direction == "fwd" else host64(w).T), "f32", f"{direction} {m} x {n}, packed")
     assert torch.equal(outs[0], outs[1])
+
+
+def _far(rows, cols, ld, dtype=torch.bfloat16, fill=float("nan")):
+    """A [rows, cols] view at a leading dimension of `ld`, with NaN (or `fill`) around it."""
+    return torch.full((rows, ld), fill, dtype=dtype, device="cuda")[:, 8:8 + cols]
+
+
+@pytest.mark.parametrize("tile", [0, 2, 3, 4])
+def test_operands_beyond_32_bit_offsets(tile):
+    """Strides that the 32-bit offsets of the other kernels cannot reach go to the eight-wave kernel, every form of it: outputs
+    at a leading dimension above 2^22 (forward with epilogue and saved pre-activation, dX, a grouped dX), operands whose K rows
+    span more than 2 GiB (dW, a grouped dW)."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(13)
+    rnd = lambda *shape: torch.randn(shape, generator=gen, device="cuda").to(torch.bfloat16)
+    ld_out, ld_in = (1 << 22) + 64, 1 << 20
+    m, k, n = 40, 200, 264
+    with T.plan_opts(tile=tile):
+        grid, dims = T.Grid(T.MODE_2D, q=2, ri=1, rj=0), (2 * m, 2 * k, 2 * n)
+        xs, ws_, bias = [rnd(m, k) for _ in range(2)], [rnd(k, n).mul_(0.1) for _ in range(2)], rnd(n)
+        y, pre = _far(m, n, ld_out, torch.float32), torch.empty((m, n), dtype=torch.bfloat16, device="cuda")
+        T.tp_linear_fwd(grid, dims, 2, xs, ws_, bias, T.EPI_BIAS_GELU, y, pre, workspace_for(grid, dims))
+        A, Y = O.share_fwd([host64(b) for b in xs], [host64(b) for b in ws_], host64(bias))
+        check(host64(y), Y, "f32", f"tile {tile}: Y")
+        check(host64(pre), A, "bf16", f"tile {tile}: A_saved")
+        assert bool(torch.isnan(y._base[:, :8]).all()) and bool(torch.isnan(y._base[:, 8 + n:]).all())
+        del y
+        dims = (2 * m, 2 * n, 2 * k)                                  # dX [m, n] = sum dA_k [m, k] W_k [n, k]^T
+        das, wts = [rnd(m, k) for _ in range(2)], [rnd(n, k).mul_(0.1) for _ in range(2)]
+        dx = _far(m, n, ld_out, torch.float32)
+        T.tp_linear_bwd(grid, dims, 2, 0, da_row_blocks=das, w_blocks_dx=wts, dx=dx, workspace=workspace_for(grid, dims))
+        check(host64(dx), O.share_dx([host64(b) for b in das], [host64(b) for b in wts]), "f32", f"tile {tile}: dX")
+        del dx
+        parts = [_far(m, n, ld_out, torch.float32) for _ in range(2)]
+        T.tp_linear_bwd_partials(grid, dims, das[0], wts, parts, workspace=torch.empty(max(T.tp_linear_workspace_size(grid, dims, T.PASS_DX_PARTIALS), 256), dtype=torch.uint8, device="cuda"))
+        for i, part in enumerate(parts):
+            check(host64(part), host64(das[0]) @ host64(wts[i]).T, "f32", f"tile {tile}: dX partial {i}")
+        del parts
+        rows = 1100                                                   # dW [n, k] = sum X_k [rows, n]^T dA_k [rows, k]
+        dims = (2 * rows, 2 * n, 2 * k)
+        tight, das = [rnd(rows, n) for _ in range(2)], [rnd(rows, k) for _ in range(2)]
+        xs = [_far(rows, n, ld_in) for _ in range(2)]
+        for far, near in zip(xs, tight):
+            far.copy_(near)
+        dw = torch.empty((n, k), dtype=torch.float32, device="cuda")
+        T.tp_linear_bwd(grid, dims, 0, 2, x_blocks_dw=xs, da_col_blocks=das, dw=dw, workspace=workspace_for(grid, dims))
+        check(host64(dw), O.share_dw([host64(b) for b in tight], [host64(b) for b in das]), "f32", f"tile {tile}: dW")
+        parts = [torch.empty((n, k), dtype=torch.float32, device="cuda") for _ in range(2)]
+        T.tp_linear_bwd_partials(grid, dims, das[0], x_blocks_dw=xs, dw_partials=parts, workspace=torch.empty(max(T.tp_linear_workspace_size(grid, dims, T.PASS_DW_PARTIALS), 256), dtype=torch.uint8, device="cuda"))
+        for i, part in enumerate(parts):
+            check(host64(part), host64(tight[i]).T @ host64(das[0]), "f32", f"tile {tile}: dW partial {i}")
+
+
+def test_products_beyond_32_bit_offsets_keep_their_k_split_and_walk_many_tiles():
+    """Beyond the 32-bit offsets a few rows with a long K are split over workgroups, whose partial planes fill the workspace
+    (the smaller kernel that needs no planes cannot take them); and 258 tiles of 128 x 128 on 256 persistent workgroups."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(14)
+    ld = (1 << 22) + 64
+    for m, k, n, tile in ((24, 4096, 264, 0), (64, 64, 33000, 4)):
+        grid, dims = T.Grid(T.MODE_2D, q=1), (m, n, k)
+        a, w = (torch.randn(s, generator=gen, device="cuda").to(torch.bfloat16) for s in ((m, k), (n, k)))
+        dx = _far(m, n, ld, torch.float32)
+        with T.plan_opts(tile=tile):
+            need = T.tp_linear_workspace_size(grid, dims, T.PASS_DX)
+            ws = torch.full((max(need, 256) // 4,), float("nan"), dtype=torch.float32, device="cuda")
+            T.tp_linear_bwd(grid, dims, 1, 0, da_row_blocks=[a], w_blocks_dx=[w], dx=dx, workspace=ws)
+        check(host64(dx), host64(a) @ host64(w).T, "f32", f"{m} x {k} x {n}")
+        if tile == 0:
+            assert need >= 8 * m * n * 4 and not bool(torch.isnan(ws[:8 * m * n]).any())
+        del dx
