@@ -50,7 +50,7 @@ def test_k_rotation_and_other_group_heights():
     """The K-tile rotation and the tile-order group only change the order of work, never the result
     beyond fp32 summation order."""
     grid, dims = T.Grid(T.MODE_2D, q=2, ri=1, rj=1), (2 * 520, 2 * 1032, 2 * 776)
-    for tile in (1, 2):          # the four-wave kernel (rotation off unless asked for) and the eight-wave one (on unless asked)
+    for tile in (1, 2, 5):       # the 256 x 256 stream kernel and the ring kernel (rotation off unless asked for), the eight-wave one (on unless asked)
         for rotate in (0, 1):
             with overrides(tile=tile, rotate=rotate):
                 run_share(grid, dims, y_dtype="f32", dx_dtype="f32", use_own_slot=False, label=f"tile {tile} rotation {'on' if rotate else 'off'}")
@@ -60,11 +60,16 @@ def test_k_rotation_and_other_group_heights():
 
 
 def test_many_tiles_per_workgroup():
-    """More tiles than workgroups (128 x 128 tiles forced: 324 per product on 256 persistent
-    workgroups): all three memory forms, one-step and two-step shares, ragged edges."""
+    """More tiles than compute units, ragged edges.  128 x 128 tiles (one workgroup each, 324 per product): all three memory
+    forms, one-step and two-step shares.  256 x 256 tiles on 256 persistent workgroups, stream kernel and eight-wave
+    kernel: 306 tiles of the forward and, by the other two cases, of dX and dW."""
     with overrides(tile=4):
         run_share(T.Grid(T.MODE_2D, q=1), (2250, 2184, 2312), use_own_slot=False, label="324 tiles per product")
         run_share(T.Grid(T.MODE_2D, q=2, ri=1, rj=0), (2 * 2250, 2 * 520, 2 * 2312), backward=False, y_dtype="f32", label="two steps")
+    for tile in (1, 5):
+        with overrides(tile=tile):
+            for dims in ((4100, 72, 4360), (4100, 4360, 72), (100, 4104, 4360)):
+                run_share(T.Grid(T.MODE_2D, q=1), dims, use_own_slot=False, label=f"tile {tile}: 306 tiles of one product")
 
 
 @pytest.mark.parametrize("name,grid,ogrid,dims", [
@@ -707,7 +712,8 @@ def test_own_dA_and_bias_gradient_in_one_pass(rows, cols, with_workspace):
 
 def test_small_product_with_a_leading_dimension_beyond_32_bit_offsets():
     """A product small enough for the workgroup-split kernel whose weight rows lie so far apart that its 32-bit offsets
-    cannot reach the last one: it runs on the eight-wave kernel, against the same blocks packed tightly."""
+    cannot reach the last one: it runs on the eight-wave kernel, and the same blocks packed tightly on the other; both against
+    the oracle."""
     m, k, n, ld = 24, 4096, 40, 1 << 18
     gen = torch.Generator(device="cuda")
     gen.manual_seed(11)
