@@ -127,7 +127,7 @@ int tp_block_map(const tp_grid_t* grid, const tp_dims_t* dims, int pass,
  * tp_linear_bwd_partials (TP_PASS_DX_PARTIALS, TP_PASS_DW_PARTIALS) may need for this share:
  * cross-workgroup split-K partials in fp32 (never more than 8 x m x n x 4 bytes per product), and, for
  * the two backward passes, the row-slab sums of the bias gradient (at most 64 x n_fwd x 4 bytes; a
- * smaller workspace makes tp_linear_bwd fall back to the single-pass column sum).  0 on invalid
+ * smaller workspace makes tp_linear_bwd fall back to the single-slab column sum).  0 on invalid
  * arguments. */
 size_t tp_linear_workspace_size(const tp_grid_t* grid, const tp_dims_t* dims, int pass);
 /* The same for calls made with plan options (NULL = tp_linear_workspace_size). */
@@ -288,14 +288,15 @@ int tp_dgelu(const void* dy, int64_t ld_dy, const void* preact, int64_t ld_pre,
 
 /*
  * tp_bias_grad -- db = 1^T dA: column sums of a bf16 block [rows, cols] (leading dimension ld) into
- * fp32 [cols], in a summation order fixed by (rows, cols) alone (the same bits on every call).  This is
+ * fp32 [cols], in a summation order fixed by (rows, cols) and whether there is a workspace (the same bits on every call).  This is
  * what tp_linear_bwd writes to db_f32 for the block it forms itself; here for a dA block that already
  * exists (the 1D chain, where dA is the epilogue of the second layer's dX).  HBM-bound.
  *   workspace : optional device scratch of >= tp_bias_grad_workspace_size(rows, cols) bytes, 16-byte
- *               aligned: the rows are then summed in slabs by many workgroups and the slab sums added
- *               in ascending order by a second kernel.  NULL: one workgroup per 64 columns sums all
- *               rows (slow when cols is small).  The two forms add in different orders and may differ
- *               in the last bits; each is reproducible.  Too small or misaligned: TP_ERR_WORKSPACE.
+ *               aligned: more than 512 rows are then summed in slabs by many workgroups and the slab
+ *               sums added in a fixed order (eight interleaved chains) by a second kernel.  NULL: each
+ *               workgroup sums all rows of its strip of columns (slow when cols is small).  The two
+ *               forms add in different orders and may differ in the last bits; each is reproducible.
+ *               Too small or misaligned: TP_ERR_WORKSPACE.
  * Defined by: the bias gradient of the layer of tp_linear_fwd for one column chunk of the bias
  * (Section 2.2 chunking of the output columns).
  * Errors: TP_ERR_NULL, TP_ERR_SHAPE, TP_ERR_ALIGN, TP_ERR_WORKSPACE, TP_ERR_HIP.

@@ -414,56 +414,74 @@ __global__ __launch_bounds__(256) void tp_bias_act_kernel(const float* c, int64_
 }
 
 // Column sums of a bf16 [rows][cols] block into fp32.  Workgroup (bx, by) sums rows
-// [by * rows_per_split, ...) of columns 128 bx .. 128 bx + 127 into out[by][cols]; with one split that is the
-// result, with several tp_colsum_finish_kernel adds the splits.  Every order of summation is fixed by
-// (rows, cols) and the number of splits: the result is reproducible.
+// [by * rows_per_split, ...) of columns COLS bx .. COLS (bx + 1) - 1 into out[by][cols]; with one split that is the
+// result, with several tp_colsum_finish_kernel adds the splits.  Every order of summation is fixed by the rows, the columns
+// and the number of splits, whatever COLS is: the result is reproducible.
 // FROM_DY: the block does not exist yet; it is formed on the way, da = dy * GeLU'(pre), and written.  The own dA
 // block and its bias gradient then take one pass over memory (6 bytes per element) instead of 8 and one launch less;
-// the sums are those of the finished block, bit for bit.  Bound by memory; two passes against one, finish included:
-// 8192 x 1024 25.1 -> 18.4 us, 2048 x 8192 35.2 -> 28.2, 32896 x 2560 127 -> 119, 4096 x 24576 145 -> 131.
-constexpr int COLSUM_COLS = 128, COLSUM_LANES = 32;           // columns per workgroup, rows side by side
-template <bool FROM_DY>
-__global__ __launch_bounds__(512) void tp_colsum_kernel(const uint16_t* dy, int64_t ld_dy, const uint16_t* pre, int64_t ld_pre,
-                                                        uint16_t* da, int64_t ld, int64_t rows, int cols, float* out,
-                                                        int64_t rows_per_split) {
-    __shared__ float part[COLSUM_LANES][COLSUM_COLS + 1];
-    const int cl = threadIdx.x & 15, rl = threadIdx.x >> 4;       // 16 chunk lanes x 32 row lanes
-    const int c = blockIdx.x * COLSUM_COLS + cl * 8;
+// the sums are those of the finished block, bit for bit.  Bound by memory, and by latency where a workgroup walks many
+// rows or there are few workgroups: launch_dgelu_colsum has both sides.
+constexpr int COLSUM_LANES = 32;                              // rows side by side
+template <bool FROM_DY, int COLS>
+__global__ __launch_bounds__(COLS * 4) void tp_colsum_kernel(const uint16_t* dy, int64_t ld_dy, const uint16_t* pre, int64_t ld_pre,
+                                                             uint16_t* da, int64_t ld, int64_t rows, int cols, float* out,
+                                                             int64_t rows_per_split) {
+    __shared__ float part[COLSUM_LANES][COLS + 1];
+    constexpr int CL = COLS / 8;                                  // chunk lanes x 32 row lanes
+    const int cl = threadIdx.x % CL, rl = threadIdx.x / CL;
+    const int c = blockIdx.x * COLS + cl * 8;
     const int64_t r_begin = (int64_t)blockIdx.y * rows_per_split;
     const int64_t r_end = r_begin + rows_per_split < rows ? r_begin + rows_per_split : rows;
     float s[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    auto some_rows = [&](auto n_, int64_t r) __attribute__((always_inline)) {      // n rows, 32 apart, in flight together
+    // rows r0 + rl + 32 u, u < n, in flight together; FULL: all of them exist, else those past the end are loaded from the
+    // last row and dropped
+    auto some_rows = [&](auto n_, auto full_, int64_t r0) __attribute__((always_inline)) {
         constexpr int n = decltype(n_)::value;
+        constexpr bool FULL = decltype(full_)::value;
         u32x4_t v[n], a[n];
 #pragma unroll
         for (int u = 0; u < n; ++u) {
-            const int64_t row = r + COLSUM_LANES * u;
-            v[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(FROM_DY ? dy + row * ld_dy + c : da + row * ld + c));
+            int64_t row = r0 + rl + COLSUM_LANES * u;
+            if (!FULL && row >= r_end) row = r_end - 1;
+            const u32x4_t* const src = reinterpret_cast<const u32x4_t*>(FROM_DY ? dy + row * ld_dy + c : da + row * ld + c);
+            if constexpr (FROM_DY || n > 1) v[u] = __builtin_nontemporal_load(src);
+            else                            v[u] = *src;
             if constexpr (FROM_DY) a[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(pre + row * ld_pre + c));
         }
 #pragma unroll
         for (int u = 0; u < n; ++u) {
+            const int64_t row = r0 + rl + COLSUM_LANES * u;
+            if (!FULL && row >= r_end) break;
             if constexpr (FROM_DY) {
                 v[u] = dgelu8(v[u], a[u]);
-                __builtin_nontemporal_store(v[u], reinterpret_cast<u32x4_t*>(da + (r + COLSUM_LANES * u) * ld + c));
+                __builtin_nontemporal_store(v[u], reinterpret_cast<u32x4_t*>(da + row * ld + c));
             }
 #pragma unroll
             for (int i = 0; i < 4; ++i) { s[2 * i] += bf16_lo(v[u][i]); s[2 * i + 1] += bf16_hi(v[u][i]); }
         }
     };
     if (c < cols) {
-        int64_t r = r_begin + rl;
-        for (; r + 3 * COLSUM_LANES < r_end; r += 4 * COLSUM_LANES) some_rows(std::integral_constant<int, 4>{}, r);
-        for (; r < r_end; r += COLSUM_LANES) some_rows(std::integral_constant<int, 1>{}, r);
+        int64_t r = r_begin;
+        if constexpr (FROM_DY) {                                  // the remainder in one batch: each trip is two loads, GeLU' and a store
+            for (; r + 4 * COLSUM_LANES <= r_end; r += 4 * COLSUM_LANES) some_rows(std::integral_constant<int, 4>{}, std::true_type{}, r);
+            const int64_t left = (r_end - r + COLSUM_LANES - 1) / COLSUM_LANES;
+            if (left > 3)       some_rows(std::integral_constant<int, 4>{}, std::false_type{}, r);
+            else if (left == 3) some_rows(std::integral_constant<int, 3>{}, std::false_type{}, r);
+            else if (left == 2) some_rows(std::integral_constant<int, 2>{}, std::false_type{}, r);
+            else if (left == 1) some_rows(std::integral_constant<int, 1>{}, std::false_type{}, r);
+        } else {
+            for (; r + rl + 3 * COLSUM_LANES < r_end; r += 4 * COLSUM_LANES) some_rows(std::integral_constant<int, 4>{}, std::true_type{}, r);
+            for (; r + rl < r_end; r += COLSUM_LANES) some_rows(std::integral_constant<int, 1>{}, std::true_type{}, r);
+        }
     }
 #pragma unroll
     for (int i = 0; i < 8; ++i) part[rl][cl * 8 + i] = s[i];
     __syncthreads();
-    if (threadIdx.x < COLSUM_COLS) {
+    if (threadIdx.x < COLS) {
         float tot = 0.0f;
 #pragma unroll
         for (int r = 0; r < COLSUM_LANES; ++r) tot += part[r][threadIdx.x];
-        const int cc = blockIdx.x * COLSUM_COLS + threadIdx.x;
+        const int cc = blockIdx.x * COLS + threadIdx.x;
         if (cc < cols) out[(int64_t)blockIdx.y * cols + cc] = tot;
     }
 }
@@ -595,7 +613,9 @@ hipError_t launch_bias_act(const float* c, int64_t ldc, const void* bias, int ge
                          gelu, y, ldy, y_f32, static_cast<uint16_t*>(pre), ldp, rows, (int)(cols >> 2));
 }
 
-// Row splits of the column sum: enough workgroups to fill the chip four times over, at least 256 rows each.
+// Row splits that the workspace of a column sum is sized for: columns counted in strips of 64, workgroups enough to fill the
+// chip four times over, at least 256 rows each.  (Callers size workspaces by this; how many splits run, and how wide
+// the strips are, is decided below within it.)
 int colsum_splits(int64_t rows, int64_t cols) {
     const int64_t col_blocks = (cols + 63) / 64;
     if (col_blocks >= 256) return 1;                    // one workgroup per 64 columns already fills the chip
@@ -609,30 +629,63 @@ size_t colsum_ws_bytes(int64_t rows, int64_t cols) {
     const int r = colsum_splits(rows, cols);
     return r > 1 ? (size_t)r * (size_t)cols * 4 : 0;
 }
-template <bool FROM_DY>
-static hipError_t colsum_passes(const uint16_t* dy, int64_t ld_dy, const uint16_t* pre, int64_t ld_pre, uint16_t* da, int64_t ld,
-                                int64_t rows, int64_t cols, float* out, float* ws, hipStream_t s) {
-    const unsigned strips = (unsigned)((cols + COLSUM_COLS - 1) / COLSUM_COLS);
-    const int splits = ws ? colsum_splits(rows, cols) : 1;
-    const int64_t per = splits == 1 ? rows : ((rows + splits - 1) / splits + 31) / 32 * 32;
-    if (hipError_t e = launch_kernel(tp_colsum_kernel<FROM_DY>, dim3(strips, (unsigned)splits), dim3(512), 0, s, dy, ld_dy, pre, ld_pre,
-                                     da, ld, rows, (int)cols, splits == 1 ? out : ws, per); e != hipSuccess || splits == 1)
+// How the sum runs.  Times in us, replayed graphs.
+struct ColsumPlan { int splits; bool wide; int64_t per; };
+ColsumPlan colsum_plan(int64_t rows, int64_t cols, bool has_ws, bool from_dy) {
+    ColsumPlan p;
+    // up to 512 rows one slab: a second one costs the finish launch (300 x 1024: 3.1 against 4.8, 300 x 8192 3.3 / 5.0)
+    p.splits = has_ws && rows > 512 ? colsum_splits(rows, cols) : 1;
+    p.per = p.splits == 1 ? rows : ((rows + p.splits - 1) / p.splits + 31) / 32 * 32;
+    // Strips of 128 columns (256-byte pieces of a row) where they make workgroups enough, else 64 (twice the workgroups).
+    // One slab: 128 once the narrow ones no longer fit one to a CU: 4096 x 16384 31.4 against 29.2 (64), 4096 x 20480 34.6 / 44.0,
+    // 2048 x 2560 14.4 / 13.0.  Several: 4096 x 1024 (128 workgroups) 6.5 / 5.3, 1024 x 6184 (196) 7.0 / 7.5, 4096 x 8192 15.5 / 16.7.
+    // Few rows keep 64 (600 x 6184, three slabs, 7.4 / 6.0; 150 x 24576 3.8 / 3.3) unless dA is formed too (600 x 20480 19.4 / 24.4,
+    // 600 x 12288, three slabs, 14.2 / 15.4).
+    const int64_t strips = (cols + 127) / 128;
+    p.wide = strips * p.splits > 128 && (rows >= 1024 || (from_dy && (p.splits == 1 || strips * p.splits > 256)));
+    return p;
+}
+template <bool FROM_DY, int COLS>
+static hipError_t colsum_passes(const ColsumPlan& p, const uint16_t* dy, int64_t ld_dy, const uint16_t* pre, int64_t ld_pre, uint16_t* da,
+                                int64_t ld, int64_t rows, int64_t cols, float* out, float* ws, hipStream_t s) {
+    const unsigned strips = (unsigned)((cols + COLS - 1) / COLS);
+    if (hipError_t e = launch_kernel(tp_colsum_kernel<FROM_DY, COLS>, dim3(strips, (unsigned)p.splits), dim3(COLS * 4), 0, s, dy, ld_dy,
+                                     pre, ld_pre, da, ld, rows, (int)cols, p.splits == 1 ? out : ws, p.per); e != hipSuccess || p.splits == 1)
         return e;
     return launch_kernel(tp_colsum_finish_kernel, dim3((unsigned)((cols + 31) / 32)), dim3(256), 0, s,
-                         static_cast<const float*>(ws), splits, (int)cols, out);
+                         static_cast<const float*>(ws), p.splits, (int)cols, out);
 }
-// ws: colsum_ws_bytes(rows, cols) bytes, or null for the single-pass form (one workgroup per 128 columns)
+// ws: colsum_ws_bytes(rows, cols) bytes, or null for the single-slab form
 hipError_t launch_colsum(const void* da, int64_t ld, int64_t rows, int64_t cols, float* out, float* ws, hipStream_t s) {
-    return colsum_passes<false>(nullptr, 0, nullptr, 0, static_cast<uint16_t*>(const_cast<void*>(da)), ld, rows, cols, out, ws, s);
+    const ColsumPlan p = colsum_plan(rows, cols, ws != nullptr, false);
+    uint16_t* const block = static_cast<uint16_t*>(const_cast<void*>(da));
+    return p.wide ? colsum_passes<false, 128>(p, nullptr, 0, nullptr, 0, block, ld, rows, cols, out, ws, s)
+                  : colsum_passes<false, 64>(p, nullptr, 0, nullptr, 0, block, ld, rows, cols, out, ws, s);
 }
-// da = dy * GeLU'(pre) and its column sums.  One pass where its workgroups keep the chip busy (half of the CUs), or where
-// the block is so small (4M elements, 4 us of traffic) that a launch costs more; else (no workspace, narrow block) the elementwise kernel's own grid and then the sums.
+// da = dy * GeLU'(pre) and its column sums, in one pass or in two (the elementwise kernel's own grid, then the sums; times
+// in us, one pass / two).
+//   One pass where no workgroup walks more than 384 rows (300 x 1024 6.9 / 7.3, 2048 x 1024 8.8 / 9.6, 8192 x 1024 15.1 / 17.5;
+//   one slab of 424 x 1792 9.9 / 8.7) or where at least 192 strips of 64 columns are at work (4096 x 12288, one slab, 70.5 / 77.4;
+//   32896 x 2560 121.6 / 120.9; below: 4096 x 8192, one slab, 64.9 / 59.0; 100000 x 8, 64 slabs, 71 / 18; 2048 x 2560, one slab, 33 / 20).
+//   Two passes where the last strip has 8 columns: half a 32-byte sector a row, 5 us by itself (300 x 136 11.5 / 6.8, 300 x 144
+//   6.6 / 7.0, 5760 x 8 15.2 / 7.1), or the only one less than 32 (300 x 16 6.3 / 5.5, 61 x 8 4.6 / 3.9); not for a few rows
+//   (88 x 2632 4.9 / 6.3, 14 x 8 3.3 / 3.8).
+//   Rows that start off cache lines leave each workgroup partial lines to write: two passes too, once the block is so large
+//   (7M elements) that traffic counts: 8192 x 656 14.0 / 15.0, 837 x 9752 22.2 / 20, 8192 x 6184 112 / 80, 32896 x 656 49 / 42;
+//   with one slab of wide strips from 32M on (941 x 29552 43 / 47, 4096 x 16400 116 / 108, 6717 x 27448 344 / 287).
 hipError_t launch_dgelu_colsum(const void* dy, int64_t ld_dy, const void* pre, int64_t ld_pre, void* da, int64_t ld, int64_t rows,
                                int64_t cols, float* out, float* ws, hipStream_t s) {
-    const int64_t wgs = (cols + COLSUM_COLS - 1) / COLSUM_COLS * (ws ? colsum_splits(rows, cols) : 1);
-    if (wgs >= 128 || rows * cols <= ((int64_t)1 << 22))
-        return colsum_passes<true>(static_cast<const uint16_t*>(dy), ld_dy, static_cast<const uint16_t*>(pre), ld_pre,
-                                   static_cast<uint16_t*>(da), ld, rows, cols, out, ws, s);
+    const ColsumPlan p = colsum_plan(rows, cols, ws != nullptr, true);
+    const bool off_lines = ((ld_dy | ld_pre | ld) & 63) || ((reinterpret_cast<uintptr_t>(dy) | reinterpret_cast<uintptr_t>(pre) |
+                                                             reinterpret_cast<uintptr_t>(da)) & 127);
+    const bool ragged = cols < 32 ? rows > 32 : cols % 64 == 8 && rows > 96;
+    const bool partial_lines = off_lines && rows * cols > ((int64_t)(p.wide && p.splits == 1 ? 32 : 7) << 20);
+    if (!ragged && !partial_lines && (p.per <= 384 || (cols + 63) / 64 * p.splits >= 192)) {
+        const uint16_t *g = static_cast<const uint16_t*>(dy), *a = static_cast<const uint16_t*>(pre);
+        uint16_t* const block = static_cast<uint16_t*>(da);
+        return p.wide ? colsum_passes<true, 128>(p, g, ld_dy, a, ld_pre, block, ld, rows, cols, out, ws, s)
+                      : colsum_passes<true, 64>(p, g, ld_dy, a, ld_pre, block, ld, rows, cols, out, ws, s);
+    }
     if (hipError_t e = launch_dgelu(dy, ld_dy, pre, ld_pre, da, ld, rows, cols, s); e != hipSuccess) return e;
     return launch_colsum(da, ld, rows, cols, out, ws, s);
 }

@@ -692,11 +692,14 @@ def test_workgroup_split_kernel_edges(m, k, n):
                   seed=S.BASE_SEED + seed, label=f"{m}x{k}x{n}")
 
 
-@pytest.mark.parametrize("rows,cols", [(1, 8), (33, 136), (257, 128), (700, 1032), (5000, 1024)])
+@pytest.mark.parametrize("rows,cols", [(1, 8), (33, 136), (96, 136), (97, 136), (257, 128), (700, 1032), (5000, 1024),
+                                       # one slab or several; strips of 64 or 128 columns; one pass or two; 1 .. 4 rows left over a lane
+                                       (384, 72), (384, 80), (385, 80), (512, 32), (513, 24), (1100, 6224), (672, 12288), (608, 12224), (576, 16400), (3000, 16384), (40000, 16), (2100, 4112)])
 @pytest.mark.parametrize("with_workspace", [True, False])
 def test_own_dA_and_bias_gradient_in_one_pass(rows, cols, with_workspace):
-    """The pass that forms the own dA block and sums its columns: the block is that of tp_dgelu and the sums are those of
-    tp_bias_grad on it, bit for bit, for one slab and several, ragged strips, and leading dimensions beyond the columns."""
+    """The own dA block and the sums of its columns, formed in one pass or in two: the block is that of tp_dgelu and the sums
+    are those of tp_bias_grad on it, bit for bit, for one slab and several, strips of either width and ragged ones, rows on
+    and off cache lines, and leading dimensions beyond the columns."""
     grid, dims = T.Grid(T.MODE_2D, q=1), (rows, 64, cols)
     g, a = (dev(S.normal_block_bf16(S.BASE_SEED + i, S.T_G, cols + 8, 0, rows, 0, cols + 8, 1.0))[:, :cols] for i in (1, 2))
     ws = torch.empty(max(T.tp_linear_workspace_size(grid, dims, T.PASS_DX), 16), dtype=torch.uint8, device="cuda") if with_workspace else None
