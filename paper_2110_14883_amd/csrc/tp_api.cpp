@@ -168,18 +168,21 @@ struct Plan {
 };
 
 // Costs in shader cycles, by macro-tile area (256 x 256; half; quarter).  k_tile: one 64-deep K tile of one
-// workgroup with the chip full; on a chip that is not, a K tile takes (1 - spare) of that plus spare in proportion
-// to the workgroups (clock and L2 are shared).  c_tile: what a C tile costs besides (epilogue, filling the
-// pipeline).  plane: cycles x 1667 per element and plane of a K split; launch: the fix-up launch; trim: a tail launch.
-struct Costs { double k_tile[3], c_tile[3], spare, plane, launch, trim; };
-// What the kernels take, fitted to a sweep of tiles and splits over eight shapes (0.1 .. 275 GFLOP, all three forms;
-// times in us, one round of 256 workgroups): a K tile 1.5 / 0.9 / 0.53 full and 0.95 / 0.6 / 0.36 alone (half tiles
-// are charged 10 % more: over many rounds their extra traffic costs clock).  The pick
-// is within 1.5 % of the best of the sweep in 23 of 24 products, within 9 % in all.
-constexpr Costs kRunCosts{{2730.0, 1800.0, 1000.0}, {20000.0, 14000.0, 10000.0}, 0.3, 4.0, 10000.0, 40000.0};
+// workgroup; c_tile: what a C tile costs besides (epilogue, filling the pipeline).  plane: cycles x 1667 per element
+// and plane of a K split; launch: the fix-up launch; trim: a tail launch.
+struct Costs { double k_tile[3], c_tile[3], plane, launch, trim; };
+// What the kernels take, fitted together with small_cost below to every admissible tile and split of 3700 drawn products
+// (0.2 .. 250 GFLOP, all forms, grouped ones too), each timed with its operands in rotation over 450 MB, i.e. from
+// memory as a step of a model finds its weights, and again with them in the caches.  Over those products the pick takes 1 %
+// (from memory) and 1.6 % (cached) more than the best of them; constants fitted to cached operands alone took 7 % and left 345 of
+// the 3700 slower than the eight-wave kernel's plan, up to 1.45 x: from memory a K tile of few workgroups takes its full time,
+// and a split that spreads it pays (4 products of 678 x 4240 x 168: 46.5 us whole, 32.3 split in five).
+// (The half tiles' K tile fits 1670 to 1870; the upper end, as over many rounds their extra traffic costs clock: dW 14744 x 13568 x 1640
+// 710 us in three rounds of 256 x 128, 660 in two of 256 x 256.)
+constexpr Costs kRunCosts{{2730.0, 1870.0, 1200.0}, {21000.0, 15000.0, 10000.0}, 4.5, 6500.0, 52000.0};
 // What the workspace query has always been computed from.  Callers size and keep workspaces by it, so it goes on
 // deciding how many bytes a call needs (and which calls are refused); the plan that runs stays within them.
-constexpr Costs kQueryCosts{{2730.0, 2220.0, 1410.0}, {12000.0, 20000.0, 20000.0}, 0.0, 8.0, 12000.0, 15000.0};
+constexpr Costs kQueryCosts{{2730.0, 2220.0, 1410.0}, {12000.0, 20000.0, 20000.0}, 8.0, 12000.0, 15000.0};
 
 int area_class(int bm, int bn) { return bm * bn == 65536 ? 0 : (bm * bn == 32768 ? 1 : 2); }
 
@@ -211,9 +214,8 @@ Plan plan_whole(const Costs& cs, const Opts& o, int64_t m, int64_t n, int64_t k,
             if (z > T) break;
             Plan c{tile_ids[ti], bm, bn, (int)tm, (int)tn, z, 4, groups, 0, 0, 0, 0, 0, 0};
             if (ws_bytes_for(c, m, n) > limit) break;
-            const int64_t full = tiles * z / kCUs, rem = tiles * z % kCUs;
-            const double k_cost = (double)((T + z - 1) / z) * cs.k_tile[cls], last = 1.0 - cs.spare + cs.spare * (double)rem / kCUs;
-            const double main_cost = (double)full * (k_cost + cs.c_tile[cls]) + (rem ? k_cost * last + cs.c_tile[cls] : 0.0);
+            const int64_t rounds = (tiles * z + kCUs - 1) / kCUs;
+            const double main_cost = (double)rounds * ((double)((T + z - 1) / z) * cs.k_tile[cls] + cs.c_tile[cls]);
             const double fix = z > 1 ? ((double)m * n * cs.plane * z / 1667.0 + cs.launch) * groups : 0.0;
             const double cost = main_cost + fix;
             if (cost < best_cost) {
@@ -264,17 +266,25 @@ Plan plan_by(const Costs& cs, const Opts& o, int64_t m, int64_t n, int64_t k, in
     return best;
 }
 
-// The same for the kernel that splits K over the waves of a workgroup (no partial planes, one launch): `wgs`
-// workgroups, T chunks of 64 k each.  Fitted to 22 shapes, each form, up to 512 workgroups and 64 (NN) or 256 chunks
-// (replayed graphs): 2 - 2.5 us per launch, then per round of 256 workgroups 1.6 - 1.9 us and 0.06 - 0.12 us a chunk.
-// Both sides: 128 x 2048 x 512, 2 steps, forward 5.2 us against 14.0 (128 x 128, split 4 and fix-up); 300 x 328 x 136, 2 steps
-// 4.7 / 4.4 / 4.3 us against 10.0 / 9.4 / 8.2; 64 x 4096 x 4096 dX 9.8 against 14.4.  Beyond, the larger tiles' reuse of
-// operands wins: 1024 x 256 x 1024 dX (1024 workgroups) 11.3 against 6.5, 16 x 16384 x 4096 forward 27.1 against 27.4.
-double small_cost(int form, int64_t wgs, int64_t T) {
+// The same for the kernel that splits K over the waves of a workgroup (no partial planes, one launch): `wgs` workgroups of bm
+// rows, T chunks of 64 k each, operands of `bytes` in all.  Its few bytes in flight per wave make a chunk's time a matter of where
+// the operands are and of how many workgroups ask (0.07 us a chunk cached and alone, 0.18 from memory, 0.5 with two rounds):
+// fitted with kRunCosts, up to 512 workgroups and 256 chunks.  Both sides, from memory, in us: 128 x 2048 x 1024 forward 8.1
+// against 12.4 (128 x 128, split 8 and fix-up), 7 x 9128 x 4360 dX 28.4 / 31.5, 40 x 1192 x 4064 dW 11.7 / 13.6; and where it loses,
+// many workgroups with many chunks: 2176 x 7760 x 32 dW, four products, 58.6 / 37.3, 57 x 2552 x 320 dX, four steps, 32.8 / 23.5.
+//   At most 16 rows (bm) leave room for a third slot a wave: one more chunk on its way, hardly any time a chunk of its own.
+//   dW of less than 1 MB of operands finds them in the L2 (32 x 1736 x 16, three steps, 8.3 / 12.1).
+//   NN stops at 64 chunks whatever the costs say.  It reads 64-byte pieces of weight rows, and the line depends on where
+//   they are: 16 x K x 4096 from memory is even at K = 3072 (13.6 / 13.7; 4096: 20.1 / 15.2), from L2 at 5000 (4608: 14.6 / 15.4;
+//   5120: 16.5 / 16.0); 16 x K x 1024 at 4096 (12.9 / 12.5) and beyond 12288 (14.0 / 19.3).
+double small_cost(int form, int bm, int64_t wgs, int64_t T, double bytes) {
     if (wgs > 2 * kCUs || T > (form == FORM_NN ? 64 : 256)) return 1e300;
-    const double launch = form == FORM_NN ? 4500.0 : 3600.0, round = form == FORM_TN ? 3450.0 : 2900.0;
-    const double chunk = form == FORM_NN ? 220.0 : (form == FORM_NT ? 137.0 : 110.0);
-    return launch + (double)((wgs + kCUs - 1) / kCUs) * (round + chunk * (double)T);
+    struct C { double launch, round, chunk, crowd; };
+    const C c = form == FORM_NN   ? C{1500.0, 4500.0, 155.0, 290.0}
+                : form == FORM_TN ? C{150.0, 7300.0, bytes < 1e6 ? 60.0 : 260.0, 160.0}
+                : bm == 16        ? C{2200.0, 6900.0, 10.0, 320.0}
+                                  : C{300.0, 8400.0, 200.0, 50.0};
+    return c.launch + (double)((wgs + kCUs - 1) / kCUs) * c.round + (double)T * (c.chunk + c.crowd * (double)wgs / kCUs);
 }
 
 // Bytes of workspace a call needs, and the plan the eight-wave kernel runs: its costs are those the query is made of.
@@ -294,7 +304,10 @@ Plan make_plan(const Opts& o, int form, int64_t m, int64_t n, int64_t k, int n_s
     if (!o.tile && !o.split) {
         const int bm = m <= 16 && form != FORM_TN ? 16 : 32;
         const int64_t tm = (m + bm - 1) / bm, tn = (n + 31) / 32;
-        if (1.1 * small_cost(form, tm * tn * groups, (int64_t)n_steps * ((k + 63) / 64)) < cost)
+        // (the products of a grouped launch share one operand)
+        const double bytes = 2.0 * (double)k * (form == FORM_NT ? (double)m * n_steps + (double)n * n_steps * groups
+                                                                : (double)m * n_steps * groups + (double)n * n_steps);
+        if (small_cost(form, bm, tm * tn * groups, (int64_t)n_steps * ((k + 63) / 64), bytes) < cost)
             p = Plan{bm == 16 ? TILE_16x32_SMALL : TILE_32x32_SMALL, bm, 32, (int)tm, (int)tn, 1, o.group > 0 ? o.group : 4, groups, 0, 0, 0, 0, 0, 0};
     }
     p.need = need;

@@ -829,3 +829,28 @@ def test_products_beyond_32_bit_offsets_keep_their_k_split_and_walk_many_tiles()
         if tile == 0:
             assert need >= 8 * m * n * 4 and not bool(torch.isnan(ws[:8 * m * n]).any())
         del dx
+
+
+@pytest.mark.parametrize("kind,m,k,n,count", [("dW", 3640, 5992, 104, 1), ("dX partials", 678, 4240, 168, 4)])
+def test_long_k_and_few_large_tiles_are_split_over_workgroups(kind, m, k, n, count):
+    """Products whose K the plan splits over workgroups because neither the kernel that splits it inside a workgroup (many
+    workgroups, many chunks) nor whole tiles (few of them, operands from memory) keep up: the partial planes fill the
+    workspace, and the results are the oracle's."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(15)
+    rnd = lambda *shape: torch.randn(shape, generator=gen, device="cuda").to(torch.bfloat16)
+    grid = T.Grid(T.MODE_2D, q=count)
+    dims, pass_ = ((k, m, n), T.PASS_DW) if kind == "dW" else ((m * count, n * count, k * count), T.PASS_DX_PARTIALS)
+    ws = torch.full((max(T.tp_linear_workspace_size(grid, dims, pass_), 256) // 4,), float("nan"), dtype=torch.float32, device="cuda")
+    outs = [torch.empty((m, n), dtype=torch.float32, device="cuda") for _ in range(count)]
+    if kind == "dW":
+        x, da = rnd(k, m), rnd(k, n).mul_(0.02)
+        T.tp_linear_bwd(grid, dims, 0, 1, x_blocks_dw=[x], da_col_blocks=[da], dw=outs[0], workspace=ws)
+        refs = [host64(x).T @ host64(da)]
+    else:
+        da, w = rnd(m, k), [rnd(n, k).mul_(0.02) for _ in range(count)]
+        T.tp_linear_bwd_partials(grid, dims, da, w, outs, workspace=ws)
+        refs = [host64(da) @ host64(b).T for b in w]
+    for i, ref in enumerate(refs):
+        check(host64(outs[i]), ref, "f32", f"{kind} {i}")
+    assert not bool(torch.isnan(ws[:2 * count * m * n]).any())
