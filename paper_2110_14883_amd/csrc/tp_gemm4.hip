@@ -36,7 +36,8 @@ constexpr int W4_LDS_BYTES = W4_EPI_BASE + 4 * W4_EPI_BYTES_PER_WAVE;
 
 }  // namespace
 
-template <bool A_KC, bool B_KC, int EPI, bool F32_OUT>
+// A_LATE: see k_tile
+template <bool A_KC, bool B_KC, int EPI, bool F32_OUT, bool A_LATE>
 __global__ __launch_bounds__(W4_THREADS) __attribute__((amdgpu_waves_per_eu(1, 1)))
 void tp_gemm4_kernel(const GemmArgs p) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
@@ -109,7 +110,7 @@ void tp_gemm4_kernel(const GemmArgs p) {
         c.left = uni((T - z + Z - 1) / Z);        // K tiles z, z + Z, ... of the n_steps x KT sequence
         c.odd = c.left & 1; c.live = 1;
     };
-    Cursor f, c;                                  // fetch cursor (three K tiles ahead) and compute cursor
+    Cursor f, c;                                  // fetch cursor (one K tile ahead, two from the middle of a K tile on) and compute cursor
 
     // ------------------------------------------------------------------ loads
     // Per (C tile, step) an operand has one buffer descriptor that starts at the tile's first row (or
@@ -239,16 +240,17 @@ void tp_gemm4_kernel(const GemmArgs p) {
     //   reads: those of MFMA step ks + 1 during step ks (every other slot when there are 8, every slot but
     //     every fourth when 12, every slot when 16); those of step 0 of the NEXT K tile during step 3,
     //     from the other stage, after the barrier before slot 48;
-    //   loads: operand B of the K tile at the fetch cursor during step 0 (into the stage being refilled),
-    //     then the cursor moves on, and after the barrier operand A of the following K tile goes into the
-    //     stage this body has just finished reading.  All four waves run the same schedule, so a slot with
-    //     a load asks the CU's one address path for 4 KB (64 B/clk: two slots): loads every other slot.
+    //   loads: the LATE operand of the K tile at the fetch cursor from slot 1 on (into the stage being refilled), then
+    //     the cursor moves on, and after the barrier the EARLY operand of the following K tile goes into the stage this
+    //     body has just finished reading.  All four waves run the same schedule, so a slot with a load asks the CU's one
+    //     address path for 4 KB (64 B/clk: two slots): loads every other slot, over step 0 and over step 3.
     //   Where the rows of a contraction-contiguous operand do not start on cache lines, each of its loads asks for 16 lines
-    //   and not 8 (four slots of the address path), and bunched loads hold up the MFMAs behind them: in the NN form
-    //   operand A is the late one, and in both forms with such an A the late operand has a load every fourth slot.
-    //   8192 x 4096, K = 12528: 728 -> 690 us (NN); 19633 x 3424, K = 4880: 647 -> 625 (NN), 658 -> 640 (NT); aligned rows
-    //   gain up to 1 %.
-    constexpr bool A_LATE = A_KC && !B_KC;
+    //   and not 8 (four slots of the address path), and bunched loads hold up the MFMAs behind them: in the NT form the late
+    //   operand has a load every fourth slot (19633 x 3424, K = 4880: 669 -> 648 us; aligned rows: no difference).
+    //   In the NN form the late operand is A if its rows are off the lines (the early one lands under fewer MFMAs: 8192 x 4096,
+    //   K = 12528: 751 us against 778, 8448 x 4096, K = 4456: 347 / 375) or if C is at least as tall as wide in tiles
+    //   (16384 x 4096, K = 4096: 469 / 474; 2048 x 2048, K = 32768: 240 / 245), else B (4096 x 24576, K = 6144: 988 us against
+    //   1036; 8192 x 24576 1963 / 2051).  From memory; every fourth slot instead costs up to 2 % here.
     using Late = std::integral_constant<bool, A_LATE>;
     using Early = std::integral_constant<bool, !A_LATE>;
     auto k_tile = [&](auto S_) __attribute__((always_inline)) {
@@ -271,8 +273,8 @@ void tp_gemm4_kernel(const GemmArgs p) {
             if constexpr (NR == 8)       { if constexpr (q % 2 == 0) read_n(std::integral_constant<int, q / 2>{}, KN{}, ST{}); }
             else if constexpr (NR == 12) { if constexpr (q % 4 != 3) read_n(std::integral_constant<int, q - q / 4>{}, KN{}, ST{}); }
             else                         read_n(std::integral_constant<int, q>{}, KN{}, ST{});
-            if constexpr (A_KC) { if constexpr ((s & 3) == 1 && s < 32) dtl1(Late{}, std::integral_constant<int, s / 4>{}, SW{}); }
-            else                  { if constexpr ((s & 1) == 1 && s < 16) dtl1(Late{}, std::integral_constant<int, s / 2>{}, SW{}); }
+            if constexpr (A_KC && B_KC) { if constexpr ((s & 3) == 1 && s < 32) dtl1(Late{}, std::integral_constant<int, s / 4>{}, SW{}); }
+            else                          { if constexpr ((s & 1) == 1 && s < 16) dtl1(Late{}, std::integral_constant<int, s / 2>{}, SW{}); }
             if constexpr ((s & 1) == 1 && s > 48) dtl1(Early{}, std::integral_constant<int, (s - 49) / 2>{}, SR{});
             if constexpr (s == 38) advance_fast();
             if constexpr (s == 40) { if (f_reopen) advance_slow(); }
@@ -287,8 +289,8 @@ void tp_gemm4_kernel(const GemmArgs p) {
     c = f;
     open_operand(std::true_type{});
     open_operand(std::false_type{});
-    // K tile 0 -> stage 0 (both operands), operand A of K tile 1 -> stage 1; operand B of K tile 1 is the
-    // first thing the loop body loads
+    // K tile 0 -> stage 0 (both operands), the early operand of K tile 1 -> stage 1; the late operand of K tile 1
+    // is the first thing the loop body loads
     using S0 = std::integral_constant<int, 0>;
     using S1 = std::integral_constant<int, 1>;
     prep_tile();
@@ -317,21 +319,32 @@ void tp_gemm4_kernel(const GemmArgs p) {
 // ---------------------------------------------------------------------------------------------
 // host launcher
 // ---------------------------------------------------------------------------------------------
-template <bool A_KC, bool B_KC, int EPI, bool F32_OUT>
-static hipError_t launch4_one(const GemmArgs& a, hipStream_t stream) {
+template <bool A_KC, bool B_KC, int EPI, bool F32_OUT, bool A_LATE>
+static hipError_t launch4_late(const GemmArgs& a, hipStream_t stream) {
     static std::atomic<uint64_t> attr_done{0};
     int dev = 0;
     if (hipError_t e = hipGetDevice(&dev); e != hipSuccess) return e;
     const uint64_t bit = 1ull << (dev & 63);
     if (!(attr_done.load(std::memory_order_relaxed) & bit)) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&tp_gemm4_kernel<A_KC, B_KC, EPI, F32_OUT>),
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&tp_gemm4_kernel<A_KC, B_KC, EPI, F32_OUT, A_LATE>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, W4_LDS_BYTES);
         if (e != hipSuccess) return e;
         attr_done.fetch_or(bit, std::memory_order_relaxed);
     }
     const int total = a.tiles_m * a.tiles_n * a.split_k;
     const unsigned grid = (unsigned)(total < a.max_workgroups ? total : a.max_workgroups);
-    return launch_kernel(tp_gemm4_kernel<A_KC, B_KC, EPI, F32_OUT>, dim3(grid), dim3(W4_THREADS), W4_LDS_BYTES, stream, a);
+    return launch_kernel(tp_gemm4_kernel<A_KC, B_KC, EPI, F32_OUT, A_LATE>, dim3(grid), dim3(W4_THREADS), W4_LDS_BYTES, stream, a);
+}
+
+// the operand whose loads come late (the figures are at k_tile)
+template <bool A_KC, bool B_KC, int EPI, bool F32_OUT>
+static hipError_t launch4_one(const GemmArgs& a, hipStream_t s) {
+    if constexpr (A_KC && !B_KC) {
+        bool a_late = a.tiles_m >= a.tiles_n;
+        for (int k = 0; k < a.n_steps; ++k) a_late |= (a.lda[k] & 63) || (reinterpret_cast<uintptr_t>(a.a[k]) & 127);
+        if (a_late) return launch4_late<A_KC, B_KC, EPI, F32_OUT, true>(a, s);
+    }
+    return launch4_late<A_KC, B_KC, EPI, F32_OUT, false>(a, s);
 }
 
 hipError_t launch_gemm4(int form, const GemmArgs& a, hipStream_t s) {

@@ -854,3 +854,14 @@ def test_long_k_and_few_large_tiles_are_split_over_workgroups(kind, m, k, n, cou
     for i, ref in enumerate(refs):
         check(host64(outs[i]), ref, "f32", f"{kind} {i}")
     assert not bool(torch.isnan(ws[:2 * count * m * n]).any())
+
+
+@pytest.mark.parametrize("m,n", [(300, 1416), (1300, 264)])
+@pytest.mark.parametrize("k", [64, 128, 192, 200])
+def test_either_operand_of_the_stream_kernel_forward_late(m, n, k):
+    """The forward on 256 x 256 tiles with operand B late (rows of A on cache lines, C wider than tall) and with operand A
+    late (rows off the lines, or C as tall as wide): one K tile a step to four, two steps, K whole and split."""
+    for split in (1, 3):
+        with overrides(tile=1, split=split if 2 * ((k + 63) // 64) >= split else 2):
+            run_share(T.Grid(T.MODE_2D, q=2, ri=0, rj=1), (2 * m, 2 * k, 2 * n), backward=False, y_dtype="f32" if split == 1 else "bf16",
+                      label=f"{m} x {k} x {n} split {split}")
