@@ -296,3 +296,17 @@ def test_static_entry_point_refuses_what_its_scratch_cannot_hold():
     with pytest.raises(T.TpError) as e:
         T.tp_linear_fwd_static(grid, dims, 1, [(0x10000, k)], [(0x20000, n)], None, T.EPI_NONE, (0x30000, n, B.DT_F32), stream=0)
     assert e.value.status == 9 and "scratch" in str(e.value)
+
+
+def test_typed_prototypes_of_the_loaded_library():
+    """`lib()` takes the C ABI's own types: a single block as a structure, an array or a pointer to either; and nothing else
+    for a block pointer.  (Arguments that the library refuses before it looks for a GPU.)"""
+    L, grid, dims, none = T.lib(), T.Grid(T.MODE_2D)._c(), B._DimsS(8, 8, 8), B._OBlk(None, 0, 0)
+    block, out = B._CBlk(4096, 8), B._OBlk(4096, 8, 1)
+    for blocks in (block, (B._CBlk * 1)(block), C.byref(block), C.pointer(block)):
+        assert L.tp_linear_fwd(grid, dims, 0, blocks, blocks, None, 0, out, none, None, 0, None) == 4          # n_steps
+        assert L.tp_linear_bwd(grid, dims, 0, 0, None, None, blocks, blocks, None, None, -1, -1, None, out, none, none, None, None, 0, None) == 4
+        assert L.tp_linear_bwd_partials(grid, dims, 2, 0, blocks, blocks, C.pointer(out), None, None, None, 0, None) == 4
+    for blocks in (dims, (C.c_int64 * 2)(4096, 8)):
+        with pytest.raises(C.ArgumentError):
+            L.tp_linear_fwd(grid, dims, 0, blocks, blocks, None, 0, out, none, None, 0, None)
