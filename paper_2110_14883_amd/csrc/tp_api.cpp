@@ -176,7 +176,7 @@ struct Costs { double k_tile[3], c_tile[3], plane, launch, trim; };
 // memory as a step of a model finds its weights, and again with them in the caches.  Over those products the pick takes 1 %
 // (from memory) and 1.6 % (cached) more than the best of them; constants fitted to cached operands alone took 7 % and left 345 of
 // the 3700 slower than the eight-wave kernel's plan, up to 1.45 x: from memory a K tile of few workgroups takes its full time,
-// and a split that spreads it pays (4 products of 678 x 4240 x 168: 46.5 us whole, 32.3 split in five).
+// and a split that spreads it pays (4 products of 678 x 4240 x 168: 46.5 us whole, 28.5 split in five).
 // (The half tiles' K tile fits 1670 to 1870; the upper end, as over many rounds their extra traffic costs clock: dW 14744 x 13568 x 1640
 // 710 us in three rounds of 256 x 128, 660 in two of 256 x 256.)
 constexpr Costs kRunCosts{{2730.0, 1870.0, 1200.0}, {21000.0, 15000.0, 10000.0}, 4.5, 6500.0, 52000.0};
