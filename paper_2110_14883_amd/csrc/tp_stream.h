@@ -56,6 +56,11 @@ template <int N> __device__ __forceinline__ void wait_vm() {      // at most N v
 // dropped by the range check, and a lane whose columns lie beyond N carries an out-of-range offset.
 // One slab = 32 rows x 32 TN columns passes through the wave's LDS patch `eps` (2 TN KB, at least 4) so that
 // stores are whole row segments.  ACC_HALF: the accumulators live in the accumulator half of the register file.
+// Outputs leave with the streaming hint, K-split planes without: an output is not read again by this launch, and as ordinary lines
+// of the L2 it drives out the operand panels that the XCD's other workgroups are about to read (6144 x 24576 fp32, K = 4096: 991 ->
+// 905 us; 32896 x 2560 bf16 twice, K = 2 x 640: 287 -> 272; 8192 x 1024 bf16, K = 2 x 1024: 43 -> 40).  The planes are read by the fix-up
+// at once, from wherever they still are: with the hint 520 x 2056 in three planes takes 23.2 us against 21.8.
+constexpr int ST_PLAIN = 0, ST_STREAM = 2;        // cache policy bits of a buffer store
 template <int TM, int TN, int EPI, bool F32_OUT, bool ACC_HALF>
 __device__ __forceinline__ void store_c_block(const GemmArgs& p, f32x16_t (&acc)[TM][TN], const int m_sub, const int n_sub,
                                               const int z, const int g_out, char* const eps) {
@@ -149,12 +154,12 @@ __device__ __forceinline__ void store_c_block(const GemmArgs& p, f32x16_t (&acc)
         for (int it = 0; it < 32 / RPI; ++it) {
             const int rr = it * RPI + l / CPR;
             const u32x4_t v = *reinterpret_cast<const u32x4_t*>(eps + rr * (16 * CPR) + ((cc ^ swz(rr)) << 4));
-            __builtin_amdgcn_raw_buffer_store_b128(v, rs, (int)(lane + (uint32_t)((32 * i + RPI * it) * ld * 2)), 0, 0);
+            __builtin_amdgcn_raw_buffer_store_b128(v, rs, (int)(lane + (uint32_t)((32 * i + RPI * it) * ld * 2)), 0, ST_STREAM);
         }
     };
     // fp32 slab, one 32-column block at a time: rows of 128 bytes; lane l stores columns
     // 4 (l % 8) .. + 3 of rows l / 8 + 8 it
-    auto slab_f32 = [&](int i, auto value4, __amdgpu_buffer_rsrc_t rs, int ld) __attribute__((always_inline)) {
+    auto slab_f32 = [&](int i, auto value4, auto policy, __amdgpu_buffer_rsrc_t rs, int ld) __attribute__((always_inline)) {
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
             const int n = n_sub + 32 * j + 4 * (l & 7);
@@ -170,7 +175,7 @@ __device__ __forceinline__ void store_c_block(const GemmArgs& p, f32x16_t (&acc)
             for (int it = 0; it < 4; ++it) {
                 const int rr = it * 8 + (l >> 3), cc = l & 7;
                 const u32x4_t v = *reinterpret_cast<const u32x4_t*>(eps + rr * 128 + ((cc ^ ((rr >> 1) & 7)) << 4));
-                __builtin_amdgcn_raw_buffer_store_b128(v, rs, (int)(lane + (uint32_t)((32 * i + 8 * it) * ld * 4)), 0, 0);
+                __builtin_amdgcn_raw_buffer_store_b128(v, rs, (int)(lane + (uint32_t)((32 * i + 8 * it) * ld * 4)), 0, decltype(policy)::value);
             }
         }
     };
@@ -180,7 +185,7 @@ __device__ __forceinline__ void store_c_block(const GemmArgs& p, f32x16_t (&acc)
         const __amdgpu_buffer_rsrc_t rs_ws = block_rsrc(p.ws + ((int64_t)z * p.n_groups + g_out) * p.M * p.N, (int64_t)p.N, 4);
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
-            slab_f32(i, raw4, rs_ws, p.N);
+            slab_f32(i, raw4, std::integral_constant<int, ST_PLAIN>{}, rs_ws, p.N);
             __builtin_amdgcn_sched_barrier(0);
         }
     } else {
@@ -194,7 +199,7 @@ __device__ __forceinline__ void store_c_block(const GemmArgs& p, f32x16_t (&acc)
             if constexpr (!use_dg) {
                 if (use_pre) slab_bf16(i, preact4, rs_pre, (int)p.ldp);
             }
-            if constexpr (F32_OUT) slab_f32(i, final4, rs_out, ldo);
+            if constexpr (F32_OUT) slab_f32(i, final4, std::integral_constant<int, ST_STREAM>{}, rs_out, ldo);
             else                   slab_bf16(i, final4, rs_out, ldo);
             __builtin_amdgcn_sched_barrier(0);
         }
