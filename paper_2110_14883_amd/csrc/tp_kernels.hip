@@ -315,31 +315,41 @@ __global__ __launch_bounds__(NTHREADS) void tp_gemm_kernel(const GemmArgs p) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// split-K fix-up: sum the fp32 partials in a fixed order, then the same epilogue
+// position of a thread in a block of rows x `per_row` pieces: idx / per_row without a division (the 64-bit one is 150
+// instructions a thread).  magic = floor(2^(31 + shift) / per_row) + 1 with 2^(shift - 1) < per_row <= 2^shift is exact for idx < 2^31,
+// which is what one launch covers.
 // ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void tp_reduce_kernel(const ReduceArgs p) {
-    const int n4 = p.N >> 2;
-    const int64_t total = (int64_t)p.M * n4;
-    const int64_t plane = p.plane;
-    Epilogue e{p.out, p.ldo, p.out_f32, p.pre, p.ldp, p.bias, p.gelu, p.dg, p.lddg};
-    for (int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; idx < total;
-         idx += (int64_t)gridDim.x * blockDim.x) {
-        const int m = (int)(idx / n4);
-        const int n = (int)(idx - (int64_t)m * n4) * 4;
-        const float* src = p.ws + (int64_t)m * p.N + n;
-        f32x4_t s = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(src));
-        for (int zz = 1; zz < p.split_k; ++zz) {
-            const f32x4_t q = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(src + zz * plane));
-            s[0] += q[0]; s[1] += q[1]; s[2] += q[2]; s[3] += q[3];
-        }
-        float v[4] = {s[0], s[1], s[2], s[3]};
-        epilogue4(e, v, m, n);
-    }
+struct RowOf { uint32_t per_row, magic, shift; };
+__device__ __forceinline__ uint32_t row_of(const RowOf d, uint32_t idx, uint32_t& in_row) {
+    const uint32_t r = (uint32_t)(((uint64_t)idx * d.magic) >> (31 + d.shift));
+    in_row = idx - r * d.per_row;
+    return r;
 }
 
 // ---------------------------------------------------------------------------------------------
-// da = bf16(dy * GeLU'(pre)).  8 elements per 128-bit access; every thread keeps two independent
-// trips (four loads) in flight.  GeLU'(a) = 1 + h for a >= 0 and -h for a < 0 with
+// split-K fix-up: sum the fp32 partials in a fixed order, then the same epilogue.  Z: number of planes, all of a
+// thread's loads in flight together.  Bound by memory (the planes), by latency where they are small.
+// ---------------------------------------------------------------------------------------------
+template <int Z>
+__global__ __launch_bounds__(256) void tp_reduce_kernel(const ReduceArgs p, const uint32_t total, const RowOf d) {
+    const uint32_t idx = blockIdx.x * 256u + threadIdx.x;
+    if (idx >= total) return;
+    uint32_t n4;
+    const int m = (int)row_of(d, idx, n4), n = (int)n4 * 4;
+    Epilogue e{p.out, p.ldo, p.out_f32, p.pre, p.ldp, p.bias, p.gelu, p.dg, p.lddg};
+    const float* const src = p.ws + (int64_t)m * p.N + n;
+    f32x4_t q[Z];
+#pragma unroll
+    for (int z = 0; z < Z; ++z) q[z] = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(src + z * p.plane));
+    f32x4_t s = q[0];
+#pragma unroll
+    for (int z = 1; z < Z; ++z) { s[0] += q[z][0]; s[1] += q[z][1]; s[2] += q[z][2]; s[3] += q[z][3]; }
+    float v[4] = {s[0], s[1], s[2], s[3]};
+    epilogue4(e, v, m, n);
+}
+
+// ---------------------------------------------------------------------------------------------
+// da = bf16(dy * GeLU'(pre)).  8 elements per 128-bit access.  GeLU'(a) = 1 + h for a >= 0 and -h for a < 0 with
 // h = |a| phi(a) - Phi(-|a|), which needs the sign only once, at the end.
 // ---------------------------------------------------------------------------------------------
 __device__ __forceinline__ float dgelu_times(float g, float a) {
@@ -361,55 +371,50 @@ __device__ __forceinline__ u32x4_t dgelu8(const u32x4_t g, const u32x4_t a) {
         o[i] = pack_bf16(dgelu_times(bf16_lo(g[i]), bf16_lo(a[i])), dgelu_times(bf16_hi(g[i]), bf16_hi(a[i])));
     return o;
 }
-// One 128-bit access per thread and a grid that covers the block (the loop only runs again beyond 2^30
-// workgroups): neighbouring workgroups then touch neighbouring memory, which measured 15 % faster than a
-// persistent grid-stride loop with several loads in flight; the streaming (nontemporal) hint on loads and
-// stores is worth another 9 %: 6.4 TB/s against 5.9 for a plain bf16 add of the same shape.
-__global__ __launch_bounds__(256) void tp_dgelu_kernel(const uint16_t* dy, int64_t ld_dy, const uint16_t* pre,
-                                                       int64_t ld_pre, uint16_t* da, int64_t ld_da,
-                                                       int64_t rows, int cols8) {
-    const int64_t total = rows * cols8;
-    for (int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; idx < total;
-         idx += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t r = idx / cols8;
-        const int c = (int)(idx - r * cols8) * 8;
-        const u32x4_t g = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(dy + r * ld_dy + c));
-        const u32x4_t a = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(pre + r * ld_pre + c));
-        __builtin_nontemporal_store(dgelu8(g, a), reinterpret_cast<u32x4_t*>(da + r * ld_da + c));
-    }
+// One 128-bit access per thread and a grid that covers the block: neighbouring workgroups then touch neighbouring memory, which
+// measured 15 % faster than a persistent grid-stride loop with several loads in flight; the streaming (nontemporal) hint on loads and
+// stores is worth another 9 %: 4096 x 24576 in 92 us, 6.6 TB/s (98 us with a 64-bit division a thread), against 5.9 for a plain bf16 add.
+__global__ __launch_bounds__(256) void tp_dgelu_kernel(const uint16_t* dy, int64_t ld_dy, const uint16_t* pre, int64_t ld_pre, uint16_t* da,
+                                                       int64_t ld_da, const uint32_t total, const RowOf d) {
+    const uint32_t idx = blockIdx.x * 256u + threadIdx.x;
+    if (idx >= total) return;
+    uint32_t c8;
+    const int64_t r = row_of(d, idx, c8);
+    const uint32_t c = c8 * 8;
+    const u32x4_t g = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(dy + r * ld_dy + c));
+    const u32x4_t a = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(pre + r * ld_pre + c));
+    __builtin_nontemporal_store(dgelu8(g, a), reinterpret_cast<u32x4_t*>(da + r * ld_da + c));
 }
 
-// y = [GeLU](c + bias) over an fp32 block (what follows the summation of forward partials),
-// optional bf16 copy of c + bias; 4 elements per thread, same launch shape and hints as tp_dgelu_kernel
-__global__ __launch_bounds__(256) void tp_bias_act_kernel(const float* c, int64_t ldc, const uint16_t* bias, int gelu,
-                                                          void* y, int64_t ldy, int y_f32, uint16_t* pre, int64_t ldp,
-                                                          int64_t rows, int cols4) {
-    const int64_t total = rows * cols4;
-    for (int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; idx < total;
-         idx += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t r = idx / cols4;
-        const int n = (int)(idx - r * cols4) * 4;
-        const f32x4_t x = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(c + r * ldc + n));
-        float v[4] = {x[0], x[1], x[2], x[3]};
-        if (bias) {
-            const u32x2_t b = *reinterpret_cast<const u32x2_t*>(bias + n);
-            v[0] += bf16_lo(b[0]); v[1] += bf16_hi(b[0]); v[2] += bf16_lo(b[1]); v[3] += bf16_hi(b[1]);
-        }
-        if (pre) {
-            const u32x2_t s = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
-            __builtin_nontemporal_store(s, reinterpret_cast<u32x2_t*>(pre + r * ldp + n));
-        }
-        if (gelu) {
+// y = [GeLU](c + bias) over an fp32 block (what follows the summation of forward partials), optional bf16 copy of
+// c + bias; 4 elements per thread (8 are 8 % slower), same launch shape and hints as tp_dgelu_kernel.  What is written is
+// compiled in: between branches the second store waits for the first.
+template <bool GELU, bool PRE, bool F32>
+__global__ __launch_bounds__(256) void tp_bias_act_kernel(const float* c, int64_t ldc, const uint16_t* bias, void* y, int64_t ldy, uint16_t* pre,
+                                                          int64_t ldp, const uint32_t total, const RowOf d) {
+    const uint32_t idx = blockIdx.x * 256u + threadIdx.x;
+    if (idx >= total) return;
+    uint32_t n4;
+    const int64_t r = row_of(d, idx, n4);
+    const uint32_t n = n4 * 4;
+    f32x4_t v = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(c + r * ldc + n));
+    if (bias) {
+        const u32x2_t b = *reinterpret_cast<const u32x2_t*>(bias + n);
+        v[0] += bf16_lo(b[0]); v[1] += bf16_hi(b[0]); v[2] += bf16_lo(b[1]); v[3] += bf16_hi(b[1]);
+    }
+    if constexpr (PRE) {
+        const u32x2_t s = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
+        __builtin_nontemporal_store(s, reinterpret_cast<u32x2_t*>(pre + r * ldp + n));
+    }
+    if constexpr (GELU) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) v[i] = gelu_f(v[i]);
-        }
-        if (y_f32) {
-            const f32x4_t o = {v[0], v[1], v[2], v[3]};
-            __builtin_nontemporal_store(o, reinterpret_cast<f32x4_t*>(static_cast<float*>(y) + r * ldy + n));
-        } else {
-            const u32x2_t o = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
-            __builtin_nontemporal_store(o, reinterpret_cast<u32x2_t*>(static_cast<uint16_t*>(y) + r * ldy + n));
-        }
+        for (int i = 0; i < 4; ++i) v[i] = gelu_f(v[i]);
+    }
+    if constexpr (F32) {
+        __builtin_nontemporal_store(v, reinterpret_cast<f32x4_t*>(static_cast<float*>(y) + r * ldy + n));
+    } else {
+        const u32x2_t o = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
+        __builtin_nontemporal_store(o, reinterpret_cast<u32x2_t*>(static_cast<uint16_t*>(y) + r * ldy + n));
     }
 }
 
@@ -584,33 +589,74 @@ hipError_t launch_gemm(int form, int tile_id, const GemmArgs& args, hipStream_t 
     }
 }
 
+// f(first row, rows, threads, RowOf): launches over the rows of a block, at most 2^31 - 1 threads each
+template <class F>
+static hipError_t over_rows(int64_t rows, int64_t per_row, F&& f) {
+    if (rows <= 0 || per_row <= 0) return hipSuccess;
+    RowOf d{(uint32_t)per_row, 0, 0};
+    while (((int64_t)1 << d.shift) < per_row) ++d.shift;
+    d.magic = (uint32_t)((((uint64_t)1 << (31 + d.shift)) / (uint64_t)per_row) + 1);
+    if (per_row >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
+    const int64_t most = (((int64_t)1 << 31) - 1) / per_row;
+    for (int64_t r = 0; r < rows; r += most) {
+        const int64_t n = rows - r < most ? rows - r : most;
+        if (hipError_t e = f(r, n, (uint32_t)(n * per_row), d); e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+static dim3 covering(uint32_t threads) { return dim3((threads + 255u) / 256u); }
+
+template <int Z>
+static hipError_t reduce_planes(const ReduceArgs& a, hipStream_t s) {
+    return over_rows(a.M, a.N >> 2, [&](int64_t r, int64_t n, uint32_t total, RowOf d) {
+        ReduceArgs p = a;
+        p.M = (int32_t)n;
+        p.ws += r * a.N;
+        p.out = static_cast<char*>(a.out) + r * a.ldo * (a.out_f32 ? 4 : 2);
+        if (a.pre) p.pre = static_cast<char*>(a.pre) + r * a.ldp * 2;
+        if (a.dg) p.dg = static_cast<const char*>(a.dg) + r * a.lddg * 2;
+        return launch_kernel(tp_reduce_kernel<Z>, covering(total), dim3(256), 0, s, p, total, d);
+    });
+}
 hipError_t launch_reduce(const ReduceArgs& a, hipStream_t s) {
-    const int64_t total = (int64_t)a.M * (a.N >> 2);
-    int64_t blocks = (total + 255) / 256;
-    if (blocks > ((int64_t)1 << 30)) blocks = (int64_t)1 << 30;
-    if (blocks < 1) blocks = 1;
-    return launch_kernel(tp_reduce_kernel, dim3((unsigned)blocks), dim3(256), 0, s, a);
+    switch (a.split_k) {
+        case 2: return reduce_planes<2>(a, s);
+        case 3: return reduce_planes<3>(a, s);
+        case 4: return reduce_planes<4>(a, s);
+        case 5: return reduce_planes<5>(a, s);
+        case 6: return reduce_planes<6>(a, s);
+        case 7: return reduce_planes<7>(a, s);
+        case 8: return reduce_planes<8>(a, s);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 hipError_t launch_dgelu(const void* dy, int64_t ld_dy, const void* pre, int64_t ld_pre, void* da, int64_t ld_da,
                         int64_t rows, int64_t cols, hipStream_t s) {
-    const int64_t total = rows * (cols >> 3);
-    if (total == 0) return hipSuccess;
-    int64_t blocks = (total + 255) / 256;
-    if (blocks > ((int64_t)1 << 30)) blocks = (int64_t)1 << 30;
-    return launch_kernel(tp_dgelu_kernel, dim3((unsigned)blocks), dim3(256), 0, s, static_cast<const uint16_t*>(dy), ld_dy,
-                         static_cast<const uint16_t*>(pre), ld_pre, static_cast<uint16_t*>(da), ld_da, rows,
-                         (int)(cols >> 3));
+    return over_rows(rows, cols >> 3, [&](int64_t r, int64_t, uint32_t total, RowOf d) {
+        return launch_kernel(tp_dgelu_kernel, covering(total), dim3(256), 0, s, static_cast<const uint16_t*>(dy) + r * ld_dy, ld_dy,
+                             static_cast<const uint16_t*>(pre) + r * ld_pre, ld_pre, static_cast<uint16_t*>(da) + r * ld_da, ld_da, total, d);
+    });
 }
 
+template <bool GELU, bool PRE, bool F32>
+static hipError_t bias_act(const float* c, int64_t ldc, const void* bias, void* y, int64_t ldy, void* pre, int64_t ldp, int64_t rows,
+                           int64_t cols, hipStream_t s) {
+    return over_rows(rows, cols >> 2, [&](int64_t r, int64_t, uint32_t total, RowOf d) {
+        return launch_kernel(tp_bias_act_kernel<GELU, PRE, F32>, covering(total), dim3(256), 0, s, c + r * ldc, ldc, static_cast<const uint16_t*>(bias),
+                             static_cast<void*>(static_cast<char*>(y) + r * ldy * (F32 ? 4 : 2)), ldy,
+                             PRE ? static_cast<uint16_t*>(pre) + r * ldp : nullptr, ldp, total, d);
+    });
+}
 hipError_t launch_bias_act(const float* c, int64_t ldc, const void* bias, int gelu, void* y, int64_t ldy, int y_f32,
                            void* pre, int64_t ldp, int64_t rows, int64_t cols, hipStream_t s) {
-    const int64_t total = rows * (cols >> 2);
-    if (total == 0) return hipSuccess;
-    int64_t blocks = (total + 255) / 256;
-    if (blocks > ((int64_t)1 << 30)) blocks = (int64_t)1 << 30;
-    return launch_kernel(tp_bias_act_kernel, dim3((unsigned)blocks), dim3(256), 0, s, c, ldc, static_cast<const uint16_t*>(bias),
-                         gelu, y, ldy, y_f32, static_cast<uint16_t*>(pre), ldp, rows, (int)(cols >> 2));
+    auto pick = [&](auto g, auto p) {
+        return y_f32 ? bias_act<decltype(g)::value, decltype(p)::value, true>(c, ldc, bias, y, ldy, pre, ldp, rows, cols, s)
+                     : bias_act<decltype(g)::value, decltype(p)::value, false>(c, ldc, bias, y, ldy, pre, ldp, rows, cols, s);
+    };
+    using Y = std::true_type;
+    using N = std::false_type;
+    return gelu ? (pre ? pick(Y{}, Y{}) : pick(Y{}, N{})) : (pre ? pick(N{}, Y{}) : pick(N{}, N{}));
 }
 
 // Row splits that the workspace of a column sum is sized for: columns counted in strips of 64, workgroups enough to fill the

@@ -865,3 +865,27 @@ def test_either_operand_of_the_stream_kernel_forward_late(m, n, k):
         with overrides(tile=1, split=split if 2 * ((k + 63) // 64) >= split else 2):
             run_share(T.Grid(T.MODE_2D, q=2, ri=0, rj=1), (2 * m, 2 * k, 2 * n), backward=False, y_dtype="f32" if split == 1 else "bf16",
                       label=f"{m} x {k} x {n} split {split}")
+
+
+@pytest.mark.parametrize("rows,cols", [(1, 8), (3, 8), (257, 16), (5, 24), (33, 264), (129, 2056), (64, 4096), (7, 32776)])
+def test_elementwise_blocks_of_every_width(rows, cols):
+    """The elementwise kernels find a thread's row with a multiplication: one piece a row, powers of two, odd widths, long rows."""
+    g, a = (dev(S.normal_block_bf16(S.BASE_SEED + i, S.T_G, cols + 8, 0, rows, 0, cols + 8, 2.0))[:, :cols] for i in (1, 2))
+    bias = dev(S.normal_block_bf16(S.BASE_SEED, S.T_B1, cols, 0, 1, 0, cols, 0.5)[0])
+    da = torch.full((rows, cols + 16), 7.0, dtype=torch.bfloat16, device="cuda")
+    T.tp_dgelu(g, a, da[:, :cols])
+    check(host64(da[:, :cols]), O.share_da(host64(g), host64(a)), "bf16", f"dA {rows} x {cols}")
+    assert bool((da[:, cols:] == 7.0).all())
+    c = a.float().contiguous()
+    y, pre = torch.empty_like(c), torch.empty((rows, cols), dtype=torch.bfloat16, device="cuda")
+    T.tp_bias_act(c, bias, T.EPI_BIAS_GELU, y, pre)
+    A, Y = O.bias_gelu(host64(c), host64(bias), True)
+    check(host64(y), Y, "f32", f"bias + GeLU {rows} x {cols}")
+    check(host64(pre), A, "bf16", f"bias {rows} x {cols}")
+
+
+@pytest.mark.parametrize("split", [2, 4, 5, 6, 7, 8])
+def test_fix_up_of_every_number_of_planes(split):
+    grid, dims = T.Grid(T.MODE_2D, q=2, ri=1, rj=0), (2 * 131, 2 * 264, 2 * 264)
+    with overrides(tile=4, split=split):
+        run_share(grid, dims, y_dtype="bf16", dx_dtype="f32", use_own_slot=False, label=f"split {split}")
