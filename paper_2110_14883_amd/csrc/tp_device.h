@@ -57,31 +57,31 @@ __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {   // a -> low 
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2_t));
 }
 
-// Standard normal cdf and pdf in fp32.  erfc(x) for x >= 0 is taken from the five-term
-// rational form of Abramowitz & Stegun 7.1.26 (|error| <= 1.5e-7 on erf), which is an erfc
-// formula to begin with, so the negative tail of Phi keeps its relative accuracy.
-__device__ __forceinline__ void normal_cdf_pdf(float a, float& cdf, float& pdf) {
-    const float x = fabsf(a) * 0.70710678118654752f;
-    const float t = __builtin_amdgcn_rcpf(fmaf(0.3275911f, x, 1.0f));
-    float p = fmaf(t, 1.061405429f, -1.453152027f);
-    p = fmaf(t, p, 1.421413741f);
-    p = fmaf(t, p, -0.284496736f);
-    p = fmaf(t, p, 0.254829592f);
-    p *= t;
-    const float e = __builtin_amdgcn_exp2f(a * a * -0.72134752044448170f);   // exp(-a^2/2)
-    const float tail = 0.5f * p * e;                                           // Phi(-|a|)
-    cdf = a < 0.0f ? tail : 1.0f - tail;
-    pdf = e * 0.39894228040143268f;
+// erf-GeLU and its derivative in fp32.  Phi(-|a|) = q e with q = t poly(t) / 2, t = 1 / (1 + 0.3275911 |a| / sqrt 2),
+// e = exp(-a^2 / 2): the five-term rational form of Abramowitz & Stegun 7.1.26 (|error| <= 1.5e-7 on erf), which is an erfc
+// formula to begin with, so the negative tail keeps its relative accuracy.  The epilogues that apply them are bound by vector
+// instructions (a 256 x 256 tile: 65536 values at 16 a SIMD and clock), so constants are folded and the sign is needed once.
+__device__ __forceinline__ float half_erfc_poly(float t) {           // q / t
+    float q = fmaf(t, 0.5f * 1.061405429f, 0.5f * -1.453152027f);
+    q = fmaf(t, q, 0.5f * 1.421413741f);
+    q = fmaf(t, q, 0.5f * -0.284496736f);
+    return fmaf(t, q, 0.5f * 0.254829592f);
 }
+__device__ __forceinline__ float erfc_t(float x) { return __builtin_amdgcn_rcpf(fmaf(0.3275911f * 0.70710678118654752f, x, 1.0f)); }
+__device__ __forceinline__ float exp_half_square(float a) { return __builtin_amdgcn_exp2f(a * a * -0.72134752044448170f); }   // exp(-a^2/2)
+// max(a, 0) - |a| Phi(-|a|).  (|a| is held below infinity, so that +inf gives +inf and not inf - inf x 0; a NaN stays one.
+// The maximum is written out: fmaxf() takes a second instruction to quieten a NaN that the fma carries on anyway.)
 __device__ __forceinline__ float gelu_f(float a) {
-    float c, d;
-    normal_cdf_pdf(a, c, d);
-    return a * c;
+    const float x = __builtin_amdgcn_fmed3f(fabsf(a), 0.0f, 1e30f), t = erfc_t(x);
+    float relu;
+    asm("v_max_f32 %0, 0, %1" : "=v"(relu) : "v"(a));
+    return fmaf(-x, half_erfc_poly(t) * t * exp_half_square(a), relu);
 }
-__device__ __forceinline__ float dgelu_f(float a) {
-    float c, d;
-    normal_cdf_pdf(a, c, d);
-    return fmaf(a, d, c);
+// g GeLU'(a).  GeLU'(a) = Phi(a) + a phi(a) = 1 + h for a >= 0 and -h for a < 0 with h = |a| phi(a) - Phi(-|a|)
+__device__ __forceinline__ float dgelu_times(float g, float a) {
+    const float x = fabsf(a), t = erfc_t(x);
+    const float h = exp_half_square(a) * fmaf(x, 0.39894228040143268f, -(half_erfc_poly(t) * t));
+    return g * (a < 0.0f ? -h : 1.0f + h);
 }
 
 struct Epilogue {
@@ -107,8 +107,8 @@ __device__ __forceinline__ void epilogue4(const Epilogue& e, float (&v)[4], int 
     }
     if (e.dg) {
         const u32x2_t g = *reinterpret_cast<const u32x2_t*>(static_cast<const uint16_t*>(e.dg) + (int64_t)m * e.lddg + n);
-        v[0] *= dgelu_f(bf16_lo(g[0])); v[1] *= dgelu_f(bf16_hi(g[0]));
-        v[2] *= dgelu_f(bf16_lo(g[1])); v[3] *= dgelu_f(bf16_hi(g[1]));
+        v[0] = dgelu_times(v[0], bf16_lo(g[0])); v[1] = dgelu_times(v[1], bf16_hi(g[0]));
+        v[2] = dgelu_times(v[2], bf16_lo(g[1])); v[3] = dgelu_times(v[3], bf16_hi(g[1]));
     }
     if (e.out_f32) {
         f32x4_t s = {v[0], v[1], v[2], v[3]};

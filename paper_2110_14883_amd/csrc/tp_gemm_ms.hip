@@ -186,6 +186,11 @@ void tp_gemm_ms_kernel(const GemmArgs p) {
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
 
+    // (the bias is on its way while the K loop runs and is added once, before the epilogue)
+    constexpr bool USE_BIAS = EPI == EPI_BIAS || EPI == EPI_BIAS_GELU;
+    BiasBlock<TN> bias;
+    if constexpr (USE_BIAS) load_bias(bias, p, n0 + wn * WN);
+
     // ------------------------------------------------------------------ prologue: tiles 0 .. NS - 2, and A of tile NS - 1
     open_operand(std::true_type{});
     open_operand(std::false_type{});
@@ -241,6 +246,16 @@ void tp_gemm_ms_kernel(const GemmArgs p) {
     // every load has landed and every fragment is in registers before the patch reuses the ring
     wait_vm<0>();
     barrier();
+    if constexpr (USE_BIAS) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const float b = bias_of(bias, j, e);
+#pragma unroll
+                for (int i = 0; i < TM; ++i) acc[i][j][e] += b;
+            }
+    }
     store_c_block<TM, TN, EPI, F32_OUT, false>(p, acc, m0 + wm * WM, n0 + wn * WN, z, g, lds + w * 8192);
 }
 

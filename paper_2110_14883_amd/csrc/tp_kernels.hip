@@ -235,8 +235,8 @@ __device__ __forceinline__ void gemm_role(const GemmArgs& p, char* lds, const in
                     const int m = m_sub + 32 * i + r, n = n_sub + 32 * j + 8 * g + 4 * ch;
                     if (m < p.M && n < p.N) {
                         const u32x2_t a = *reinterpret_cast<const u32x2_t*>(static_cast<const uint16_t*>(p.dg) + (int64_t)m * p.lddg + n);
-                        v[0] *= dgelu_f(bf16_lo(a[0])); v[1] *= dgelu_f(bf16_hi(a[0]));
-                        v[2] *= dgelu_f(bf16_lo(a[1])); v[3] *= dgelu_f(bf16_hi(a[1]));
+                        v[0] = dgelu_times(v[0], bf16_lo(a[0])); v[1] = dgelu_times(v[1], bf16_hi(a[0]));
+                        v[2] = dgelu_times(v[2], bf16_lo(a[1])); v[3] = dgelu_times(v[3], bf16_hi(a[1]));
                     }
                 }
             };
@@ -349,21 +349,8 @@ __global__ __launch_bounds__(256) void tp_reduce_kernel(const ReduceArgs p, cons
 }
 
 // ---------------------------------------------------------------------------------------------
-// da = bf16(dy * GeLU'(pre)).  8 elements per 128-bit access.  GeLU'(a) = 1 + h for a >= 0 and -h for a < 0 with
-// h = |a| phi(a) - Phi(-|a|), which needs the sign only once, at the end.
+// da = bf16(dy * GeLU'(pre)).  8 elements per 128-bit access.
 // ---------------------------------------------------------------------------------------------
-__device__ __forceinline__ float dgelu_times(float g, float a) {
-    const float x = fabsf(a) * 0.70710678118654752f;
-    const float t = __builtin_amdgcn_rcpf(fmaf(0.3275911f, x, 1.0f));
-    float q = fmaf(t, 0.5f * 1.061405429f, 0.5f * -1.453152027f);      // half the erfc polynomial: Phi(-|a|) = q e
-    q = fmaf(t, q, 0.5f * 1.421413741f);
-    q = fmaf(t, q, 0.5f * -0.284496736f);
-    q = fmaf(t, q, 0.5f * 0.254829592f);
-    q *= t;
-    const float e = __builtin_amdgcn_exp2f(a * a * -0.72134752044448170f);   // exp(-a^2/2)
-    const float h = e * fmaf(x, 0.56418958354775629f, -q);                    // |a| phi(a) = x e / sqrt(pi)
-    return g * (a < 0.0f ? -h : 1.0f + h);
-}
 __device__ __forceinline__ u32x4_t dgelu8(const u32x4_t g, const u32x4_t a) {
     u32x4_t o;
 #pragma unroll

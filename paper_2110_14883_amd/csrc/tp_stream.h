@@ -49,7 +49,29 @@ template <int N> __device__ __forceinline__ void wait_vm() {      // at most N v
     __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
 }
 
-// Epilogue of one wave's block of C: 32 TM rows x 32 TN columns from (m_sub, n_sub).
+// The bias of a wave's 32 TN columns from n_sub, as the accumulators need it: word pair (j, g) is columns 32 j + 8 g + 4 (lane/32) .. + 3.
+// Columns past N read as zero.
+template <int TN> struct BiasBlock { u32x2_t v[TN][4]; };
+template <int TN>
+__device__ __forceinline__ void load_bias(BiasBlock<TN>& b, const GemmArgs& p, const int n_sub) {
+    const __amdgpu_buffer_rsrc_t rs = make_rsrc(uni_ptr(p.bias), (int64_t)p.N * 2);
+    const int at = n_sub + 4 * ((threadIdx.x & 63) >> 5);
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const u32x2_t w = __builtin_amdgcn_raw_buffer_load_b64(rs, (at + 32 * j + 8 * g) * 2, 0, 0);
+            b.v[j][g] = w;
+        }
+}
+// its value for accumulator element e of column block j
+template <int TN>
+__device__ __forceinline__ float bias_of(const BiasBlock<TN>& b, int j, int e) {
+    const uint32_t w = b.v[j][e >> 2][(e >> 1) & 1];
+    return e & 1 ? bf16_hi(w) : bf16_lo(w);
+}
+
+// Epilogue of one wave's block of C: 32 TM rows x 32 TN columns from (m_sub, n_sub).  The bias is in the accumulators already.
 // acc[i][j][e]: row m = 32 i + lane%32, columns n = 32 j + 8 (e/4) + 4 (lane/32) + e%4.
 // No branch depends on a lane: every global access goes through a buffer descriptor that starts at
 // the first row of the block and ends with the last row of the matrix, so rows below a ragged edge are
@@ -66,7 +88,6 @@ __device__ __forceinline__ void store_c_block(const GemmArgs& p, f32x16_t (&acc)
                                               const int z, const int g_out, char* const eps) {
     const int l = threadIdx.x & 63, r = l & 31, ch = l >> 5;
     const bool partial = p.split_k > 1;          // split K: raw fp32 partials, the fix-up kernel runs the epilogue
-    constexpr bool use_bias = EPI == EPI_BIAS || EPI == EPI_BIAS_GELU;
     constexpr bool use_gelu = EPI == EPI_BIAS_GELU;
     constexpr bool use_dg = EPI == EPI_MUL_DGELU;
     const bool use_pre = !use_dg && p.pre != nullptr;
@@ -76,17 +97,6 @@ __device__ __forceinline__ void store_c_block(const GemmArgs& p, f32x16_t (&acc)
         const int64_t nrec = rows_left > 0 ? ((int64_t)(rows_left - 1) * ld + p.N) * es : 0;
         return make_rsrc(uni_ptr(static_cast<const char*>(base) + (int64_t)m_sub * ld * es), nrec);
     };
-    u32x2_t bias_v[TN][4];
-    if constexpr (use_bias) {
-        const __amdgpu_buffer_rsrc_t rs_bias = make_rsrc(uni_ptr(p.bias), (int64_t)p.N * 2);
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const u32x2_t b = __builtin_amdgcn_raw_buffer_load_b64(rs_bias, (n_sub + 32 * j + 8 * g + 4 * ch) * 2, 0, 0);
-                bias_v[j][g] = b;
-            }
-    }
     __amdgpu_buffer_rsrc_t rs_dg;
     uint32_t dg_lane = 0;
     if constexpr (use_dg) {
@@ -103,14 +113,7 @@ __device__ __forceinline__ void store_c_block(const GemmArgs& p, f32x16_t (&acc)
             else                    v[e] = acc[i][j][4 * g + e];
         }
     };
-    auto preact4 = [&](int i, int j, int g, float (&v)[4]) __attribute__((always_inline)) {
-        raw4(i, j, g, v);
-        if constexpr (use_bias) {
-            const u32x2_t b = bias_v[j][g];
-            v[0] += bf16_lo(b[0]); v[1] += bf16_hi(b[0]); v[2] += bf16_lo(b[1]); v[3] += bf16_hi(b[1]);
-        }
-    };
-    u32x2_t dg_v[TN][4];
+    u32x2_t dg_v[TN][4];                         // (asked for one slab ahead the pass is 2 % slower)
     auto load_dg = [&](int i) __attribute__((always_inline)) {
         if constexpr (use_dg) {
 #pragma unroll
@@ -121,15 +124,15 @@ __device__ __forceinline__ void store_c_block(const GemmArgs& p, f32x16_t (&acc)
         }
     };
     auto final4 = [&](int i, int j, int g, float (&v)[4]) __attribute__((always_inline)) {
-        preact4(i, j, g, v);
+        raw4(i, j, g, v);
         if constexpr (use_gelu) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) v[e] = gelu_f(v[e]);
         }
         if constexpr (use_dg) {
             const u32x2_t a = dg_v[j][g];
-            v[0] *= dgelu_f(bf16_lo(a[0])); v[1] *= dgelu_f(bf16_hi(a[0]));
-            v[2] *= dgelu_f(bf16_lo(a[1])); v[3] *= dgelu_f(bf16_hi(a[1]));
+            v[0] = dgelu_times(v[0], bf16_lo(a[0])); v[1] = dgelu_times(v[1], bf16_hi(a[0]));
+            v[2] = dgelu_times(v[2], bf16_lo(a[1])); v[3] = dgelu_times(v[3], bf16_hi(a[1]));
         }
     };
     // bf16 slab of 32 rows x 32 TN columns: rows of 64 TN bytes in the patch; a lane writes 8 bytes and
@@ -197,7 +200,7 @@ __device__ __forceinline__ void store_c_block(const GemmArgs& p, f32x16_t (&acc)
         for (int i = 0; i < TM; ++i) {
             load_dg(i);
             if constexpr (!use_dg) {
-                if (use_pre) slab_bf16(i, preact4, rs_pre, (int)p.ldp);
+                if (use_pre) slab_bf16(i, raw4, rs_pre, (int)p.ldp);
             }
             if constexpr (F32_OUT) slab_f32(i, final4, std::integral_constant<int, ST_STREAM>{}, rs_out, ldo);
             else                   slab_bf16(i, final4, rs_out, ldo);

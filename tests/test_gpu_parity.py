@@ -889,3 +889,14 @@ def test_fix_up_of_every_number_of_planes(split):
     grid, dims = T.Grid(T.MODE_2D, q=2, ri=1, rj=0), (2 * 131, 2 * 264, 2 * 264)
     with overrides(tile=4, split=split):
         run_share(grid, dims, y_dtype="bf16", dx_dtype="f32", use_own_slot=False, label=f"split {split}")
+
+
+def test_gelu_of_the_ends_of_the_range():
+    """Infinities, a NaN and values whose square overflows: +inf stays, -inf gives its limit 0, a NaN stays one."""
+    inf, nan = float("inf"), float("nan")
+    c = torch.tensor([[inf, -inf, nan, 3e38, -3e38, 1e20, -1e20, 0.0]], device="cuda")
+    y = torch.empty_like(c)
+    T.tp_bias_act(c, torch.zeros(8, dtype=torch.bfloat16, device="cuda"), T.EPI_BIAS_GELU, y)
+    got, big = y[0].tolist(), c[0].tolist()
+    assert got[0] == inf and got[2] != got[2] and [got[3], got[5]] == [big[3], big[5]]
+    assert got[1] == 0.0 and got[4] == 0.0 and got[6] == 0.0 and got[7] == 0.0
