@@ -38,9 +38,9 @@ NSETS = int(os.environ.get("TPL_BENCH_NSETS", "3"))   # buffer sets rotated thro
 # of the headline workload.  (Its dX is planned with K split in two: the launch is the fp32-partials
 # instantiation, followed by the fix-up kernel's 252 MB.)
 MEASURED_TRAFFIC_BYTES = {
-    "tpl::tp_gemm4_kernel<true, false, 2, false, false>": 2220000000,     # forward NN + bias + GeLU: 1817 MB read, 403 MB written
-    "tpl::tp_gemm4_kernel<false, false, 0, true, false>": 2959000000,     # dW TN: 2355 MB read, 604 MB written
-    "tpl::tp_gemm4_kernel<true, true, 0, true, false>": 2019000000,       # dX NT: 1818 MB read, 201 MB written
+    "tpl::tp_gemm4_kernel<true, false, 2, false>": 2220000000,     # forward NN + bias + GeLU: 1817 MB read, 403 MB written
+    "tpl::tp_gemm4_kernel<false, false, 0, true>": 2959000000,     # dW TN: 2355 MB read, 604 MB written
+    "tpl::tp_gemm4_kernel<true, true, 0, true>": 2019000000,       # dX NT: 1818 MB read, 201 MB written
 }
 
 
@@ -48,13 +48,11 @@ def log(*a):
     print(*a, file=sys.stderr, flush=True)
 
 
-def gemm_symbol(form: str, epi: int, f32_out: bool, m: int = 0, n: int = 0) -> str:
+def gemm_symbol(form: str, epi: int, f32_out: bool) -> str:
     """Name of the 256x256 GEMM instantiation a call launches when K is not split (as rocprofv3 prints it, without
-    'void' and the argument list).  form: NN / NT / TN; epi: 0 none, 1 bias, 2 bias+GeLU, 3 *GeLU'; m, n: the
-    output's extents (the forward has operand A late if C has at least as many tile rows as columns)."""
+    'void' and the argument list).  form: NN / NT / TN; epi: 0 none, 1 bias, 2 bias+GeLU, 3 *GeLU'."""
     kc = {"NN": "true, false", "NT": "true, true", "TN": "false, false"}[form]
-    late = form == "NN" and -(-m // 256) >= -(-n // 256)
-    return f"tpl::tp_gemm4_kernel<{kc}, {epi}, {'true' if f32_out else 'false'}, {'true' if late else 'false'}>"
+    return f"tpl::tp_gemm4_kernel<{kc}, {epi}, {'true' if f32_out else 'false'}>"
 
 
 # Calls of these workloads whose main kernel the kernel traces under profiles/ show to be another: K split into fp32
@@ -64,7 +62,7 @@ TRACED_KERNELS = {
     ("c3_2d_q4", "dX NT"): gemm_symbol("NT", 0, True),
     ("c5_3d_p2", "dX NT"): gemm_symbol("NT", 0, True),
     ("c5x_3d_p2_exact", "dX NT"): gemm_symbol("NT", 0, True),
-    ("n1_2d_q4_fc2", "fwd NN +bias"): gemm_symbol("NN", 0, True, 2048, 2048),
+    ("n1_2d_q4_fc2", "fwd NN +bias"): gemm_symbol("NN", 0, True),
 }
 
 
@@ -124,9 +122,9 @@ def main() -> int:
                      dW2=empty((fb, H), True), dX=empty((M, H), True), dW1=empty((H, fb), True),
                      ws1=ws_for(g1, d1), ws2=ws_for(g2, d2))
             calls = [
-                ("fc1_fwd NN +bias+GeLU", one, gemm_symbol("NN", 2, False, M, fb), lambda b=b, o=o: T.tp_linear_fwd(
+                ("fc1_fwd NN +bias+GeLU", one, gemm_symbol("NN", 2, False), lambda b=b, o=o: T.tp_linear_fwd(
                     g1, d1, 1, [b["X"]], [b["W1"]], b["b1"], T.EPI_BIAS_GELU, o["Z"], o["A"], o["ws1"])),
-                ("fc2_fwd NN fp32 partial", one, gemm_symbol("NN", 0, True, M, H), lambda b=b, o=o: T.tp_linear_fwd(
+                ("fc2_fwd NN fp32 partial", one, gemm_symbol("NN", 0, True), lambda b=b, o=o: T.tp_linear_fwd(
                     g2, d2, 1, [o["Z"]], [b["W2"]], None, T.EPI_NONE, o["Y"], None, o["ws2"])),
                 ("fc2_dX NT *GeLU'", one, gemm_symbol("NT", 3, False), lambda b=b, o=o: T.tp_linear_bwd(
                     g2, d2, 1, 0, da_row_blocks=[b["G"]], w_blocks_dx=[b["W2"]], dgelu_preact=o["A"], dx=o["dA"],
@@ -190,7 +188,7 @@ def main() -> int:
             b = {k_: cp(v) for k_, v in base.items()}
             o = dict(y=empty((m, n), f32y), pre=empty((m, n)), ws=ws_for(grid, dims))
             if second:
-                calls = [("fwd NN +bias", one, gemm_symbol("NN", 1, f32y, m, n), lambda b=b, o=o: T.tp_linear_fwd(
+                calls = [("fwd NN +bias", one, gemm_symbol("NN", 1, f32y), lambda b=b, o=o: T.tp_linear_fwd(
                     grid, dims, sf, b["x"], b["w"], b["bias"], T.EPI_BIAS, o["y"], None, o["ws"]))]
                 o.update(dx=empty((m, k)), dw=empty((k, n), True))
                 rows = [b["g"] if i == inp["own_slot_dx"] else b["g_row"][i] for i in range(sx)]
@@ -204,7 +202,7 @@ def main() -> int:
                 ]
                 sets.append(calls)
                 continue
-            calls = [("fwd NN +bias+GeLU", one, gemm_symbol("NN", 2, f32y, m, n), lambda b=b, o=o: T.tp_linear_fwd(
+            calls = [("fwd NN +bias+GeLU", one, gemm_symbol("NN", 2, f32y), lambda b=b, o=o: T.tp_linear_fwd(
                 grid, dims, sf, b["x"], b["w"], b["bias"], T.EPI_BIAS_GELU, o["y"], o["pre"], o["ws"]))]
             if cfg.backward:
                 o.update(da=empty((m, n)), dx=empty((m, k), cfg.dx_dtype == "f32"), dw=empty((k, n), True))
@@ -237,7 +235,7 @@ def main() -> int:
             o = dict(y=empty((m, n)), pre=empty((m, n)), da=empty((m, n)), ws=torch.empty(wsb, dtype=torch.uint8, device="cuda"),
                      dxp=[empty((m, k), True) for _ in range(q)], dwp=[empty((k, n), True) for _ in range(q)])
             sets.append([
-                ("fwd NN +bias+GeLU", one, gemm_symbol("NN", 2, False, m, n), lambda b=b, o=o: T.tp_linear_fwd(
+                ("fwd NN +bias+GeLU", one, gemm_symbol("NN", 2, False), lambda b=b, o=o: T.tp_linear_fwd(
                     grid, dims, sf, b["x"], b["w"], b["bias"], T.EPI_BIAS_GELU, o["y"], o["pre"], o["ws"])),
                 ("dA = dY*GeLU'(A)", 0.0, "tpl::tp_dgelu_kernel", lambda b=b, o=o: T.tp_dgelu(b["g"], o["pre"], o["da"]), 6.0 * m * n),
                 (f"dX partials NT x{q}", one, gemm_symbol("NT", 0, True), lambda b=b, o=o: T.tp_linear_bwd_partials(
@@ -260,7 +258,7 @@ def main() -> int:
             o = dict(c=empty((ms, fb), True), y=empty((mc, fb)), pre=empty((mc, fb)), dx=empty((ms, hb), True),
                      dw=empty((hb, fb), True), ws=ws_for(grid, dims))
             sets.append([
-                ("fwd NN fp32 partial", one, gemm_symbol("NN", 0, True, ms, fb), lambda b=b, o=o: T.tp_linear_fwd(
+                ("fwd NN fp32 partial", one, gemm_symbol("NN", 0, True), lambda b=b, o=o: T.tp_linear_fwd(
                     grid, dims, 1, [b["x"]], [b["w"]], None, T.EPI_NONE, o["c"], None, o["ws"])),
                 ("bias+GeLU on the rank's chunk", 0.0, "tpl::tp_bias_act_kernel", lambda b=b, o=o: T.tp_bias_act(
                     o["c"][l * mc:(l + 1) * mc], b["bias"], T.EPI_BIAS_GELU, o["y"], o["pre"]), 8.0 * mc * fb),

@@ -5,9 +5,10 @@
 //   * four wave64 per workgroup, one per SIMD, each owning a 128 x 128 block of the C tile: 16 MFMA
 //     32x32x16 accumulators = 256 registers in the accumulator half of the register file, and only
 //     32 LDS fragment reads per 64 MFMAs (the eight-wave kernel reads 48);
-//   * the K tiles of ALL the C tiles a persistent workgroup owns form one stream: K tile u is being
-//     multiplied out of one LDS stage while tile u+1 travels into the other one, across C-tile
-//     boundaries too, so the epilogue of a C tile runs with the next one's first K tile in LDS;
+//   * the K tiles of ALL the C tiles a persistent workgroup owns form one stream: while K tile u is being
+//     multiplied, tiles u+1 and u+2 travel into the other LDS stages (three of operand A, two of B: all of the
+//     CU's LDS), across C-tile boundaries too, so the epilogue of a C tile runs with the next one's first K tiles in LDS or on
+//     their way; its patch is the one stage that is free just then;
 //   * both operands of every memory form go from memory straight into LDS.  An operand whose contraction
 //     index is not contiguous is transposed on the way OUT, by ds_read_b64_tr_b16.  (It used to be
 //     transposed in registers on the way in, 8 loads, 32 byte permutes and 8 LDS writes per wave and K
@@ -28,16 +29,14 @@ namespace {
 
 constexpr int W4_THREADS = 256;
 constexpr int W4_BM = 256, W4_BN = 256;
-constexpr int W4_STAGE_STRIDE = W4_BM * BK * 2;              // 32 KB: one stage of one operand
-constexpr int W4_B_BASE = 2 * W4_STAGE_STRIDE;               // LDS: A stage 0 | A stage 1 | B stage 0 | B stage 1 | epilogue
-constexpr int W4_EPI_BASE = 4 * W4_STAGE_STRIDE;
-constexpr int W4_EPI_BYTES_PER_WAVE = 8192;                  // 32 rows x 256 bytes
-constexpr int W4_LDS_BYTES = W4_EPI_BASE + 4 * W4_EPI_BYTES_PER_WAVE;
+constexpr int W4_STAGE = W4_BM * BK * 2;                     // 32 KB: one stage of one operand
+constexpr int W4_A_BASE = 2 * W4_STAGE;                      // LDS: two stages of operand B | three of operand A
+constexpr int W4_LDS_BYTES = 5 * W4_STAGE;                   // all 160 KB
+constexpr int W4_EPI_BYTES_PER_WAVE = 8192;                  // 32 rows x 256 bytes, in the stage that is free between two C tiles
 
 }  // namespace
 
-// A_LATE: see k_tile
-template <bool A_KC, bool B_KC, int EPI, bool F32_OUT, bool A_LATE>
+template <bool A_KC, bool B_KC, int EPI, bool F32_OUT>
 __global__ __launch_bounds__(W4_THREADS) __attribute__((amdgpu_waves_per_eu(1, 1)))
 void tp_gemm4_kernel(const GemmArgs p) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
@@ -46,7 +45,6 @@ void tp_gemm4_kernel(const GemmArgs p) {
     const int l = t & 63;
     const int w = __builtin_amdgcn_readfirstlane(t >> 6);
     const int wm = w & 1, wn = w >> 1;
-    char* const eps = lds + W4_EPI_BASE + w * W4_EPI_BYTES_PER_WAVE;
 
     const int KT = (p.K + BK - 1) / BK;
     const int T = p.n_steps * KT;
@@ -55,10 +53,8 @@ void tp_gemm4_kernel(const GemmArgs p) {
     const int grid = (int)gridDim.x;
 
     // ------------------------------------------------------------------ LDS addresses (bytes), per lane
-    // LDS map: A stage 0 | A stage 1 | B stage 0 | B stage 1 (32 KB each) | epilogue patches.  The two
-    // stages of an operand are 32 KB apart, which fits the 16-bit immediate offset of the LDS
-    // instructions: the K tiles of a C tile alternate between two compiled bodies that differ only in
-    // those immediates, and no address is recomputed inside the loop.
+    // LDS map: two stages of operand B, three of A, 32 KB each.  A K tile's addresses are those of the last one plus the
+    // distance to the next stage: four registers an operand.
     // Fragment of 32 rows (columns of C) x 16 k for MFMA step ks, block i.
     // Contraction-contiguous operand (rows of 128 B, chunks swizzled as in lds_off()): lane reads row
     // lr + 32 i of the wave's 128-row slab, chunk 2 ks + lane/32, with one ds_read_b128.  The chunk
@@ -78,22 +74,20 @@ void tp_gemm4_kernel(const GemmArgs p) {
         const int r = (l & 15) >> 2, low = 2 * ((l >> 4) & 1) + ((l >> 1) & 1);
 #pragma unroll
         for (int vi = 0; vi < 4; ++vi) {
-            ra_addr[vi] = A_KC ? (uint32_t)((wm * 128 + lr) * 128 + ((L ^ (2 * vi)) << 4))
-                               : (uint32_t)((ch * 8 + r) * 512 + (wm * 16 + 4 * (vi ^ r) + low) * 16 + (l & 1) * 8);
-            rb_addr[vi] = W4_B_BASE + (B_KC ? (uint32_t)((wn * 128 + lr) * 128 + ((L ^ (2 * vi)) << 4))
-                                            : (uint32_t)((ch * 8 + r) * 512 + (wn * 16 + 4 * (vi ^ r) + low) * 16 + (l & 1) * 8));
+            ra_addr[vi] = W4_A_BASE + (A_KC ? (uint32_t)((wm * 128 + lr) * 128 + ((L ^ (2 * vi)) << 4))
+                                                         : (uint32_t)((ch * 8 + r) * 512 + (wm * 16 + 4 * (vi ^ r) + low) * 16 + (l & 1) * 8));
+            rb_addr[vi] = (B_KC ? (uint32_t)((wn * 128 + lr) * 128 + ((L ^ (2 * vi)) << 4))
+                                               : (uint32_t)((ch * 8 + r) * 512 + (wn * 16 + 4 * (vi ^ r) + low) * 16 + (l & 1) * 8));
             // (opaque, so that the constant part of every address goes into the instruction's offset field)
             asm volatile("" : "+v"(ra_addr[vi]), "+v"(rb_addr[vi]));
         }
     }
     // ------------------------------------------------------------------ cursors over the K-tile stream
-    // left: K tiles of the cursor's C tile still to come (the current one included); odd: that C tile has
-    // an odd number of K tiles, so one all-zero tile follows its last one (the loop body handles K tiles
-    // in pairs); live: 0 = the cursor stands on such a zero tile, or past the end of the stream
-    struct Cursor { int v, m0, n0, z, rot, g, step, kt, left, odd, live; };
+    // left: K tiles of the cursor's C tile still to come (the current one included); 0 = past the end of the stream
+    struct Cursor { int v, m0, n0, z, rot, g, step, kt, left; };
     auto start = [&](Cursor& c, int v) __attribute__((always_inline)) {
         c.v = v;
-        c.left = 0; c.odd = 0; c.live = 0;
+        c.left = 0;
         if (v >= total) return;
         int tm, tn, z;
         tile_of_id(p, v, tm, tn, z);
@@ -108,9 +102,8 @@ void tp_gemm4_kernel(const GemmArgs p) {
         c.kt = uni(z - s * KT);
         c.step = uni(s + g);                      // a grouped launch has one step per group: operand slot = group
         c.left = uni((T - z + Z - 1) / Z);        // K tiles z, z + Z, ... of the n_steps x KT sequence
-        c.odd = c.left & 1; c.live = 1;
     };
-    Cursor f, c;                                  // fetch cursor (one K tile ahead, two from the middle of a K tile on) and compute cursor
+    Cursor f, c;                                  // fetch cursor (two K tiles ahead) and compute cursor
 
     // ------------------------------------------------------------------ loads
     // Per (C tile, step) an operand has one buffer descriptor that starts at the tile's first row (or
@@ -131,7 +124,7 @@ void tp_gemm4_kernel(const GemmArgs p) {
     auto open_operand = [&](auto is_a) __attribute__((always_inline)) {
         constexpr bool IS_A = decltype(is_a)::value;
         constexpr bool KC = IS_A ? A_KC : B_KC;
-        const bool ok = f.live != 0;
+        const bool ok = f.left != 0;
         const int s = f.step < TP_MAX_STEPS ? f.step : TP_MAX_STEPS - 1;
         const uint16_t* ptr = uni_ptr(IS_A ? p.a[s] : p.b[s]);
         const int ld = uni(IS_A ? p.lda[s] : p.ldb[s]);
@@ -151,79 +144,84 @@ void tp_gemm4_kernel(const GemmArgs p) {
             if constexpr (IS_A) dl_a[h] = off; else dl_b[h] = off;
         }
     };
-    // lane offsets of the fetch cursor's K tile.  (k beyond K: a contraction-contiguous chunk is masked
+    // lane offsets of the fetch cursor's K tile, in three parts.  (k beyond K: a contraction-contiguous chunk is masked
     // here; a row of the other kind lies past the end of its descriptor.)
-    auto prep_tile = [&]() __attribute__((always_inline)) {
+    int t_k0 = 0;
+    auto prep_k0 = [&]() __attribute__((always_inline)) {
         int kt = f.kt + f.rot;
         if (kt >= KT) kt -= KT;
-        const int k0 = kt * BK;
+        t_k0 = kt * BK;
+    };
+    auto prep_operand = [&](auto is_a) __attribute__((always_inline)) {
+        constexpr bool IS_A = decltype(is_a)::value;
+        constexpr bool KC = IS_A ? A_KC : B_KC;
+        const uint32_t at = (uint32_t)(t_k0 * (IS_A ? a_kmul : b_kmul));
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            const bool kok = (k0 + (d_c0 ^ (2 * h)) * 8) < p.K;
-            dv_a[h] = !A_KC || kok ? dl_a[h] + (uint32_t)(k0 * a_kmul) : OOB_OFFSET;
-            dv_b[h] = !B_KC || kok ? dl_b[h] + (uint32_t)(k0 * b_kmul) : OOB_OFFSET;
+            const bool kok = !KC || (t_k0 + (d_c0 ^ (2 * h)) * 8) < p.K;
+            if constexpr (IS_A) dv_a[h] = kok ? dl_a[h] + at : OOB_OFFSET;
+            else                dv_b[h] = kok ? dl_b[h] + at : OOB_OFFSET;
         }
+    };
+    auto prep_tile = [&]() __attribute__((always_inline)) {
+        prep_k0();
+        prep_operand(std::true_type{});
+        prep_operand(std::false_type{});
     };
     // Move the fetch cursor to the next K tile of the stream.  The common case (same C tile, same step)
     // is a few scalar instructions issued between two MFMAs; a change of step or of C tile needs other
-    // blocks and other descriptors and is left to advance_slow() at the end of the K tile.
-    bool f_reopen = false;
-    auto advance_fast = [&]() __attribute__((always_inline)) {
-        const int live = f.left != 0;             // past the end nothing moves: every further tile reads as zero
-        f.left -= live;
-        f.kt += live ? Z : 0;
-        f_reopen = live && (f.left == 0 || f.kt >= KT);
+    // blocks and other descriptors (advance_slow()).
+    int f_live = 0, f_reopen = 0;
+    auto advance_count = [&]() __attribute__((always_inline)) {
+        f_live = f.left != 0 ? 1 : 0;             // past the end nothing moves: every further tile reads as zero
+        f.left -= f_live;
     };
+    auto advance_k = [&]() __attribute__((always_inline)) { f.kt += f_live ? Z : 0; };
+    auto advance_check = [&]() __attribute__((always_inline)) { f_reopen = f_live != 0 && (f.left == 0 || f.kt >= KT); };
     auto advance_slow = [&]() __attribute__((always_inline)) {
-        {
-            if (f.left != 0) {                    // next step of this C tile
-                do { f.kt -= KT; ++f.step; } while (f.kt >= KT);
-            } else if (f.odd) {                   // the zero tile that makes the count even
-                f.odd = 0; f.live = 0; f.left = 1;
-            } else {
-                start(f, f.v + grid);             // next C tile (or the end)
-            }
-            open_operand(std::true_type{});
-            open_operand(std::false_type{});
+        if (f.left != 0) {                        // next step of this C tile
+            do { f.kt -= KT; ++f.step; } while (f.kt >= KT);
+        } else {
+            start(f, f.v + grid);                 // next C tile (or the end)
         }
+        open_operand(std::true_type{});
+        open_operand(std::false_type{});
     };
-    // n-th direct-to-LDS load of an operand into stage S
-    auto dtl1 = [&](auto is_a, auto n_, auto S_) __attribute__((always_inline)) {
+    // n-th direct-to-LDS load of an operand, into the stage that starts at byte `stage` of the LDS (plus this wave's share)
+    auto dtl1 = [&](auto is_a, auto n_, uint32_t stage) __attribute__((always_inline)) {
         constexpr bool IS_A = decltype(is_a)::value;
         constexpr int n = decltype(n_)::value;
-        constexpr uint32_t dst = (IS_A ? 0u : (uint32_t)W4_B_BASE) + decltype(S_)::value * W4_STAGE_STRIDE + n * 4096;
-        if constexpr (IS_A) dtl_load16(rw_a, dv_a[n & 1] + (uint32_t)(n * a_step), s_wbase + dst);
-        else                dtl_load16(rw_b, dv_b[n & 1] + (uint32_t)(n * b_step), s_wbase + dst);
+        if constexpr (IS_A) dtl_load16_at<n * 4096>(rw_a, dv_a[n & 1] + (uint32_t)(n * a_step), stage);
+        else                dtl_load16_at<n * 4096>(rw_b, dv_b[n & 1] + (uint32_t)(n * b_step), stage);
     };
 
     // ------------------------------------------------------------------ fragments and accumulators
     bf16x8_t fa[2][TM], fb[2][TN];
     f32x16_t acc[TM][TN];
-    // read n (0 .. NR - 1) of MFMA step ks from stage S, in the order the step's MFMAs need the fragments:
+    // read n (0 .. NR - 1) of MFMA step ks, in the order the step's MFMAs need the fragments:
     // B0, A0, B1, B2, B3, A1, A2, A3 (a transposed fragment takes two reads)
     constexpr int RA = A_KC ? 1 : 2, RB = B_KC ? 1 : 2, NR = 4 * (RA + RB);
-    auto read_frag = [&](auto is_a, auto ks_, auto i_, auto h_, auto S_) __attribute__((always_inline)) {
+    auto read_frag = [&](auto is_a, auto ks_, auto i_, auto h_) __attribute__((always_inline)) {
         constexpr bool IS_A = decltype(is_a)::value;
         constexpr int ks = decltype(ks_)::value & 3, i = decltype(i_)::value, h = decltype(h_)::value;
-        constexpr int so = decltype(S_)::value * W4_STAGE_STRIDE;
         bf16x8_t& f = IS_A ? fa[ks & 1][i] : fb[ks & 1][i];
         if constexpr (IS_A ? A_KC : B_KC) {
-            f = lds_load_frag((IS_A ? ra_addr : rb_addr)[ks ^ (i & 1)] + (so + i * 4096));
+            f = lds_load_frag((IS_A ? ra_addr : rb_addr)[ks ^ (i & 1)] + i * 4096);
         } else {
-            const bf16x4_t v = lds_load_tr((IS_A ? ra_addr : rb_addr)[i] + (so + ks * 8192 + h * 2048));
+            const bf16x4_t v = lds_load_tr((IS_A ? ra_addr : rb_addr)[i] + (ks * 8192 + h * 2048));
             if constexpr (h == 0) f = __builtin_shufflevector(v, v, 0, 1, 2, 3, 0, 1, 2, 3);
             else                  f = __builtin_shufflevector(f, __builtin_shufflevector(v, v, 0, 1, 2, 3, 0, 1, 2, 3), 0, 1, 2, 3, 8, 9, 10, 11);
         }
     };
-    auto read_n = [&](auto n_, auto ks_, auto S_) __attribute__((always_inline)) {
+    auto read_n = [&](auto n_, auto ks_) __attribute__((always_inline)) {
         constexpr int n = decltype(n_)::value;
         constexpr int e1 = RB, e2 = RB + RA, e3 = RA + 4 * RB;         // ends of B0, A0, B1 .. B3
         using AT = std::true_type;
         using BT = std::false_type;
-        if constexpr (n < e1)      read_frag(BT{}, ks_, std::integral_constant<int, 0>{}, std::integral_constant<int, n>{}, S_);
-        else if constexpr (n < e2) read_frag(AT{}, ks_, std::integral_constant<int, 0>{}, std::integral_constant<int, n - e1>{}, S_);
-        else if constexpr (n < e3) read_frag(BT{}, ks_, std::integral_constant<int, 1 + (n - e2) / RB>{}, std::integral_constant<int, (n - e2) % RB>{}, S_);
-        else                       read_frag(AT{}, ks_, std::integral_constant<int, 1 + (n - e3) / RA>{}, std::integral_constant<int, (n - e3) % RA>{}, S_);
+        if constexpr (n < e1)      read_frag(BT{}, ks_, std::integral_constant<int, 0>{}, std::integral_constant<int, n>{});
+        else if constexpr (n < e2) read_frag(AT{}, ks_, std::integral_constant<int, 0>{}, std::integral_constant<int, n - e1>{});
+        else if constexpr (n < e3) read_frag(BT{}, ks_, std::integral_constant<int, 1 + (n - e2) / RB>{}, std::integral_constant<int, (n - e2) % RB>{});
+        else                       read_frag(AT{}, ks_, std::integral_constant<int, 1 + (n - e3) / RA>{}, std::integral_constant<int, (n - e3) % RA>{});
     };
     // The accumulators start from the bias: nothing is left to add in the epilogue, which reads them twice where the
     // pre-activation is kept too.  The bias of the next C tile is asked for before the epilogue of this one.  (With the
@@ -243,50 +241,61 @@ void tp_gemm4_kernel(const GemmArgs p) {
     };
 
     // ------------------------------------------------------------------ one K tile: 64 MFMA slots
-    // Multiplies the K tile in stage S and keeps the loads going.  Slot s = 16 ks + 4 i + j issues MFMA
-    // (ks, i, j), then at most one fragment read and at most one load.
+    // Multiplies K tile u and keeps the loads going.  Slot s = 16 ks + 4 i + j issues MFMA (ks, i, j), then at most one
+    // fragment read and at most one load.
     //   reads: those of MFMA step ks + 1 during step ks (every other slot when there are 8, every slot but
     //     every fourth when 12, every slot when 16); those of step 0 of the NEXT K tile during step 3,
-    //     from the other stage, after the barrier before slot 48;
-    //   loads: the LATE operand of the K tile at the fetch cursor from slot 1 on (into the stage being refilled), then
-    //     the cursor moves on, and after the barrier the EARLY operand of the following K tile goes into the stage this
-    //     body has just finished reading.  All four waves run the same schedule, so a slot with a load asks the CU's one
-    //     address path for 4 KB (64 B/clk: two slots): loads every other slot, over step 0 and over step 3.
-    //   Where the rows of a contraction-contiguous operand do not start on cache lines, each of its loads asks for 16 lines
-    //   and not 8 (four slots of the address path), and bunched loads hold up the MFMAs behind them: in the NT form the late
-    //   operand has a load every fourth slot (19633 x 3424, K = 4880: 669 -> 648 us; aligned rows: no difference).
-    //   In the NN form the late operand is A if its rows are off the lines (the early one lands under fewer MFMAs: 8192 x 4096,
-    //   K = 12528: 751 us against 778, 8448 x 4096, K = 4456: 347 / 375) or if C is at least as tall as wide in tiles
-    //   (16384 x 4096, K = 4096: 469 / 474; 2048 x 2048, K = 32768: 240 / 245), else B (4096 x 24576, K = 6144: 988 us against
-    //   1036; 8192 x 24576 1963 / 2051).  From memory; every fourth slot instead costs up to 2 % here.
-    using Late = std::integral_constant<bool, A_LATE>;
-    using Early = std::integral_constant<bool, !A_LATE>;
-    auto k_tile = [&](auto S_) __attribute__((always_inline)) {
-        constexpr int S = decltype(S_)::value;
-        using SR = std::integral_constant<int, S>;          // stage read
-        using SW = std::integral_constant<int, 1 - S>;      // stage refilled
+    //     from the next stages, after the barrier before slot 48;
+    //   loads: those of K tile u + 2.  A has three stages: its loads come from slot 9 on, every fourth slot, into the stage of
+    //     tile u - 1, free since the last barrier; they have 70 - 100 slots to land.  B has two: its loads come after the barrier, every other
+    //     slot, into the stage that tile u has just been read from, and have 49 - 63.  (All four waves run the same schedule, so a slot
+    //     with a load asks the CU's one address path for 4 KB, two slots at 64 B/clk; four where rows are off cache lines.)
+    //   With two stages of each and the epilogue's patches beside them one operand had 17 - 47 slots, less than a load from beyond the
+    //   L2 takes.  From memory, in us, before and now: dX 2048 x 2048, K = 4 x 8192 255 -> 224; 4096 x 6144, K = 24576 1026 -> 946;
+    //   32896 x 640 243 -> 225; dW 640 x 2560, K = 2 x 32896 222 -> 208; rows off cache lines: 6144 x 768, K = 4 x 5256 227 -> 199,
+    //   dW 3680 x 5128, K = 3 x 5904 715 -> 635, dX 19633 x 3424, K = 4880 626 -> 585; aligned products that were short of nothing
+    //   (forward 16384 x 4096, K = 4096; dW 6144 x 24576, K = 4096) within 1 %.  Which operand is the deep one, and loads every second to fifth
+    //   slot, make less than 1 %.
+    using OpA = std::true_type;
+    using OpB = std::false_type;
+    // at_a, at_b: stages of tile u (from slot 44 / 46 on: u + 1), in bytes from the operand's first one; fill_a, fill_b: this
+    // wave's share of those to refill; to_next_a: from the stage of tile u to that of u + 1
+    uint32_t at_a = 0, at_b = 0, fill_a = s_wbase + W4_A_BASE + 2 * W4_STAGE, fill_b = 0, to_next_a = 0;
+    auto barrier = [&]() __attribute__((always_inline)) { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+    auto k_tile = [&]() __attribute__((always_inline)) {
         static_for<64>([&](auto s_) __attribute__((always_inline)) {
             constexpr int s = decltype(s_)::value;
             constexpr int ks = s >> 4, q = s & 15, i = (s >> 2) & 3, j = s & 3;
             if constexpr (s == 48) {
-                // this wave's loads of the next K tile have landed; after the barrier everybody's have, and
-                // nobody reads the current stage any more (the step-3 fragments were requested during step
-                // 2 and have arrived: the barrier waits for them)
-                wait_vm<0>();
-                __syncthreads();
+                // this wave's loads of tile u + 1 have landed (A's of tile u + 2 may be under way); after the
+                // barrier everybody's have, and nobody reads tile u any more (the step-3 fragments were requested
+                // during step 2 and have arrived: the barrier waits for them)
+                wait_vm<8>();
+                barrier();
+#pragma unroll
+                for (int vi = 0; vi < 4; ++vi) {
+                    ra_addr[vi] += to_next_a;
+                    rb_addr[vi] ^= W4_STAGE;
+                }
             }
             acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[ks & 1][j], fa[ks & 1][i], acc[i][j], 0, 0, 0);
             using KN = std::integral_constant<int, ks + 1>;
-            using ST = std::integral_constant<int, ks == 3 ? 1 - S : S>;
-            if constexpr (NR == 8)       { if constexpr (q % 2 == 0) read_n(std::integral_constant<int, q / 2>{}, KN{}, ST{}); }
-            else if constexpr (NR == 12) { if constexpr (q % 4 != 3) read_n(std::integral_constant<int, q - q / 4>{}, KN{}, ST{}); }
-            else                         read_n(std::integral_constant<int, q>{}, KN{}, ST{});
-            if constexpr (A_KC && B_KC) { if constexpr ((s & 3) == 1 && s < 32) dtl1(Late{}, std::integral_constant<int, s / 4>{}, SW{}); }
-            else                          { if constexpr ((s & 1) == 1 && s < 16) dtl1(Late{}, std::integral_constant<int, s / 2>{}, SW{}); }
-            if constexpr ((s & 1) == 1 && s > 48) dtl1(Early{}, std::integral_constant<int, (s - 49) / 2>{}, SR{});
-            if constexpr (s == 38) advance_fast();
-            if constexpr (s == 40) { if (f_reopen) advance_slow(); }
-            if constexpr (s == 42) prep_tile();
+            if constexpr (NR == 8)       { if constexpr (q % 2 == 0) read_n(std::integral_constant<int, q / 2>{}, KN{}); }
+            else if constexpr (NR == 12) { if constexpr (q % 4 != 3) read_n(std::integral_constant<int, q - q / 4>{}, KN{}); }
+            else                         read_n(std::integral_constant<int, q>{}, KN{});
+            // (about seven instructions pass under an MFMA: the cursor's are spread)
+            if constexpr (s == 0) advance_count();
+            if constexpr (s == 1) advance_k();
+            if constexpr (s == 2) advance_check();
+            if constexpr (s == 3) { if (f_reopen) advance_slow(); }
+            if constexpr (s == 4) prep_k0();
+            if constexpr (s == 6) prep_operand(OpA{});
+            if constexpr (s == 8) prep_operand(OpB{});
+            if constexpr (s >= 9 && s < 41 && s % 4 == 1) dtl1(OpA{}, std::integral_constant<int, (s - 9) / 4>{}, fill_a);
+            if constexpr (s == 42) to_next_a = at_a == 2 * W4_STAGE ? 0u - 2 * W4_STAGE : (uint32_t)W4_STAGE;
+            if constexpr (s == 44) { fill_a = s_wbase + W4_A_BASE + at_a; at_a += to_next_a; }
+            if constexpr (s == 46) { fill_b = s_wbase + at_b; at_b ^= W4_STAGE; }
+            if constexpr ((s & 1) == 1 && s > 48) dtl1(OpB{}, std::integral_constant<int, (s - 49) / 2>{}, fill_b);
             __builtin_amdgcn_sched_barrier(0);
         });
     };
@@ -297,65 +306,56 @@ void tp_gemm4_kernel(const GemmArgs p) {
     c = f;
     open_operand(std::true_type{});
     open_operand(std::false_type{});
-    // K tile 0 -> stage 0 (both operands), the early operand of K tile 1 -> stage 1; the late operand of K tile 1
-    // is the first thing the loop body loads
-    using S0 = std::integral_constant<int, 0>;
-    using S1 = std::integral_constant<int, 1>;
     prep_tile();
     if constexpr (USE_BIAS) load_bias(bias, p, c.n0 + wn * 128);
-    static_for<8>([&](auto n_) __attribute__((always_inline)) { dtl1(std::true_type{}, n_, S0{}); });
-    static_for<8>([&](auto n_) __attribute__((always_inline)) { dtl1(std::false_type{}, n_, S0{}); });
-    advance_fast();
+    // K tiles 0 and 1
+    auto load_both = [&](uint32_t a, uint32_t b) __attribute__((always_inline)) {
+        static_for<8>([&](auto n_) __attribute__((always_inline)) { dtl1(OpA{}, n_, s_wbase + W4_A_BASE + a); });
+        static_for<8>([&](auto n_) __attribute__((always_inline)) { dtl1(OpB{}, n_, s_wbase + b); });
+    };
+    load_both(0, 0);
+    advance_count();
+    advance_k();
+    advance_check();
     if (f_reopen) advance_slow();
     prep_tile();
-    static_for<8>([&](auto n_) __attribute__((always_inline)) { dtl1(Early{}, n_, S1{}); });
-    wait_vm<8>();
-    __syncthreads();
-    static_for<NR>([&](auto n_) __attribute__((always_inline)) { read_n(n_, S0{}, S0{}); });
+    load_both(W4_STAGE, W4_STAGE);
+    wait_vm<16>();
+    barrier();
+    static_for<NR>([&](auto n_) __attribute__((always_inline)) { read_n(n_, std::integral_constant<int, 0>{}); });
 
     while (true) {
         init_acc();
-        for (int n = c.left + c.odd; n > 0; n -= 2) {
-            k_tile(S0{});
-            k_tile(S1{});
-        }
+        for (int n = c.left; n > 0; --n) k_tile();
         const Cursor done = c;
         start(c, c.v + grid);
         if constexpr (USE_BIAS) { if (c.left != 0) load_bias(bias, p, c.n0 + wn * 128); }
+        // A's stage of the last K tile is free until the next body's loads: the wave's patch
+        char* const eps = lds + (fill_a - s_wbase) + w * W4_EPI_BYTES_PER_WAVE;
         store_c_block<TM, TN, EPI, F32_OUT, true>(p, acc, done.m0 + wm * 128, done.n0 + wn * 128, done.z, done.g, eps);
         if (c.left == 0) break;
+        barrier();                                    // every wave is done with its patch
     }
 }
 
 // ---------------------------------------------------------------------------------------------
 // host launcher
 // ---------------------------------------------------------------------------------------------
-template <bool A_KC, bool B_KC, int EPI, bool F32_OUT, bool A_LATE>
-static hipError_t launch4_late(const GemmArgs& a, hipStream_t stream) {
+template <bool A_KC, bool B_KC, int EPI, bool F32_OUT>
+static hipError_t launch4_one(const GemmArgs& a, hipStream_t stream) {
     static std::atomic<uint64_t> attr_done{0};
     int dev = 0;
     if (hipError_t e = hipGetDevice(&dev); e != hipSuccess) return e;
     const uint64_t bit = 1ull << (dev & 63);
     if (!(attr_done.load(std::memory_order_relaxed) & bit)) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&tp_gemm4_kernel<A_KC, B_KC, EPI, F32_OUT, A_LATE>),
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&tp_gemm4_kernel<A_KC, B_KC, EPI, F32_OUT>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, W4_LDS_BYTES);
         if (e != hipSuccess) return e;
         attr_done.fetch_or(bit, std::memory_order_relaxed);
     }
     const int total = a.tiles_m * a.tiles_n * a.split_k;
     const unsigned grid = (unsigned)(total < a.max_workgroups ? total : a.max_workgroups);
-    return launch_kernel(tp_gemm4_kernel<A_KC, B_KC, EPI, F32_OUT, A_LATE>, dim3(grid), dim3(W4_THREADS), W4_LDS_BYTES, stream, a);
-}
-
-// the operand whose loads come late (the figures are at k_tile)
-template <bool A_KC, bool B_KC, int EPI, bool F32_OUT>
-static hipError_t launch4_one(const GemmArgs& a, hipStream_t s) {
-    if constexpr (A_KC && !B_KC) {
-        bool a_late = a.tiles_m >= a.tiles_n;
-        for (int k = 0; k < a.n_steps; ++k) a_late |= (a.lda[k] & 63) || (reinterpret_cast<uintptr_t>(a.a[k]) & 127);
-        if (a_late) return launch4_late<A_KC, B_KC, EPI, F32_OUT, true>(a, s);
-    }
-    return launch4_late<A_KC, B_KC, EPI, F32_OUT, false>(a, s);
+    return launch_kernel(tp_gemm4_kernel<A_KC, B_KC, EPI, F32_OUT>, dim3(grid), dim3(W4_THREADS), W4_LDS_BYTES, stream, a);
 }
 
 hipError_t launch_gemm4(int form, const GemmArgs& a, hipStream_t s) {

@@ -44,6 +44,11 @@ __device__ __forceinline__ void dtl_load16(u32x4_t rsrc_words, uint32_t voff, ui
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
                  :: "s"(lds_base), "v"(voff), "s"(rsrc_words) : "memory");
 }
+// the same at a constant distance from a wave-uniform base
+template <int OFF> __device__ __forceinline__ void dtl_load16_at(u32x4_t rsrc_words, uint32_t voff, uint32_t lds_base) {
+    asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+                 :: "s"(lds_base), "v"(voff), "s"(rsrc_words), "i"(OFF) : "memory", "scc");
+}
 template <int N> __device__ __forceinline__ void wait_vm() {      // at most N vector-memory operations outstanding
     static_assert(N >= 0 && N < 64);
     __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));

@@ -900,3 +900,26 @@ def test_gelu_of_the_ends_of_the_range():
     got, big = y[0].tolist(), c[0].tolist()
     assert got[0] == inf and got[2] != got[2] and [got[3], got[5]] == [big[3], big[5]]
     assert got[1] == 0.0 and got[4] == 0.0 and got[6] == 0.0 and got[7] == 0.0
+
+
+@pytest.mark.parametrize("k_tiles", [1, 2, 3, 4])
+@pytest.mark.parametrize("form", ["NN", "NT", "TN"])
+def test_stream_kernel_with_few_k_tiles_a_tile(form, k_tiles):
+    """256 x 256 tiles, more of them than workgroups, with so few K tiles each that the loads run one or two C tiles ahead: the ring
+    of A's three stages starts a C tile at every position.  Ragged last rows and columns, the last K tile half empty."""
+    m, n, k = 4136, 4104, 64 * k_tiles - 24
+    gen = torch.Generator(device="cuda").manual_seed(k)
+    rand = lambda r, c: torch.randn((r, c), generator=gen, device="cuda", dtype=torch.bfloat16)
+    a, b = (rand(k, m) if form == "TN" else rand(m, k)), (rand(n, k) if form == "NT" else rand(k, n))
+    out = torch.full((m, n), float("nan"), device="cuda")
+    ws = torch.empty(256, dtype=torch.uint8, device="cuda")
+    with overrides(tile=1, split=1):
+        if form == "NN":
+            T.tp_linear_fwd(T.Grid(T.MODE_2D), (m, k, n), 1, [a], [b], None, T.EPI_NONE, out, None, ws)
+        elif form == "NT":
+            T.tp_linear_bwd(T.Grid(T.MODE_2D), (m, n, k), 1, 0, da_row_blocks=[a], w_blocks_dx=[b], dx=out, workspace=ws)
+        else:
+            T.tp_linear_bwd(T.Grid(T.MODE_2D), (k, m, n), 0, 1, x_blocks_dw=[a], da_col_blocks=[b], dw=out, workspace=ws)
+    ref = (a.double().T if form == "TN" else a.double()) @ (b.double().T if form == "NT" else b.double())
+    # fp32 sums of k products of values below 6: k roundings of at most 2^-24 of the largest partial sum, 36 k
+    assert float((out.double() - ref).abs().max()) <= k * 2.0 ** -24 * 36 * k
