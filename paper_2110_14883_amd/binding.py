@@ -1,12 +1,14 @@
-"""ctypes binding of libtplinear.so: same names as the C ABI (include/tp_linear.h), argument
-marshalling only.  Tensors are torch CUDA(ROCm) tensors used purely as device buffers: their
-data_ptr(), row stride and dtype are handed to the library; nothing is computed here."""
+"""Binding of libtplinear.so: same names as the C ABI (include/tp_linear.h), argument marshalling
+only.  Tensors are torch CUDA(ROCm) tensors used purely as device buffers: their data_ptr(), row
+stride and dtype are handed to the library; nothing is computed here.  The calls that launch work are marshalled by a
+small extension module (csrc/tp_pycall.cpp), the others and lib() are ctypes."""
 from __future__ import annotations
 
 import contextlib
 import contextvars
 import ctypes as C
 import functools
+import importlib.util
 import os
 from dataclasses import dataclass
 
@@ -17,6 +19,7 @@ DT_BF16, DT_F32 = 0, 1
 MAX_STEPS = 16
 
 _LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libtplinear.so")
+_CALL_PATH = os.path.join(os.path.dirname(_LIB_PATH), "_tpcall.so")
 _lib = None
 
 
@@ -65,7 +68,7 @@ def plan_opts(tile: int = 0, split_k: int = 0, group_m: int = 0, rotate: int = 0
 
 def _opts():
     o = _plan_opts.get()
-    return None if o is None else C.byref(o)
+    return None if o is None else C.addressof(o)
 
 
 @dataclass(frozen=True)
@@ -81,6 +84,9 @@ class Grid:
 
     def _c(self) -> _GridS:
         return self._struct
+
+    def _at(self) -> int:
+        return C.addressof(self._struct)
 
     @functools.cached_property
     def _struct(self) -> _GridS:             # (immutable on both sides of the call)
@@ -148,15 +154,23 @@ def lib() -> C.CDLL:
 
 
 @functools.lru_cache(maxsize=1)
-def _calls() -> C.CDLL:
-    """The same library with prototypes of its own for the calls of this module, whose block arrays are arrays of words
-    (built in half the time of an array of structures)."""
-    L, raw = lib(), C.CDLL(_LIB_PATH)
-    for name in ("tp_linear_fwd_ex", "tp_linear_fwd_static", "tp_linear_bwd_ex", "tp_linear_bwd_partials_ex"):
-        fn, typed = getattr(raw, name), getattr(L, name)
-        fn.restype = typed.restype
-        fn.argtypes = [C.c_void_p if t is C.POINTER(_CBlk) else t for t in typed.argtypes]
-    return raw
+def _call():
+    """The extension module that makes the calls, given the loaded library's functions."""
+    L = lib()
+    if not os.path.exists(_CALL_PATH):
+        raise RuntimeError(f"{_CALL_PATH} is not built; run `python -m paper_2110_14883_amd.build`")
+    spec = importlib.util.spec_from_file_location("_tpcall", _CALL_PATH)
+    m = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(m)
+    try:
+        import torch
+        dtypes = (torch.float32, torch.bfloat16)
+    except ImportError:                      # blocks are then (address, leading dimension[, dtype]) sequences
+        dtypes = (None, None)
+    names = ("tp_linear_fwd_ex", "tp_linear_fwd_static", "tp_linear_bwd_ex", "tp_linear_bwd_partials_ex", "tp_bias_act", "tp_dgelu",
+             "tp_bias_grad")
+    m.bind(*[C.cast(getattr(L, n), C.c_void_p).value for n in names], *dtypes)
+    return m
 
 
 EXPORTS = ("tp_block_map", "tp_linear_workspace_size", "tp_linear_workspace_size_ex", "tp_linear_fwd", "tp_linear_fwd_ex",
@@ -171,93 +185,23 @@ def _dims(dims) -> _DimsS:
     return _DimsS(int(M), int(H), int(F))
 
 
-def _is_tensor(t) -> bool:
-    return hasattr(t, "data_ptr")
-
-
-# (These run for every block of every call, and the smallest calls are shorter on the GPU than here: each asks the
-# tensor as little as it can.  256 x 1024 x 4096 forward on a 2 x 2 grid: 13.7 -> 11.0 us a pass, a training step of
-# 600 x 272 x 656: 48 -> 39 us.)
-def _ld(t) -> int:
-    st = t.stride()
-    if len(st) == 2 and (st[1] == 1 or t.shape[1] <= 1):
-        return st[0]
-    if len(st) == 1:
-        return int(t.shape[0])
-    raise ValueError("blocks must be 2-D with unit column stride")
-
-
-def _blk(t):
-    """torch tensor, (ptr, ld) pair or None -> address and leading dimension."""
-    if _is_tensor(t):
-        return t.data_ptr(), _ld(t)
-    if t is None:
-        return None, 0
-    return int(t[0]) or None, int(t[1])
-
-
-def _cblk(t) -> _CBlk:
-    return _CBlk(*_blk(t))
-
-
-@functools.lru_cache(maxsize=64)
-def _array_type(block, n):
-    return block * n
-
-
-def _cblk_array(blocks, n):
-    if blocks is None:
-        return None
-    words = []                               # a tp_cblk_t is two words: an array of words is filled in one go
-    for b in blocks:
-        ptr, ld = _blk(b)
-        words += (ptr or 0, ld)
-    return _array_type(C.c_int64, 2 * max(n, len(blocks), 1))(*words)
-
-
-def _oblk_array(blocks, n):
-    if blocks is None:
-        return None
-    return _array_type(_OBlk, max(n, len(blocks), 1))(*[_oblk(b) for b in blocks])
-
-
-def _cblk_ptr(t):
-    return None if t is None else C.byref(_cblk(t))
+def _rows_cols(t, rows, cols):
+    return (t.shape[0], t.shape[1]) if rows is None else (rows, cols)
 
 
 @functools.lru_cache(maxsize=1)
-def _dtypes() -> dict:
+def _current_stream_calls():
     import torch
-    return {torch.float32: DT_F32, torch.bfloat16: DT_BF16}
-
-
-def _oblk(t) -> _OBlk:
-    """torch tensor, (ptr, ld, dtype) triple or None -> tp_oblk_t."""
-    if t is None:
-        return _OBlk(None, 0, 0)
-    if _is_tensor(t):
-        return _OBlk(t.data_ptr(), _ld(t), _dtypes().get(t.dtype, 99))    # 99: the library answers TP_ERR_DTYPE
-    return _OBlk(int(t[0]) or None, int(t[1]), int(t[2]))
-
-
-def _ptr(t):
-    if t is None:
-        return None
-    return t.data_ptr() if _is_tensor(t) else int(t)
-
-
-def _ws(workspace):
-    if workspace is None:
-        return None, 0
-    if _is_tensor(workspace):
-        return workspace.data_ptr(), workspace.numel() * workspace.element_size()
-    return int(workspace[0]), int(workspace[1])
+    torch.cuda.current_stream()              # (initialises the device, or says why it cannot)
+    return torch.cuda.current_stream, torch._C._cuda_isInBadFork, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
 
 
 def _stream(stream):
+    """A stream's handle; None is torch's current stream on the current device (asked for by its handle: making the stream
+    object as well takes 2.9 us, a third of a small call)."""
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
+        as_object, forked, device, raw = _current_stream_calls()
+        return as_object().cuda_stream if forked() else raw(device())
     return getattr(stream, "cuda_stream", stream)
 
 
@@ -287,27 +231,20 @@ def tp_block_map(grid: Grid, dims, pass_: int) -> dict:
 
 def tp_linear_workspace_size(grid: Grid, dims, pass_: int) -> int:
     g, d = grid._c(), _dims(dims)
-    return int(lib().tp_linear_workspace_size_ex(C.byref(g), C.byref(d), int(pass_), _opts()))
+    return int(lib().tp_linear_workspace_size_ex(C.byref(g), C.byref(d), int(pass_), _plan_opts.get()))
 
 
 def tp_linear_fwd(grid: Grid, dims, n_steps: int, x_blocks, w_blocks, bias, epi: int, y, preact=None,
                   workspace=None, stream=None) -> None:
-    g, d = grid._c(), _dims(dims)
-    ws, wsb = _ws(workspace)
-    st = _calls().tp_linear_fwd_ex(C.byref(g), C.byref(d), int(n_steps), _cblk_array(x_blocks, n_steps),
-                                _cblk_array(w_blocks, n_steps), _ptr(bias), int(epi), _oblk(y), _oblk(preact),
-                                ws, wsb, _stream(stream), _opts())
-    _check(st, "tp_linear_fwd")
+    _check(_call().fwd(grid._at(), dims, n_steps, x_blocks, w_blocks, bias, epi, y, preact, workspace, _stream(stream), _opts()),
+           "tp_linear_fwd")
 
 
 def tp_linear_fwd_static(grid: Grid, dims, n_steps: int, x_blocks, w_blocks, bias, epi: int, y, preact=None,
                          stream=None) -> None:
     """tp_linear_fwd without a workspace: K-split partials go to the library's built-in scratch array."""
-    g, d = grid._c(), _dims(dims)
-    st = _calls().tp_linear_fwd_static(C.byref(g), C.byref(d), int(n_steps), _cblk_array(x_blocks, n_steps),
-                                    _cblk_array(w_blocks, n_steps), _ptr(bias), int(epi), _oblk(y), _oblk(preact),
-                                    _stream(stream))
-    _check(st, "tp_linear_fwd_static")
+    _check(_call().fwd_static(grid._at(), dims, n_steps, x_blocks, w_blocks, bias, epi, y, preact, _stream(stream)),
+           "tp_linear_fwd_static")
 
 
 def tp_static_scratch_bytes() -> int:
@@ -318,23 +255,14 @@ def tp_linear_bwd(grid: Grid, dims, n_steps_dx: int = 0, n_steps_dw: int = 0, dy
                   da_row_blocks=None, w_blocks_dx=None, x_blocks_dw=None, da_col_blocks=None,
                   own_slot_dx: int = -1, own_slot_dw: int = -1, dgelu_preact=None,
                   dx=None, dw=None, da_own_out=None, db=None, workspace=None, stream=None) -> None:
-    g, d = grid._c(), _dims(dims)
-    ws, wsb = _ws(workspace)
-    st = _calls().tp_linear_bwd_ex(C.byref(g), C.byref(d), int(n_steps_dx), int(n_steps_dw),
-                             _cblk_ptr(dy_own), _cblk_ptr(preact_own),
-                             _cblk_array(da_row_blocks, n_steps_dx), _cblk_array(w_blocks_dx, n_steps_dx),
-                             _cblk_array(x_blocks_dw, n_steps_dw), _cblk_array(da_col_blocks, n_steps_dw),
-                             int(own_slot_dx), int(own_slot_dw), _cblk_ptr(dgelu_preact),
-                             _oblk(dx), _oblk(dw), _oblk(da_own_out), _ptr(db), ws, wsb, _stream(stream), _opts())
-    _check(st, "tp_linear_bwd")
+    _check(_call().bwd(grid._at(), dims, n_steps_dx, n_steps_dw, dy_own, preact_own, da_row_blocks, w_blocks_dx, x_blocks_dw,
+                       da_col_blocks, own_slot_dx, own_slot_dw, dgelu_preact, dx, dw, da_own_out, db, workspace, _stream(stream),
+                       _opts()), "tp_linear_bwd")
 
 
 def tp_dgelu(dy, preact, da, rows: int | None = None, cols: int | None = None, stream=None) -> None:
-    if rows is None:
-        rows, cols = int(dy.shape[0]), int(dy.shape[1])
-    a, b, c = _cblk(dy), _cblk(preact), _cblk(da)
-    st = lib().tp_dgelu(a.ptr, a.ld, b.ptr, b.ld, c.ptr, c.ld, int(rows), int(cols), _stream(stream))
-    _check(st, "tp_dgelu")
+    rows, cols = _rows_cols(dy, rows, cols)
+    _check(_call().dgelu(dy, preact, da, rows, cols, _stream(stream)), "tp_dgelu")
 
 
 def tp_partials_map(grid: Grid, dims, pass_: int) -> dict:
@@ -352,33 +280,22 @@ def tp_partials_map(grid: Grid, dims, pass_: int) -> dict:
 
 def tp_linear_bwd_partials(grid: Grid, dims, da_own, w_blocks_dx=None, dx_partials=None, x_blocks_dw=None,
                            dw_partials=None, workspace=None, stream=None) -> None:
-    g, d = grid._c(), _dims(dims)
-    ws, wsb = _ws(workspace)
     n_dx = 0 if w_blocks_dx is None else len(w_blocks_dx)
     n_dw = 0 if x_blocks_dw is None else len(x_blocks_dw)
     if (dx_partials is not None and len(dx_partials) != n_dx) or (dw_partials is not None and len(dw_partials) != n_dw):
         raise ValueError("one output block per operand block")
-    st = _calls().tp_linear_bwd_partials_ex(C.byref(g), C.byref(d), n_dx, n_dw, _cblk_ptr(da_own),
-                                      _cblk_array(w_blocks_dx, n_dx), _oblk_array(dx_partials, n_dx),
-                                      _cblk_array(x_blocks_dw, n_dw), _oblk_array(dw_partials, n_dw),
-                                      ws, wsb, _stream(stream), _opts())
-    _check(st, "tp_linear_bwd_partials")
+    _check(_call().bwd_partials(grid._at(), dims, n_dx, n_dw, da_own, w_blocks_dx, dx_partials, x_blocks_dw, dw_partials, workspace,
+                                _stream(stream), _opts()), "tp_linear_bwd_partials")
 
 
 def tp_bias_act(c, bias, epi: int, y, preact=None, rows: int | None = None, cols: int | None = None, stream=None) -> None:
-    if rows is None:
-        rows, cols = int(c.shape[0]), int(c.shape[1])
-    ptr, ld = (c.data_ptr(), _ld(c)) if _is_tensor(c) else (int(c[0]), int(c[1]))
-    st = lib().tp_bias_act(ptr or None, ld, _ptr(bias), int(epi), _oblk(y), _oblk(preact), int(rows), int(cols), _stream(stream))
-    _check(st, "tp_bias_act")
+    rows, cols = _rows_cols(c, rows, cols)
+    _check(_call().bias_act(c, bias, epi, y, preact, rows, cols, _stream(stream)), "tp_bias_act")
 
 
 def tp_bias_grad(da, db, rows: int | None = None, cols: int | None = None, workspace=None, stream=None) -> None:
-    if rows is None:
-        rows, cols = int(da.shape[0]), int(da.shape[1])
-    a = _cblk(da)
-    ws, wsb = _ws(workspace)
-    _check(lib().tp_bias_grad(a.ptr, a.ld, int(rows), int(cols), _ptr(db), ws, wsb, _stream(stream)), "tp_bias_grad")
+    rows, cols = _rows_cols(da, rows, cols)
+    _check(_call().bias_grad(da, db, rows, cols, workspace, _stream(stream)), "tp_bias_grad")
 
 
 def tp_bias_grad_workspace_size(rows: int, cols: int) -> int:

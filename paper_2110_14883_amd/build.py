@@ -1,4 +1,5 @@
-"""Builds libtplinear.so (gfx950) in-tree with hipcc.  `python -m paper_2110_14883_amd.build`.
+"""Builds libtplinear.so (gfx950) in-tree with hipcc, and the binding's extension module _tpcall.so (host code)
+with the C++ compiler.  `python -m paper_2110_14883_amd.build`.
 
 Every source is compiled to its own object (in parallel) and the objects are linked into the shared
 library; objects are kept under csrc/_build/ and reused while their source and the headers are older."""
@@ -7,6 +8,7 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 PKG_DIR = os.path.dirname(os.path.abspath(__file__))
@@ -15,6 +17,8 @@ CSRC = os.path.join(PKG_DIR, "csrc")
 OBJ_DIR = os.path.join(CSRC, "_build")
 LIB_PATH = os.path.join(PKG_DIR, "libtplinear.so")
 PROBE_LIB_PATH = os.path.join(PKG_DIR, "libtpprobe.so")      # bench-only measurement aid (tp_probe.hip)
+CALL_LIB_PATH = os.path.join(PKG_DIR, "_tpcall.so")
+CALL_SOURCE = "tp_pycall.cpp"
 SOURCES = ["tp_kernels.hip", "tp_gemm4.hip", "tp_gemm_ms.hip", "tp_small.hip", "tp_api.cpp"]
 PROBE_SOURCE = "tp_probe.hip"
 HEADERS = [os.path.join(ROOT, "include", "tp_linear.h"), os.path.join(ROOT, "include", "tp_probe.h"), os.path.join(CSRC, "tp_internal.h"), os.path.join(CSRC, "tp_device.h"), os.path.join(CSRC, "tp_stream.h")]
@@ -55,6 +59,8 @@ def build_library(verbose: bool = True, extra_flags: list[str] | None = None, fo
         if not fresh:
             jobs.append([hipcc, *HIPCC_FLAGS, *(extra_flags or []), "-I", os.path.join(ROOT, "include"), "-I", CSRC,
                          "-c", path, "-o", obj])
+    jobs.append([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-Wall", "-fPIC", "-shared", "-I", os.path.join(ROOT, "include"), "-I",
+                 sysconfig.get_paths()["include"], os.path.join(CSRC, CALL_SOURCE), "-o", CALL_LIB_PATH])
     with ThreadPoolExecutor(max_workers=4) as ex:
         list(ex.map(lambda c: _run(c, verbose), jobs))
     _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", *objs[:-1], "-o", LIB_PATH], verbose)

@@ -310,3 +310,47 @@ def test_typed_prototypes_of_the_loaded_library():
     for blocks in (dims, (C.c_int64 * 2)(4096, 8)):
         with pytest.raises(C.ArgumentError):
             L.tp_linear_fwd(grid, dims, 0, blocks, blocks, None, 0, out, none, None, 0, None)
+
+
+def test_marshalling_hands_over_what_it_was_given():
+    """Tensors, (address, leading dimension) sequences and None, as the C functions receive them: a recording function is put in
+    the place of the forward, and the library's own ones are put back."""
+    import numpy as np
+    import torch
+    m, L = B._call(), B.lib()
+    names = ("tp_linear_fwd_ex", "tp_linear_fwd_static", "tp_linear_bwd_ex", "tp_linear_bwd_partials_ex", "tp_bias_act", "tp_dgelu", "tp_bias_grad")
+    own = [C.cast(getattr(L, n), C.c_void_p).value for n in names]
+    got = {}
+
+    def record(grid, dims, steps, x, w, bias, epi, y, pre, ws, wsb, stream, opts):
+        got.update(mode=grid[0].mode, dims=(dims[0].M, dims[0].H, dims[0].F), steps=steps, x=[(x[i].ptr, x[i].ld) for i in range(3)] if x else None,
+                   w=(w[0].ptr, w[0].ld), bias=bias, epi=epi, y=(y.ptr, y.ld, y.dtype), pre=(pre.ptr, pre.ld, pre.dtype), ws=(ws, wsb),
+                   stream=stream, opts=(opts[0].tile, opts[0].split_k) if opts else None)
+        return 0
+
+    fn = C.CFUNCTYPE(C.c_int, C.POINTER(B._GridS), C.POINTER(B._DimsS), C.c_int, C.POINTER(B._CBlk), C.POINTER(B._CBlk), C.c_void_p, C.c_int, B._OBlk,
+                     B._OBlk, C.c_void_p, C.c_size_t, C.c_void_p, C.POINTER(B._PlanOpts))(record)
+    a, b = torch.zeros(4, 24, dtype=torch.bfloat16)[:, 8:16], torch.zeros(3, 1, dtype=torch.bfloat16).t().t()
+    row, ws = torch.zeros(40, dtype=torch.float32), torch.zeros(6, dtype=torch.float32)
+    grid = T.Grid(T.MODE_2D, q=2)
+    try:
+        m.bind(C.cast(fn, C.c_void_p).value, *own[1:], torch.float32, torch.bfloat16)
+        with B.plan_opts(tile=3, split_k=2):
+            T.tp_linear_fwd(grid, [np.int64(4), 8.0, 16], np.int32(2), (a, [0x40, 72]), [b], row, T.EPI_BIAS, row, (0x80, 64, B.DT_BF16), ws, 0x1234)
+        assert got == dict(mode=T.MODE_2D, dims=(4, 8, 16), steps=2, x=[(a.data_ptr(), 24), (0x40, 72), (None, 0)], w=(b.data_ptr(), b.stride(0)),
+                           bias=row.data_ptr(), epi=T.EPI_BIAS, y=(row.data_ptr(), 40, B.DT_F32), pre=(0x80, 64, B.DT_BF16),
+                           ws=(ws.data_ptr(), 24), stream=0x1234, opts=(3, 2))
+        T.tp_linear_fwd(grid, (4, 8, 16), 1, None, [None], None, 0, a, None, (0x100, 2 ** 40), stream=0)
+        assert got["x"] is None and got["w"] == (None, 0) and got["bias"] is None and got["y"][2] == B.DT_BF16 and got["pre"] == (None, 0, 0)
+        assert got["ws"] == (0x100, 2 ** 40) and got["stream"] is None and got["opts"] is None
+        T.tp_linear_fwd(grid, (4, 8, 16), 1, [a] * 20, [a], None, 0, a.to(torch.float16), stream=0)
+        assert got["y"][2] == 99 and got["x"][2] == (a.data_ptr(), 24) and got["ws"] == (None, 0)
+        for bad, what in (([a.t()], ValueError), ([torch.zeros(2, 2, 2)], ValueError), ([5], TypeError), (5, TypeError), ([("x", 8)], ValueError), ([(1,)], IndexError)):
+            with pytest.raises(what):
+                T.tp_linear_fwd(grid, (4, 8, 16), 1, bad, [a], None, 0, a, stream=0)
+        for dims in ((1, 2), 7):
+            with pytest.raises((ValueError, TypeError)):
+                T.tp_linear_fwd(grid, dims, 1, [a], [a], None, 0, a, stream=0)
+    finally:
+        m.bind(*own, torch.float32, torch.bfloat16)
+    assert _st(lambda: T.tp_linear_fwd(grid, (4, 8, 16), 1, None, [a], None, 0, a, stream=0)) == 1
