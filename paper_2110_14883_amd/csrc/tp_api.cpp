@@ -411,6 +411,41 @@ int run_product(const Opts& o, const Product& pr, void* workspace, hipStream_t s
     return run_one(o, pr.form, pr.four_wave, pl.tail_tile_id, pl.tail_split, tail, stream);
 }
 
+// Bytes a product reads or writes: the span of one block of rows x cols (es bytes an element)
+struct Range { uintptr_t lo, hi; };
+Range span(const void* p, int64_t ld, int64_t rows, int64_t cols, int es) {
+    const uintptr_t lo = reinterpret_cast<uintptr_t>(p);
+    return Range{lo, lo + (uintptr_t)(((rows - 1) * ld + cols) * es)};
+}
+bool overlap(const Range& a, const Range& b) { return a.lo < b.hi && b.lo < a.hi; }
+
+// whether `w` writes anything that `r` reads or writes
+bool writes_into(const GemmArgs& w, int form, const GemmArgs& r) {
+    const int outs = w.n_groups > 1 ? w.n_groups : 1, slots = r.n_groups > 1 ? r.n_groups : r.n_steps, r_outs = r.n_groups > 1 ? r.n_groups : 1;
+    for (int g = 0; g < outs; ++g) {
+        const Range o = w.n_groups > 1 ? span(w.outs[g], w.ldos[g], w.M, w.N, 4) : span(w.out, w.ldo, w.M, w.N, w.out_f32 ? 4 : 2);
+        for (int s = 0; s < slots; ++s) {
+            if (overlap(o, form == FORM_TN ? span(r.a[s], r.lda[s], r.K, r.M, 2) : span(r.a[s], r.lda[s], r.M, r.K, 2))) return true;
+            if (overlap(o, form == FORM_NT ? span(r.b[s], r.ldb[s], r.N, r.K, 2) : span(r.b[s], r.ldb[s], r.K, r.N, 2))) return true;
+        }
+        if (r.dg && overlap(o, span(r.dg, r.lddg, r.M, r.N, 2))) return true;
+        for (int h = 0; h < r_outs; ++h)
+            if (overlap(o, r.n_groups > 1 ? span(r.outs[h], r.ldos[h], r.M, r.N, 4) : span(r.out, r.ldo, r.M, r.N, r.out_f32 ? 4 : 2))) return true;
+    }
+    return false;
+}
+
+// The two products of a backward call, dX first.  Where both run on the workgroup-split kernel they share one launch, unless one
+// writes what the other reads: then the order is what the caller counts on.
+int run_backward(const Opts& o, const Product& px, const Product& pw, void* workspace, hipStream_t stream) {
+    auto small = [](const Product& p) { return p.active && (p.plan.tile_id == TILE_32x32_SMALL || p.plan.tile_id == TILE_16x32_SMALL); };
+    if (small(px) && small(pw) && !writes_into(px.args, pw.form, pw.args) && !writes_into(pw.args, px.form, px.args))
+        return launch_gemm_pair(px.plan.tile_id, px.args, pw.plan.tile_id, pw.args, stream) == hipSuccess ? TP_OK : TP_ERR_HIP;
+    if (px.active) if (int e = run_product(o, px, workspace, stream)) return e;
+    if (pw.active) if (int e = run_product(o, pw, workspace, stream)) return e;
+    return TP_OK;
+}
+
 void fill_common(const Opts& o, GemmArgs& a, int64_t m, int64_t n, int64_t k, int n_steps) {
     std::memset(&a, 0, sizeof(a));
     a.M = (int32_t)m; a.N = (int32_t)n; a.K = (int32_t)k; a.n_steps = n_steps;
@@ -436,14 +471,6 @@ void plan_product(const Opts& o, Product& pr) {
 bool ws_ok(size_t need, const void* workspace, size_t bytes) {
     return need == 0 || (workspace && bytes >= need && aligned16(workspace));
 }
-
-// byte range of an fp32 output block [rows, cols] with leading dimension ld
-struct Range { uintptr_t lo, hi; };
-Range out_range(const tp_oblk_t& b, int64_t rows, int64_t cols) {
-    const uintptr_t lo = reinterpret_cast<uintptr_t>(b.ptr);
-    return Range{lo, lo + (uintptr_t)(((rows - 1) * b.ld + cols) * 4)};
-}
-bool overlap(const Range& a, const Range& b) { return a.lo < b.hi && b.lo < a.hi; }
 
 // ---------------------------------------------------------------------------------------------
 // Built-in scratch for tp_linear_fwd_static: a fixed array in device memory (every GPU the library
@@ -686,9 +713,7 @@ int tp_linear_bwd_ex(const tp_grid_t* grid, const tp_dims_t* dims, int n_steps_d
                                                    da_own_out.ld, sf.m, sf.n, stream);
         if (e != hipSuccess) return TP_ERR_HIP;
     }
-    if (px.active) if (int e = run_product(o, px, workspace, stream)) return e;
-    if (pw.active) if (int e = run_product(o, pw, workspace, stream)) return e;
-    return TP_OK;
+    return run_backward(o, px, pw, workspace, stream);
 }
 
 int tp_linear_bwd(const tp_grid_t* grid, const tp_dims_t* dims, int n_steps_dx, int n_steps_dw,
@@ -745,7 +770,7 @@ int tp_linear_bwd_partials_ex(const tp_grid_t* grid, const tp_dims_t* dims, int 
         for (int k = 0; k < n_dx; ++k) {
             if (int e = check_cblk(w_blocks_dx[k], sx.k)) return e;    // W block [H_blk][F_blk]: n x k
             if (int e = check_oblk(dx_partials[k], sx.n, true)) return e;
-            ranges[n_ranges++] = out_range(dx_partials[k], sx.m, sx.n);
+            ranges[n_ranges++] = span(dx_partials[k].ptr, dx_partials[k].ld, sx.m, sx.n, 4);
             px.args.a[k] = da_own->ptr; px.args.lda[k] = (int32_t)da_own->ld;
             px.args.b[k] = w_blocks_dx[k].ptr; px.args.ldb[k] = (int32_t)w_blocks_dx[k].ld;
             px.args.outs[k] = dx_partials[k].ptr; px.args.ldos[k] = dx_partials[k].ld;
@@ -762,7 +787,7 @@ int tp_linear_bwd_partials_ex(const tp_grid_t* grid, const tp_dims_t* dims, int 
         for (int k = 0; k < n_dw; ++k) {
             if (int e = check_cblk(x_blocks_dw[k], sw.m)) return e;    // X block [M_blk][H_blk]: k x m
             if (int e = check_oblk(dw_partials[k], sw.n, true)) return e;
-            ranges[n_ranges++] = out_range(dw_partials[k], sw.m, sw.n);
+            ranges[n_ranges++] = span(dw_partials[k].ptr, dw_partials[k].ld, sw.m, sw.n, 4);
             pw.args.a[k] = x_blocks_dw[k].ptr; pw.args.lda[k] = (int32_t)x_blocks_dw[k].ld;
             pw.args.b[k] = da_own->ptr; pw.args.ldb[k] = (int32_t)da_own->ld;
             pw.args.outs[k] = dw_partials[k].ptr; pw.args.ldos[k] = dw_partials[k].ld;
@@ -780,9 +805,7 @@ int tp_linear_bwd_partials_ex(const tp_grid_t* grid, const tp_dims_t* dims, int 
     if (pw.active) need = std::max(need, pw.plan.need);
     if (!ws_ok(need, workspace, workspace_bytes)) return TP_ERR_WORKSPACE;
     if (int e = check_device()) return e;
-    if (px.active) if (int e = run_product(o, px, workspace, stream)) return e;
-    if (pw.active) if (int e = run_product(o, pw, workspace, stream)) return e;
-    return TP_OK;
+    return run_backward(o, px, pw, workspace, stream);
 }
 
 int tp_linear_bwd_partials(const tp_grid_t* grid, const tp_dims_t* dims, int n_dx, int n_dw, const tp_cblk_t* da_own,

@@ -65,6 +65,9 @@ hipError_t launch_gemm(int form, int tile_id, const GemmArgs& args, hipStream_t 
 hipError_t launch_gemm4(int form, const GemmArgs& args, hipStream_t stream);   // TILE_256x256_W4 (args already normalised)
 hipError_t launch_gemm_ms(int form, int tile_id, const GemmArgs& args, hipStream_t stream);   // TILE_..._MS (args already normalised)
 hipError_t launch_small(int form, int tile_id, const GemmArgs& args, hipStream_t stream);     // TILE_..._SMALL (args already normalised)
+// dX (NT) and dW (TN), both of TILE_..._SMALL, in one launch
+hipError_t launch_gemm_pair(int tile_x, const GemmArgs& x, int tile_w, const GemmArgs& w, hipStream_t stream);
+hipError_t launch_small_pair(int tile_x, const GemmArgs& x, int tile_w, const GemmArgs& w, hipStream_t stream);      // (args already normalised)
 hipError_t launch_reduce(const ReduceArgs& args, hipStream_t stream);
 hipError_t launch_dgelu(const void* dy, int64_t ld_dy, const void* pre, int64_t ld_pre,
                         void* da, int64_t ld_da, int64_t rows, int64_t cols, hipStream_t stream);

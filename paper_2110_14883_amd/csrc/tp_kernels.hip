@@ -555,15 +555,26 @@ static hipError_t launch_tile(int form, const GemmArgs& a, hipStream_t s) {
     }
 }
 
-hipError_t launch_gemm(int form, int tile_id, const GemmArgs& args, hipStream_t s) {
-    GemmArgs a = args;
-    if (a.n_groups <= 1) {             // a plain launch is one group whose output is `out`
+// A plain launch is one group whose output is `out`; false: a grouped one that does not hold together.
+static bool normalise(GemmArgs& a) {
+    if (a.n_groups <= 1) {
         a.n_groups = 1; a.group_along_n = 1; a.group_tiles = a.tiles_n;
         a.outs[0] = a.out; a.ldos[0] = a.ldo;
-    } else if (a.n_steps != 1 || a.n_groups > TP_MAX_STEPS || a.group_tiles < 1 || a.bias || a.dg || a.pre ||
-               (a.group_along_n ? a.tiles_n : a.tiles_m) != a.n_groups * a.group_tiles) {
-        return hipErrorInvalidValue;
+        return true;
     }
+    return a.n_steps == 1 && a.n_groups <= TP_MAX_STEPS && a.group_tiles >= 1 && !a.bias && !a.dg && !a.pre &&
+           (a.group_along_n ? a.tiles_n : a.tiles_m) == a.n_groups * a.group_tiles;
+}
+
+hipError_t launch_gemm_pair(int tile_x, const GemmArgs& x, int tile_w, const GemmArgs& w, hipStream_t s) {
+    GemmArgs nx = x, nw = w;
+    if (!normalise(nx) || !normalise(nw)) return hipErrorInvalidValue;
+    return launch_small_pair(tile_x, nx, tile_w, nw, s);
+}
+
+hipError_t launch_gemm(int form, int tile_id, const GemmArgs& args, hipStream_t s) {
+    GemmArgs a = args;
+    if (!normalise(a)) return hipErrorInvalidValue;
     switch (tile_id) {
         case TILE_256x256: return launch_tile<256, 256>(form, a, s);
         case TILE_128x256: return launch_tile<128, 256>(form, a, s);

@@ -25,10 +25,9 @@ template <int MT> struct SmShape {
 };
 }
 
-// MT: 16-row blocks of the tile (1 or 2; 2 if A is not contraction-contiguous)
+// One workgroup's tile `id` of a product.  MT: 16-row blocks of the tile (1 or 2; 2 if A is not contraction-contiguous)
 template <int MT, bool A_KC, bool B_KC>
-__global__ __launch_bounds__(SM_THREADS)
-void tp_small_kernel(const GemmArgs p, const Epilogue e) {
+__device__ __forceinline__ void small_tile(const GemmArgs& p, const Epilogue& e, const int id) {
     static_assert(MT == 2 || (MT == 1 && A_KC));
     using Sh = SmShape<MT>;
     constexpr int BM = Sh::BM, NS = Sh::NS, A_BYTES = BM * 128;
@@ -37,7 +36,7 @@ void tp_small_kernel(const GemmArgs p, const Epilogue e) {
     const int t = threadIdx.x, l = t & 63, c = l & 15, kg = l >> 4;
     const int w = uni(t >> 6);
     int tm, tn, z, g = 0;
-    tile_of_id(p, (int)blockIdx.x, tm, tn, z);
+    tile_of_id(p, id, tm, tn, z);
     if (p.n_groups > 1) {
         if (p.group_along_n) { g = tn / p.group_tiles; tn -= g * p.group_tiles; }
         else                 { g = tm / p.group_tiles; tm -= g * p.group_tiles; }
@@ -164,20 +163,51 @@ void tp_small_kernel(const GemmArgs p, const Epilogue e) {
 }
 
 template <int MT, bool A_KC, bool B_KC>
-static hipError_t launch_small_one(const GemmArgs& a, hipStream_t s) {
-    static std::atomic<uint64_t> attr_done{0};
-    constexpr int lds_bytes = SmShape<MT>::LDS_BYTES;
+__global__ __launch_bounds__(SM_THREADS)
+void tp_small_kernel(const GemmArgs p, const Epilogue e) {
+    small_tile<MT, A_KC, B_KC>(p, e, (int)blockIdx.x);
+}
+
+// dX (NT) and dW (TN) of one backward call in one launch: the two do not depend on each other, neither fills the chip for long, and
+// a launch of its own costs each about as much as its work (300 x 136, K = 2 x 328 and 136 x 328, K = 2 x 300: 5.2 + 5.2 us).
+template <int MT>
+__global__ __launch_bounds__(SM_THREADS)
+void tp_small_pair_kernel(const GemmArgs px, const Epilogue ex, const GemmArgs pw, const Epilogue ew, const int n_first) {
+    if ((int)blockIdx.x < n_first) small_tile<MT, true, true>(px, ex, (int)blockIdx.x);
+    else                           small_tile<2, false, false>(pw, ew, (int)blockIdx.x - n_first);
+}
+
+// the kernel with its LDS limit raised, once per device
+template <class... P>
+static hipError_t launch_with_lds(void (*kernel)(P...), std::atomic<uint64_t>& attr_done, unsigned grid, int lds_bytes, hipStream_t s, P... args) {
     int dev = 0;
     if (hipError_t err = hipGetDevice(&dev); err != hipSuccess) return err;
     const uint64_t bit = 1ull << (dev & 63);
     if (!(attr_done.load(std::memory_order_relaxed) & bit)) {
-        hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(&tp_small_kernel<MT, A_KC, B_KC>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
+        hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
         if (err != hipSuccess) return err;
         attr_done.fetch_or(bit, std::memory_order_relaxed);
     }
-    const Epilogue e{a.out, a.ldo, a.out_f32, a.pre, a.ldp, a.bias, a.gelu, a.dg, a.lddg};
-    return launch_kernel(tp_small_kernel<MT, A_KC, B_KC>, dim3((unsigned)(a.tiles_m * a.tiles_n)), dim3(SM_THREADS), lds_bytes, s, a, e);
+    return launch_kernel(kernel, dim3(grid), dim3(SM_THREADS), lds_bytes, s, args...);
+}
+static Epilogue epilogue_of(const GemmArgs& a) { return Epilogue{a.out, a.ldo, a.out_f32, a.pre, a.ldp, a.bias, a.gelu, a.dg, a.lddg}; }
+
+template <int MT, bool A_KC, bool B_KC>
+static hipError_t launch_small_one(const GemmArgs& a, hipStream_t s) {
+    static std::atomic<uint64_t> attr_done{0};
+    return launch_with_lds(tp_small_kernel<MT, A_KC, B_KC>, attr_done, (unsigned)(a.tiles_m * a.tiles_n), SmShape<MT>::LDS_BYTES, s, GemmArgs(a), epilogue_of(a));
+}
+template <int MT>
+static hipError_t launch_pair_one(const GemmArgs& x, const GemmArgs& w, hipStream_t s) {
+    static std::atomic<uint64_t> attr_done{0};
+    constexpr int lds_bytes = SmShape<MT>::LDS_BYTES > SmShape<2>::LDS_BYTES ? SmShape<MT>::LDS_BYTES : SmShape<2>::LDS_BYTES;
+    const int n_first = x.tiles_m * x.tiles_n;
+    return launch_with_lds(tp_small_pair_kernel<MT>, attr_done, (unsigned)(n_first + w.tiles_m * w.tiles_n), lds_bytes, s, GemmArgs(x), epilogue_of(x),
+                           GemmArgs(w), epilogue_of(w), int(n_first));
+}
+hipError_t launch_small_pair(int tile_x, const GemmArgs& x, int tile_w, const GemmArgs& w, hipStream_t s) {
+    if (x.split_k != 1 || w.split_k != 1 || tile_w != TILE_32x32_SMALL) return hipErrorInvalidValue;
+    return tile_x == TILE_16x32_SMALL ? launch_pair_one<1>(x, w, s) : launch_pair_one<2>(x, w, s);
 }
 
 hipError_t launch_small(int form, int tile_id, const GemmArgs& a, hipStream_t s) {

@@ -923,3 +923,37 @@ def test_stream_kernel_with_few_k_tiles_a_tile(form, k_tiles):
     ref = (a.double().T if form == "TN" else a.double()) @ (b.double().T if form == "NT" else b.double())
     # fp32 sums of k products of values below 6: k roundings of at most 2^-24 of the largest partial sum, 36 k
     assert float((out.double() - ref).abs().max()) <= k * 2.0 ** -24 * 36 * k
+
+
+@pytest.mark.parametrize("m,h,f", [(8, 64, 40), (16, 264, 72), (40, 136, 328), (300, 136, 328)])
+@pytest.mark.parametrize("overlap", ["none", "dW over W", "dX over X"])
+def test_both_backward_products_in_one_launch(m, h, f, overlap):
+    """dX and dW of one call are those of two calls, bit for bit; also where one is written over what the other reads, which the
+    order of the two (dX, then dW) makes well defined for dW over W and for dX over an X that dW reads as dX left it."""
+    gen = torch.Generator(device="cuda").manual_seed(m)
+    rand = lambda r, c: torch.randn((r, c), generator=gen, device="cuda", dtype=torch.bfloat16)
+    grid, dims = T.Grid(T.MODE_2D), (m, h, f)
+    da, x = rand(m, f), rand(m, h)
+    room = torch.zeros(h * f * 2, dtype=torch.bfloat16, device="cuda")
+    w = room[:h * f].view(h, f)
+    w.copy_(rand(h, f))
+    ws = torch.empty(max(T.tp_linear_workspace_size(grid, dims, p) for p in (T.PASS_DX, T.PASS_DW)) or 16, dtype=torch.uint8, device="cuda")
+    keep_w, keep_x = w.clone(), x.clone()
+
+    def buffers():
+        w.copy_(keep_w)
+        x.copy_(keep_x)
+        dw = room.view(torch.float32).view(h, f) if overlap == "dW over W" else torch.empty((h, f), device="cuda")
+        dx = x if overlap == "dX over X" else torch.empty((m, h), dtype=torch.bfloat16, device="cuda")
+        return dx, dw
+
+    dx, dw = buffers()
+    T.tp_linear_bwd(grid, dims, 1, 0, da_row_blocks=[da], w_blocks_dx=[w], dx=dx, workspace=ws)
+    T.tp_linear_bwd(grid, dims, 0, 1, x_blocks_dw=[x], da_col_blocks=[da], dw=dw, workspace=ws)
+    two = dx.clone(), dw.clone()
+    dx, dw = buffers()
+    T.tp_linear_bwd(grid, dims, 1, 1, da_row_blocks=[da], w_blocks_dx=[w], x_blocks_dw=[x], da_col_blocks=[da], dx=dx, dw=dw, workspace=ws)
+    assert torch.equal(dx, two[0]) and torch.equal(dw, two[1])
+    if overlap == "none":
+        check(host64(dx), host64(da) @ host64(keep_w).T, "bf16", f"dX {m} x {h} x {f}")
+        check(host64(dw), host64(x).T @ host64(da), "f32", f"dW {m} x {h} x {f}")
