@@ -287,6 +287,19 @@ double small_cost(int form, int bm, int64_t wgs, int64_t T, double bytes) {
     return c.launch + (double)((wgs + kCUs - 1) / kCUs) * c.round + (double)T * (c.chunk + c.crowd * (double)wgs / kCUs);
 }
 
+// The same kernel for a forward of at most 32 rows, with tiles of 64 columns (whole cache lines of weight rows) and K split
+// over z workgroups too where there are few of them: z > 1 writes planes and takes the fix-up launch.  A wave then has one or
+// two chunks, all on their way at once, instead of a chain of them.  Fitted to 16 rows, in us, mean of operands from memory
+// and cached (1900 cycles); from memory, against the better of 32 columns and 128 x 128 tiles: 4096 x 4096 19.9 -> 13.6 (z = 4), 4096 x
+// 1024 18.9 -> 9.7 (8), 8192 x 2048 17.1 -> 13.4 (8), 1024 x 16384 16.0 -> 11.1 (1), 4096 x 8192 21.0 -> 19.5 (2); 3 steps of
+// 392 x 5568 stay with 32 columns (7.9 against 9.1), 4 of 6144 x 6144 with 128 x 128 tiles (58 / 71).
+// 32 rows leave a wave one slot, so its chunks do not overlap.
+double wide_cost(int bm, int64_t strips, int z, int64_t T) {
+    const int64_t chunks = (T + 8 * z - 1) / (8 * z), rounds = (strips * z + kCUs - 1) / kCUs;
+    const double wgs = (double)(strips * z) / (double)rounds, chunk = bm == 16 ? 1.95 : 2.2;
+    return 1900.0 * (2.8 + (z > 1 ? 2.8 : 0.0) + (double)(rounds * chunks) * (chunk + 1.2 * std::max(0.0, wgs / (kCUs / 2) - 1.0)));
+}
+
 // Bytes of workspace a call needs, and the plan the eight-wave kernel runs: its costs are those the query is made of.
 Plan query_plan(const Opts& o, int64_t m, int64_t n, int64_t k, int n_steps, int groups = 1) {
     Plan p = plan_by(kQueryCosts, o, m, n, k, n_steps, groups, SIZE_MAX);
@@ -303,12 +316,31 @@ Plan make_plan(const Opts& o, int form, int64_t m, int64_t n, int64_t k, int n_s
     Plan p = plan_by(kRunCosts, o, m, n, k, n_steps, groups, need, &cost);
     if (!o.tile && !o.split) {
         const int bm = m <= 16 && form != FORM_TN ? 16 : 32;
-        const int64_t tm = (m + bm - 1) / bm, tn = (n + 31) / 32;
+        const int64_t tm = (m + bm - 1) / bm, T = (int64_t)n_steps * ((k + 63) / 64), wgs = tm * ((n + 31) / 32) * groups;
+        const int group_m = o.group > 0 ? o.group : 4;
         // (the products of a grouped launch share one operand)
         const double bytes = 2.0 * (double)k * (form == FORM_NT ? (double)m * n_steps + (double)n * n_steps * groups
                                                                 : (double)m * n_steps * groups + (double)n * n_steps);
-        if (small_cost(form, bm, tm * tn * groups, (int64_t)n_steps * ((k + 63) / 64), bytes) < cost)
-            p = Plan{bm == 16 ? TILE_16x32_SMALL : TILE_32x32_SMALL, bm, 32, (int)tm, (int)tn, 1, o.group > 0 ? o.group : 4, groups, 0, 0, 0, 0, 0, 0};
+        const double small = small_cost(form, bm, wgs, T, bytes);
+        if (small < cost) {
+            // dX with half the chip's workgroups or fewer and a long K: tiles of 16 columns, twice the workgroups (16 x 4096, K = 4096:
+            // 12.4 -> 10.1 us; 16 x 2048, K = 8192 18.2 -> 13.3; 128 x 512, K = 2 x 2048 8.6 -> 7.9; short of that it loses: 128 x 1000, K = 1000
+            // 5.1 / 5.4; 300 x 136, K = 2 x 328 4.9 / 5.1)
+            const int bn = form == FORM_NT && wgs <= kCUs / 2 && T >= 32 ? 16 : 32;
+            p = Plan{bn == 32 ? (bm == 16 ? TILE_16x32_SMALL : TILE_32x32_SMALL) : (bm == 16 ? TILE_16x16_SMALL : TILE_32x16_SMALL), bm, bn,
+                     (int)tm, (int)((n + bn - 1) / bn), 1, group_m, groups, 0, 0, 0, 0, 0, 0};
+            cost = small;
+        }
+        if (form == FORM_NN && m <= 32 && groups == 1) {
+            const int64_t strips = (n + 63) / 64;
+            for (int z = 1; z <= 8 && z * strips <= (z > 1 ? kCUs : 4 * kCUs); ++z) {
+                Plan c{bm == 16 ? TILE_16x64_SMALL : TILE_32x64_SMALL, bm, 64, 1, (int)strips, z, group_m, 1, 0, 0, 0, 0, 0, 0};
+                const double wide = wide_cost(bm, strips, z, T);
+                if (ws_bytes_for(c, m, n) > need || wide >= cost) continue;
+                p = c;
+                cost = wide;
+            }
+        }
     }
     p.need = need;
     return p;
@@ -438,7 +470,7 @@ bool writes_into(const GemmArgs& w, int form, const GemmArgs& r) {
 // The two products of a backward call, dX first.  Where both run on the workgroup-split kernel they share one launch, unless one
 // writes what the other reads: then the order is what the caller counts on.
 int run_backward(const Opts& o, const Product& px, const Product& pw, void* workspace, hipStream_t stream) {
-    auto small = [](const Product& p) { return p.active && (p.plan.tile_id == TILE_32x32_SMALL || p.plan.tile_id == TILE_16x32_SMALL); };
+    auto small = [](const Product& p) { return p.active && p.plan.tile_id >= TILE_32x32_SMALL; };
     if (small(px) && small(pw) && !writes_into(px.args, pw.form, pw.args) && !writes_into(pw.args, px.form, px.args))
         return launch_gemm_pair(px.plan.tile_id, px.args, pw.plan.tile_id, pw.args, stream) == hipSuccess ? TP_OK : TP_ERR_HIP;
     if (px.active) if (int e = run_product(o, px, workspace, stream)) return e;

@@ -58,7 +58,7 @@ struct ReduceArgs {
 enum TileId { TILE_256x256 = 1, TILE_128x256 = 2, TILE_256x128 = 3, TILE_128x128 = 4,
               TILE_256x256_W4 = 5,     // 256 x 256 by the four-wave stream kernel (tp_gemm4.hip)
               TILE_128x256_MS = 6, TILE_256x128_MS = 7, TILE_128x128_MS = 8,   // four waves, a ring of LDS stages (tp_gemm_ms.hip)
-              TILE_32x32_SMALL = 9, TILE_16x32_SMALL = 10 };   // K split over the workgroup's waves (tp_small.hip)
+              TILE_32x32_SMALL = 9, TILE_16x32_SMALL = 10, TILE_32x16_SMALL = 11, TILE_16x16_SMALL = 12, TILE_16x64_SMALL = 13, TILE_32x64_SMALL = 14 };   // K split over the workgroup's waves (tp_small.hip)
 void tile_shape(int tile_id, int* bm, int* bn);
 
 hipError_t launch_gemm(int form, int tile_id, const GemmArgs& args, hipStream_t stream);

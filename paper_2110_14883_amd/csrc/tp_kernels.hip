@@ -582,7 +582,7 @@ hipError_t launch_gemm(int form, int tile_id, const GemmArgs& args, hipStream_t 
         case TILE_128x128: return launch_tile<128, 128>(form, a, s);
         case TILE_256x256_W4: return launch_gemm4(form, a, s);
         case TILE_128x256_MS: case TILE_256x128_MS: case TILE_128x128_MS: return launch_gemm_ms(form, tile_id, a, s);
-        case TILE_32x32_SMALL: case TILE_16x32_SMALL: return launch_small(form, tile_id, a, s);
+        case TILE_32x32_SMALL: case TILE_16x32_SMALL: case TILE_32x16_SMALL: case TILE_16x16_SMALL: case TILE_16x64_SMALL: case TILE_32x64_SMALL: return launch_small(form, tile_id, a, s);
         default: return hipErrorInvalidValue;
     }
 }

@@ -957,3 +957,12 @@ def test_both_backward_products_in_one_launch(m, h, f, overlap):
     if overlap == "none":
         check(host64(dx), host64(da) @ host64(keep_w).T, "bf16", f"dX {m} x {h} x {f}")
         check(host64(dw), host64(x).T @ host64(da), "f32", f"dW {m} x {h} x {f}")
+
+
+@pytest.mark.parametrize("m", [1, 16, 17, 32])
+@pytest.mark.parametrize("k,n", [(2056, 264), (4096, 72), (136, 9224), (1000, 4104), (6144, 1032)])
+def test_few_rows_and_long_contractions(m, k, n):
+    """The forward of at most 32 rows on tiles of 64 columns, K over one workgroup or several (fix-up), and dX on tiles of 16: one
+    chunk a wave and several, ragged strips, two steps, every kind of output."""
+    for steps, y, dx in ((1, "f32", "bf16"), (2, "bf16", "f32")):
+        run_share(T.Grid(T.MODE_2D, q=steps), (steps * m, steps * k, steps * n), y_dtype=y, dx_dtype=dx, use_own_slot=False, label=f"{m}x{k}x{n} steps {steps}")
