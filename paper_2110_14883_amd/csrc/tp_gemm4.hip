@@ -41,6 +41,7 @@ __global__ __launch_bounds__(W4_THREADS) __attribute__((amdgpu_waves_per_eu(1, 1
 void tp_gemm4_kernel(const GemmArgs p) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
     constexpr int TM = 4, TN = 4;                  // 32 x 32 MFMA tiles per wave along M and N
+    preload(p);
     const int t = threadIdx.x;
     const int l = t & 63;
     const int w = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -98,10 +99,10 @@ void tp_gemm4_kernel(const GemmArgs p) {
             else                 { g = tm / p.group_tiles; tm -= g * p.group_tiles; }
         }
         c.m0 = uni(tm * W4_BM); c.n0 = uni(tn * W4_BN); c.z = uni(z); c.g = uni(g);
-        const int s = z / KT;
-        c.kt = uni(z - s * KT);
-        c.step = uni(s + g);                      // a grouped launch has one step per group: operand slot = group
-        c.left = uni((T - z + Z - 1) / Z);        // K tiles z, z + Z, ... of the n_steps x KT sequence
+        c.kt = uni(z);
+        c.step = uni(g);                          // a grouped launch has one step per group: operand slot = group
+        while (c.kt >= KT) { c.kt -= KT; ++c.step; }      // (z < 8)
+        c.left = uni(Z == 1 ? T : (T - z + Z - 1) / Z);        // K tiles z, z + Z, ... of the n_steps x KT sequence
     };
     Cursor f, c;                                  // fetch cursor (two K tiles ahead) and compute cursor
 

@@ -34,6 +34,7 @@ __global__ __launch_bounds__(MS_THREADS) __attribute__((amdgpu_waves_per_eu(1, 1
 void tp_gemm_ms_kernel(const GemmArgs p) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
     using Sh = MsShape<BM, BN>;
+    preload(p);
     constexpr int NS = Sh::NS, STAGE = Sh::STAGE, A_BYTES = Sh::A_BYTES;
     constexpr int WM = BM / 2, WN = BN / 2, TM = WM / 32, TN = WN / 32;      // a wave's share of the C tile
     constexpr int LA = BM / 32, LB = BN / 32;                                // loads per wave and K tile
@@ -81,9 +82,10 @@ void tp_gemm_ms_kernel(const GemmArgs p) {
     // Load n of wave w fills bytes 4096 n + 1024 w .. + 1023 of the operand's part of the stage:
     //   contraction-contiguous: rows 32 n + 8 w + l / 8, position l % 8 (the chunk differs between even and odd
     //     n by chunk ^ 2);  otherwise: k row (4096 n + 1024 w) / pitch + 16 l / pitch, position l % (pitch / 16).
-    const int total_k = (p.n_steps * KT - z + Z - 1) / Z;     // K tiles of this workgroup (split_k <= their number: >= 1)
+    const int total_k = Z == 1 ? p.n_steps * KT : (p.n_steps * KT - z + Z - 1) / Z;     // K tiles of this workgroup (split_k <= their number: >= 1)
     int f_left = uni(total_k), f_step, f_kt;
-    { const int s = z / KT; f_kt = uni(z - s * KT); f_step = uni(s + g); }
+    f_kt = uni(z); f_step = uni(g);
+    while (f_kt >= KT) { f_kt -= KT; ++f_step; }               // (z < 8)
     u32x4_t rw_a, rw_b;
     uint32_t dl_a[2], dl_b[2], dv_a[2], dv_b[2];
     int a_step, b_step, a_kmul, b_kmul;

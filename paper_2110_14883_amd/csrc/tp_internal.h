@@ -16,6 +16,16 @@ enum GemmForm {
     FORM_TN = 2    // dW      : A = X  [k][m],       B = dA [k][n]
 };
 
+// Division by a number the host knows, for dividends below 2^31: magic = floor(2^(31 + shift) / d) + 1 with 2^(shift - 1) < d <= 2^shift.
+// (On the device a 32-bit division is some 30 dependent instructions, a 64-bit one 150.)
+struct Divisor {
+    uint32_t d, magic, shift;
+};
+inline Divisor divisor(uint32_t d) {          // 1 <= d < 2^31
+    const uint32_t shift = d > 1 ? 32 - (uint32_t)__builtin_clz(d - 1) : 0;
+    return Divisor{d, (uint32_t)((((uint64_t)1 << (31 + shift)) / d) + 1), shift};
+}
+
 struct GemmArgs {
     const void* a[TP_MAX_STEPS];
     const void* b[TP_MAX_STEPS];
@@ -26,6 +36,7 @@ struct GemmArgs {
     int32_t tiles_m, tiles_n;
     int32_t split_k;             // >= 1; > 1 writes fp32 partials to ws
     int32_t group_m;             // tile-order group height (tile rows)
+    Divisor by_tiles, by_group, by_height, by_last;   // of the tile order (tile_of_id): tiles_m tiles_n; group_m tiles_n; group_m; height of the last group
     // epilogue (used when split_k == 1)
     void* out;   int64_t ldo;   int32_t out_f32;
     void* pre;   int64_t ldp;           // optional bf16 copy of the pre-activation

@@ -315,27 +315,14 @@ __global__ __launch_bounds__(NTHREADS) void tp_gemm_kernel(const GemmArgs p) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// position of a thread in a block of rows x `per_row` pieces: idx / per_row without a division (the 64-bit one is 150
-// instructions a thread).  magic = floor(2^(31 + shift) / per_row) + 1 with 2^(shift - 1) < per_row <= 2^shift is exact for idx < 2^31,
-// which is what one launch covers.
-// ---------------------------------------------------------------------------------------------
-struct RowOf { uint32_t per_row, magic, shift; };
-__device__ __forceinline__ uint32_t row_of(const RowOf d, uint32_t idx, uint32_t& in_row) {
-    const uint32_t r = (uint32_t)(((uint64_t)idx * d.magic) >> (31 + d.shift));
-    in_row = idx - r * d.per_row;
-    return r;
-}
-
-// ---------------------------------------------------------------------------------------------
 // split-K fix-up: sum the fp32 partials in a fixed order, then the same epilogue.  Z: number of planes, all of a
 // thread's loads in flight together.  Bound by memory (the planes), by latency where they are small.
 // ---------------------------------------------------------------------------------------------
 template <int Z>
-__global__ __launch_bounds__(256) void tp_reduce_kernel(const ReduceArgs p, const uint32_t total, const RowOf d) {
+__global__ __launch_bounds__(256) void tp_reduce_kernel(const ReduceArgs p, const uint32_t total, const Divisor d) {
     const uint32_t idx = blockIdx.x * 256u + threadIdx.x;
     if (idx >= total) return;
-    uint32_t n4;
-    const int m = (int)row_of(d, idx, n4), n = (int)n4 * 4;
+    const int m = (int)quotient(d, idx), n = (int)(idx - m * d.d) * 4;
     Epilogue e{p.out, p.ldo, p.out_f32, p.pre, p.ldp, p.bias, p.gelu, p.dg, p.lddg};
     const float* const src = p.ws + (int64_t)m * p.N + n;
     f32x4_t q[Z];
@@ -362,12 +349,11 @@ __device__ __forceinline__ u32x4_t dgelu8(const u32x4_t g, const u32x4_t a) {
 // measured 15 % faster than a persistent grid-stride loop with several loads in flight; the streaming (nontemporal) hint on loads and
 // stores is worth another 9 %: 4096 x 24576 in 92 us, 6.6 TB/s (98 us with a 64-bit division a thread), against 5.9 for a plain bf16 add.
 __global__ __launch_bounds__(256) void tp_dgelu_kernel(const uint16_t* dy, int64_t ld_dy, const uint16_t* pre, int64_t ld_pre, uint16_t* da,
-                                                       int64_t ld_da, const uint32_t total, const RowOf d) {
+                                                       int64_t ld_da, const uint32_t total, const Divisor d) {
     const uint32_t idx = blockIdx.x * 256u + threadIdx.x;
     if (idx >= total) return;
-    uint32_t c8;
-    const int64_t r = row_of(d, idx, c8);
-    const uint32_t c = c8 * 8;
+    const int64_t r = quotient(d, idx);
+    const uint32_t c = (idx - (uint32_t)r * d.d) * 8;
     const u32x4_t g = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(dy + r * ld_dy + c));
     const u32x4_t a = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(pre + r * ld_pre + c));
     __builtin_nontemporal_store(dgelu8(g, a), reinterpret_cast<u32x4_t*>(da + r * ld_da + c));
@@ -378,12 +364,11 @@ __global__ __launch_bounds__(256) void tp_dgelu_kernel(const uint16_t* dy, int64
 // compiled in: between branches the second store waits for the first.
 template <bool GELU, bool PRE, bool F32>
 __global__ __launch_bounds__(256) void tp_bias_act_kernel(const float* c, int64_t ldc, const uint16_t* bias, void* y, int64_t ldy, uint16_t* pre,
-                                                          int64_t ldp, const uint32_t total, const RowOf d) {
+                                                          int64_t ldp, const uint32_t total, const Divisor d) {
     const uint32_t idx = blockIdx.x * 256u + threadIdx.x;
     if (idx >= total) return;
-    uint32_t n4;
-    const int64_t r = row_of(d, idx, n4);
-    const uint32_t n = n4 * 4;
+    const int64_t r = quotient(d, idx);
+    const uint32_t n = (idx - (uint32_t)r * d.d) * 4;
     f32x4_t v = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(c + r * ldc + n));
     if (bias) {
         const u32x2_t b = *reinterpret_cast<const u32x2_t*>(bias + n);
@@ -557,6 +542,11 @@ static hipError_t launch_tile(int form, const GemmArgs& a, hipStream_t s) {
 
 // A plain launch is one group whose output is `out`; false: a grouped one that does not hold together.
 static bool normalise(GemmArgs& a) {
+    if (a.tiles_m < 1 || a.tiles_n < 1 || a.group_m < 1) return false;
+    a.by_tiles = divisor((uint32_t)(a.tiles_m * a.tiles_n));
+    a.by_group = divisor((uint32_t)(a.group_m * a.tiles_n));
+    a.by_height = divisor((uint32_t)a.group_m);
+    a.by_last = divisor((uint32_t)(a.tiles_m % a.group_m ? a.tiles_m % a.group_m : a.group_m));
     if (a.n_groups <= 1) {
         a.n_groups = 1; a.group_along_n = 1; a.group_tiles = a.tiles_n;
         a.outs[0] = a.out; a.ldos[0] = a.ldo;
@@ -587,14 +577,12 @@ hipError_t launch_gemm(int form, int tile_id, const GemmArgs& args, hipStream_t 
     }
 }
 
-// f(first row, rows, threads, RowOf): launches over the rows of a block, at most 2^31 - 1 threads each
+// f(first row, rows, threads, Divisor): launches over the rows of a block, at most 2^31 - 1 threads each
 template <class F>
 static hipError_t over_rows(int64_t rows, int64_t per_row, F&& f) {
     if (rows <= 0 || per_row <= 0) return hipSuccess;
-    RowOf d{(uint32_t)per_row, 0, 0};
-    while (((int64_t)1 << d.shift) < per_row) ++d.shift;
-    d.magic = (uint32_t)((((uint64_t)1 << (31 + d.shift)) / (uint64_t)per_row) + 1);
     if (per_row >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
+    const Divisor d = divisor((uint32_t)per_row);
     const int64_t most = (((int64_t)1 << 31) - 1) / per_row;
     for (int64_t r = 0; r < rows; r += most) {
         const int64_t n = rows - r < most ? rows - r : most;
@@ -606,7 +594,7 @@ static dim3 covering(uint32_t threads) { return dim3((threads + 255u) / 256u); }
 
 template <int Z>
 static hipError_t reduce_planes(const ReduceArgs& a, hipStream_t s) {
-    return over_rows(a.M, a.N >> 2, [&](int64_t r, int64_t n, uint32_t total, RowOf d) {
+    return over_rows(a.M, a.N >> 2, [&](int64_t r, int64_t n, uint32_t total, Divisor d) {
         ReduceArgs p = a;
         p.M = (int32_t)n;
         p.ws += r * a.N;
@@ -631,7 +619,7 @@ hipError_t launch_reduce(const ReduceArgs& a, hipStream_t s) {
 
 hipError_t launch_dgelu(const void* dy, int64_t ld_dy, const void* pre, int64_t ld_pre, void* da, int64_t ld_da,
                         int64_t rows, int64_t cols, hipStream_t s) {
-    return over_rows(rows, cols >> 3, [&](int64_t r, int64_t, uint32_t total, RowOf d) {
+    return over_rows(rows, cols >> 3, [&](int64_t r, int64_t, uint32_t total, Divisor d) {
         return launch_kernel(tp_dgelu_kernel, covering(total), dim3(256), 0, s, static_cast<const uint16_t*>(dy) + r * ld_dy, ld_dy,
                              static_cast<const uint16_t*>(pre) + r * ld_pre, ld_pre, static_cast<uint16_t*>(da) + r * ld_da, ld_da, total, d);
     });
@@ -640,7 +628,7 @@ hipError_t launch_dgelu(const void* dy, int64_t ld_dy, const void* pre, int64_t 
 template <bool GELU, bool PRE, bool F32>
 static hipError_t bias_act(const float* c, int64_t ldc, const void* bias, void* y, int64_t ldy, void* pre, int64_t ldp, int64_t rows,
                            int64_t cols, hipStream_t s) {
-    return over_rows(rows, cols >> 2, [&](int64_t r, int64_t, uint32_t total, RowOf d) {
+    return over_rows(rows, cols >> 2, [&](int64_t r, int64_t, uint32_t total, Divisor d) {
         return launch_kernel(tp_bias_act_kernel<GELU, PRE, F32>, covering(total), dim3(256), 0, s, c + r * ldc, ldc, static_cast<const uint16_t*>(bias),
                              static_cast<void*>(static_cast<char*>(y) + r * ldy * (F32 ? 4 : 2)), ldy,
                              PRE ? static_cast<uint16_t*>(pre) + r * ldp : nullptr, ldp, total, d);

@@ -32,6 +32,8 @@ template <int MT, int NT, bool A_KC, bool B_KC>
 __device__ __forceinline__ void small_tile(const GemmArgs& p, const Epilogue& e, const int id) {
     static_assert((MT == 2 || (MT == 1 && A_KC)) && (B_KC ? NT <= 2 : NT >= 2));
     using Sh = SmShape<MT, NT>;
+    preload(p);
+    asm volatile("" :: "s"(e.out), "s"(e.dg));
     constexpr int BM = Sh::BM, BN = Sh::BN, NS = Sh::NS, A_BYTES = Sh::A_BYTES;
     constexpr int LA = A_BYTES / 1024, LB = Sh::B_BYTES / 1024, LPC = LA + LB;    // loads of a chunk
     extern __shared__ __attribute__((aligned(16))) char lds[];
