@@ -179,7 +179,10 @@ struct Costs { double k_tile[3], c_tile[3], plane, launch, trim; };
 // and a split that spreads it pays (4 products of 678 x 4240 x 168: 46.5 us whole, 28.5 split in five).
 // (The half tiles' K tile fits 1670 to 1870; the upper end, as over many rounds their extra traffic costs clock: dW 14744 x 13568 x 1640
 // 710 us in three rounds of 256 x 128, 660 in two of 256 x 256.)
-constexpr Costs kRunCosts{{2730.0, 1870.0, 1200.0}, {21000.0, 15000.0, 10000.0}, 4.5, 6500.0, 52000.0};
+// (trim: since the outputs stream past the L2 a second launch waits for no write-back, and its line fell from 52000.  Whole / trimmed, us:
+// forward 32896 x 2560, K = 2 x 640 242 / 220; 8448 x 2048, K = 1024 66 / 53; 32863 x 440, K = 600 62 / 54; dX 32802 x 512, K = 1072 56 / 45;
+// dW 720 x 512, K = 33008 48 / 42; where it loses, short tiles: dX 4632 x 4024, K = 208 25.2 / 26.5, 32986 x 440, K = 136 22.6 / 24.1.)
+constexpr Costs kRunCosts{{2730.0, 1870.0, 1200.0}, {21000.0, 15000.0, 10000.0}, 4.5, 6500.0, 18000.0};
 // What the workspace query has always been computed from.  Callers size and keep workspaces by it, so it goes on
 // deciding how many bytes a call needs (and which calls are refused); the plan that runs stays within them.
 constexpr Costs kQueryCosts{{2730.0, 2220.0, 1410.0}, {12000.0, 20000.0, 20000.0}, 8.0, 12000.0, 15000.0};
