@@ -1,4 +1,4 @@
-"""MI355X-native per-rank tensor-parallel linear layer (1D / 2D-SUMMA / 2.5D / 3D): a thin ctypes
+"""MI355X-native per-rank tensor-parallel linear layer (1D / 2D-SUMMA / 2.5D / 3D): a thin
 binding over libtplinear.so.  Importing this package does not load the library; the first call
 does, and fails loudly if it has not been built (python -m paper_2110_14883_amd.build)."""
 from .binding import (  # noqa: F401
