@@ -38,9 +38,9 @@ NSETS = int(os.environ.get("TPL_BENCH_NSETS", "3"))   # buffer sets rotated thro
 # of the headline workload.  (Its dX is planned with K split in two: the launch is the fp32-partials
 # instantiation, followed by the fix-up kernel's 252 MB.)
 MEASURED_TRAFFIC_BYTES = {
-    "tpl::tp_gemm4_kernel<true, false, 2, false>": 2274000000,     # forward NN + bias + GeLU: 1872 MB read, 403 MB written
-    "tpl::tp_gemm4_kernel<false, false, 0, true>": 2959000000,     # dW TN: 2355 MB read, 604 MB written
-    "tpl::tp_gemm4_kernel<true, true, 0, true>": 2134000000,       # dX NT: 1932 MB read, 201 MB written
+    "tpl::tp_gemm4_kernel<true, false, 2, false, true>": 2274000000,     # forward NN + bias + GeLU: 1872 MB read, 403 MB written
+    "tpl::tp_gemm4_kernel<false, false, 0, true, false>": 2959000000,     # dW TN: 2355 MB read, 604 MB written
+    "tpl::tp_gemm4_kernel<true, true, 0, true, false>": 2134000000,       # dX NT: 1932 MB read, 201 MB written
 }
 
 
@@ -48,11 +48,12 @@ def log(*a):
     print(*a, file=sys.stderr, flush=True)
 
 
-def gemm_symbol(form: str, epi: int, f32_out: bool) -> str:
+def gemm_symbol(form: str, epi: int, f32_out: bool, pre: bool = False) -> str:
     """Name of the 256x256 GEMM instantiation a call launches when K is not split (as rocprofv3 prints it, without
-    'void' and the argument list).  form: NN / NT / TN; epi: 0 none, 1 bias, 2 bias+GeLU, 3 *GeLU'."""
+    'void' and the argument list).  form: NN / NT / TN; epi: 0 none, 1 bias, 2 bias+GeLU, 3 *GeLU'; pre: the
+    pre-activation is stored too."""
     kc = {"NN": "true, false", "NT": "true, true", "TN": "false, false"}[form]
-    return f"tpl::tp_gemm4_kernel<{kc}, {epi}, {'true' if f32_out else 'false'}>"
+    return f"tpl::tp_gemm4_kernel<{kc}, {epi}, {'true' if f32_out else 'false'}, {'true' if pre else 'false'}>"
 
 
 # Calls of these workloads whose main kernel the kernel traces under profiles/ show to be another: K split into fp32
@@ -122,7 +123,7 @@ def main() -> int:
                      dW2=empty((fb, H), True), dX=empty((M, H), True), dW1=empty((H, fb), True),
                      ws1=ws_for(g1, d1), ws2=ws_for(g2, d2))
             calls = [
-                ("fc1_fwd NN +bias+GeLU", one, gemm_symbol("NN", 2, False), lambda b=b, o=o: T.tp_linear_fwd(
+                ("fc1_fwd NN +bias+GeLU", one, gemm_symbol("NN", 2, False, True), lambda b=b, o=o: T.tp_linear_fwd(
                     g1, d1, 1, [b["X"]], [b["W1"]], b["b1"], T.EPI_BIAS_GELU, o["Z"], o["A"], o["ws1"])),
                 ("fc2_fwd NN fp32 partial", one, gemm_symbol("NN", 0, True), lambda b=b, o=o: T.tp_linear_fwd(
                     g2, d2, 1, [o["Z"]], [b["W2"]], None, T.EPI_NONE, o["Y"], None, o["ws2"])),
@@ -202,7 +203,7 @@ def main() -> int:
                 ]
                 sets.append(calls)
                 continue
-            calls = [("fwd NN +bias+GeLU", one, gemm_symbol("NN", 2, f32y), lambda b=b, o=o: T.tp_linear_fwd(
+            calls = [("fwd NN +bias+GeLU", one, gemm_symbol("NN", 2, f32y, True), lambda b=b, o=o: T.tp_linear_fwd(
                 grid, dims, sf, b["x"], b["w"], b["bias"], T.EPI_BIAS_GELU, o["y"], o["pre"], o["ws"]))]
             if cfg.backward:
                 o.update(da=empty((m, n)), dx=empty((m, k), cfg.dx_dtype == "f32"), dw=empty((k, n), True))
@@ -235,7 +236,7 @@ def main() -> int:
             o = dict(y=empty((m, n)), pre=empty((m, n)), da=empty((m, n)), ws=torch.empty(wsb, dtype=torch.uint8, device="cuda"),
                      dxp=[empty((m, k), True) for _ in range(q)], dwp=[empty((k, n), True) for _ in range(q)])
             sets.append([
-                ("fwd NN +bias+GeLU", one, gemm_symbol("NN", 2, False), lambda b=b, o=o: T.tp_linear_fwd(
+                ("fwd NN +bias+GeLU", one, gemm_symbol("NN", 2, False, True), lambda b=b, o=o: T.tp_linear_fwd(
                     grid, dims, sf, b["x"], b["w"], b["bias"], T.EPI_BIAS_GELU, o["y"], o["pre"], o["ws"])),
                 ("dA = dY*GeLU'(A)", 0.0, "tpl::tp_dgelu_kernel", lambda b=b, o=o: T.tp_dgelu(b["g"], o["pre"], o["da"]), 6.0 * m * n),
                 (f"dX partials NT x{q}", one, gemm_symbol("NT", 0, True), lambda b=b, o=o: T.tp_linear_bwd_partials(

@@ -36,7 +36,9 @@ constexpr int W4_EPI_BYTES_PER_WAVE = 8192;                  // 32 rows x 256 by
 
 }  // namespace
 
-template <bool A_KC, bool B_KC, int EPI, bool F32_OUT>
+// PRE: the pre-activation is stored too.  (Compiled in: with both ways through the epilogue in one kernel the one without it took 143 us
+// for 16384 x 1024, K = 4096 with GeLU, alone 134.5.)
+template <bool A_KC, bool B_KC, int EPI, bool F32_OUT, bool PRE>
 __global__ __launch_bounds__(W4_THREADS) __attribute__((amdgpu_waves_per_eu(1, 1)))
 void tp_gemm4_kernel(const GemmArgs p) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
@@ -224,21 +226,25 @@ void tp_gemm4_kernel(const GemmArgs p) {
         else if constexpr (n < e3) read_frag(BT{}, ks_, std::integral_constant<int, 1 + (n - e2) / RB>{}, std::integral_constant<int, (n - e2) % RB>{});
         else                       read_frag(AT{}, ks_, std::integral_constant<int, 1 + (n - e3) / RA>{}, std::integral_constant<int, (n - e3) % RA>{});
     };
-    // The accumulators start from the bias: nothing is left to add in the epilogue, which reads them twice where the
-    // pre-activation is kept too.  The bias of the next C tile is asked for before the epilogue of this one.  (With the
-    // shorter GeLU: 32896 x 2560, K = 2 x 640, Y and pre-activation: 276 -> 250 us; 4096 x 24576, K = 6144: 1022 -> 953.)
+    // The bias is added to the finished sums, in the epilogue: a sum that starts from it is rounded at its size with every 16 k (bias 8 to
+    // 15.5, products of 1e-5, K = 4096: off by 3.3e-5, now by 4.8e-7, the one rounding).  A lane keeps one word of it through the K loop.  The word of the next C tile
+    // is asked for before the epilogue of this one and named behind its last stores, so that the wait for it lies there, with those
+    // stores still under way: at its use the loads of the next K tiles, which the compiler does not see, would be waited for too.
     constexpr bool USE_BIAS = EPI == EPI_BIAS || EPI == EPI_BIAS_GELU;
-    BiasBlock<TN> bias;
-    auto init_acc = [&]() __attribute__((always_inline)) {
+    uint32_t own_bias = 0, next_bias = 0;
+    auto take_bias = [&]() __attribute__((always_inline)) {
+        if constexpr (USE_BIAS) {
+            asm volatile("" : "+v"(next_bias));
+            own_bias = next_bias;
+        }
+    };
+    auto zero_acc = [&]() __attribute__((always_inline)) {
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
+        for (int i = 0; i < TM; ++i)
 #pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                float b = 0.0f;
-                if constexpr (USE_BIAS) b = bias_of(bias, j, e);
+            for (int j = 0; j < TN; ++j)
 #pragma unroll
-                for (int i = 0; i < TM; ++i) acc[i][j][e] = b;
-            }
+                for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
     };
 
     // ------------------------------------------------------------------ one K tile: 64 MFMA slots
@@ -308,7 +314,7 @@ void tp_gemm4_kernel(const GemmArgs p) {
     open_operand(std::true_type{});
     open_operand(std::false_type{});
     prep_tile();
-    if constexpr (USE_BIAS) load_bias(bias, p, c.n0 + wn * 128);
+    if constexpr (USE_BIAS) next_bias = bias_word(p, c.n0 + wn * 128);
     // K tiles 0 and 1
     auto load_both = [&](uint32_t a, uint32_t b) __attribute__((always_inline)) {
         static_for<8>([&](auto n_) __attribute__((always_inline)) { dtl1(OpA{}, n_, s_wbase + W4_A_BASE + a); });
@@ -322,18 +328,22 @@ void tp_gemm4_kernel(const GemmArgs p) {
     prep_tile();
     load_both(W4_STAGE, W4_STAGE);
     wait_vm<16>();
+    take_bias();
     barrier();
     static_for<NR>([&](auto n_) __attribute__((always_inline)) { read_n(n_, std::integral_constant<int, 0>{}); });
 
     while (true) {
-        init_acc();
+        zero_acc();
         for (int n = c.left; n > 0; --n) k_tile();
         const Cursor done = c;
         start(c, c.v + grid);
-        if constexpr (USE_BIAS) { if (c.left != 0) load_bias(bias, p, c.n0 + wn * 128); }
+        if constexpr (USE_BIAS) { if (c.left != 0) next_bias = bias_word(p, c.n0 + wn * 128); }
         // A's stage of the last K tile is free until the next body's loads: the wave's patch
         char* const eps = lds + (fill_a - s_wbase) + w * W4_EPI_BYTES_PER_WAVE;
-        store_c_block<TM, TN, EPI, F32_OUT, true>(p, acc, done.m0 + wm * 128, done.n0 + wn * 128, done.z, done.g, eps);
+        BiasBlock<TN> bias;
+        if constexpr (USE_BIAS) spread_bias(bias, own_bias, eps);
+        store_c_block<TM, TN, EPI, F32_OUT, true, USE_BIAS>(p, acc, done.m0 + wm * 128, done.n0 + wn * 128, done.z, done.g, bias, eps,
+                                                            std::bool_constant<PRE>{}, take_bias);
         if (c.left == 0) break;
         barrier();                                    // every wave is done with its patch
     }
@@ -342,21 +352,29 @@ void tp_gemm4_kernel(const GemmArgs p) {
 // ---------------------------------------------------------------------------------------------
 // host launcher
 // ---------------------------------------------------------------------------------------------
-template <bool A_KC, bool B_KC, int EPI, bool F32_OUT>
+template <bool A_KC, bool B_KC, int EPI, bool F32_OUT, bool PRE = false>
 static hipError_t launch4_one(const GemmArgs& a, hipStream_t stream) {
     static std::atomic<uint64_t> attr_done{0};
     int dev = 0;
     if (hipError_t e = hipGetDevice(&dev); e != hipSuccess) return e;
     const uint64_t bit = 1ull << (dev & 63);
     if (!(attr_done.load(std::memory_order_relaxed) & bit)) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&tp_gemm4_kernel<A_KC, B_KC, EPI, F32_OUT>),
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&tp_gemm4_kernel<A_KC, B_KC, EPI, F32_OUT, PRE>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, W4_LDS_BYTES);
         if (e != hipSuccess) return e;
         attr_done.fetch_or(bit, std::memory_order_relaxed);
     }
     const int total = a.tiles_m * a.tiles_n * a.split_k;
     const unsigned grid = (unsigned)(total < a.max_workgroups ? total : a.max_workgroups);
-    return launch_kernel(tp_gemm4_kernel<A_KC, B_KC, EPI, F32_OUT>, dim3(grid), dim3(W4_THREADS), W4_LDS_BYTES, stream, a);
+    return launch_kernel(tp_gemm4_kernel<A_KC, B_KC, EPI, F32_OUT, PRE>, dim3(grid), dim3(W4_THREADS), W4_LDS_BYTES, stream, a);
+}
+
+// (the pre-activation of a split product is the fix-up's to store)
+template <int EPI>
+static hipError_t launch4_nn(const GemmArgs& a, bool f32, hipStream_t s) {
+    if (a.pre && a.split_k == 1)
+        return f32 ? launch4_one<true, false, EPI, true, true>(a, s) : launch4_one<true, false, EPI, false, true>(a, s);
+    return f32 ? launch4_one<true, false, EPI, true>(a, s) : launch4_one<true, false, EPI, false>(a, s);
 }
 
 hipError_t launch_gemm4(int form, const GemmArgs& a, hipStream_t s) {
@@ -364,9 +382,9 @@ hipError_t launch_gemm4(int form, const GemmArgs& a, hipStream_t s) {
     const bool f32 = a.split_k > 1 || a.out_f32;
     switch (form) {
         case FORM_NN:
-            if (epi == EPI_BIAS_GELU) return f32 ? launch4_one<true, false, EPI_BIAS_GELU, true>(a, s) : launch4_one<true, false, EPI_BIAS_GELU, false>(a, s);
-            if (epi == EPI_BIAS)      return f32 ? launch4_one<true, false, EPI_BIAS, true>(a, s) : launch4_one<true, false, EPI_BIAS, false>(a, s);
-            if (epi == EPI_NONE)      return f32 ? launch4_one<true, false, EPI_NONE, true>(a, s) : launch4_one<true, false, EPI_NONE, false>(a, s);
+            if (epi == EPI_BIAS_GELU) return launch4_nn<EPI_BIAS_GELU>(a, f32, s);
+            if (epi == EPI_BIAS)      return launch4_nn<EPI_BIAS>(a, f32, s);
+            if (epi == EPI_NONE)      return launch4_nn<EPI_NONE>(a, f32, s);
             return hipErrorInvalidValue;
         case FORM_NT:
             if (epi == EPI_MUL_DGELU) return f32 ? launch4_one<true, true, EPI_MUL_DGELU, true>(a, s) : launch4_one<true, true, EPI_MUL_DGELU, false>(a, s);

@@ -76,7 +76,21 @@ __device__ __forceinline__ float bias_of(const BiasBlock<TN>& b, int j, int e) {
     return e & 1 ? bf16_hi(w) : bf16_lo(w);
 }
 
-// Epilogue of one wave's block of C: 32 TM rows x 32 TN columns from (m_sub, n_sub).  The bias is in the accumulators already.
+// The same through the wave's LDS patch, from one word a lane: columns 2 lane and 2 lane + 1 of the 128 (bias_word()).
+__device__ __forceinline__ uint32_t bias_word(const GemmArgs& p, const int n_sub) {
+    return __builtin_amdgcn_raw_buffer_load_b32(make_rsrc(uni_ptr(p.bias), (int64_t)p.N * 2), (n_sub + 2 * (int)(threadIdx.x & 63)) * 2, 0, 0);
+}
+__device__ __forceinline__ void spread_bias(BiasBlock<4>& b, const uint32_t word, char* const eps) {
+    const int l = threadIdx.x & 63;
+    *reinterpret_cast<uint32_t*>(eps + 4 * l) = word;
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) b.v[j][g] = *reinterpret_cast<const u32x2_t*>(eps + (32 * j + 8 * g + 4 * (l >> 5)) * 2);
+}
+
+// Epilogue of one wave's block of C: 32 TM rows x 32 TN columns from (m_sub, n_sub).  ADD_BIAS: `bias` goes on top of the finished
+// sum (else it is there already, or there is none): one rounding, as in every other kernel here.
 // acc[i][j][e]: row m = 32 i + lane%32, columns n = 32 j + 8 (e/4) + 4 (lane/32) + e%4.
 // No branch depends on a lane: every global access goes through a buffer descriptor that starts at
 // the first row of the block and ends with the last row of the matrix, so rows below a ragged edge are
@@ -88,14 +102,17 @@ __device__ __forceinline__ float bias_of(const BiasBlock<TN>& b, int j, int e) {
 // 905 us; 32896 x 2560 bf16 twice, K = 2 x 640: 287 -> 272; 8192 x 1024 bf16, K = 2 x 1024: 43 -> 40).  The planes are read by the fix-up
 // at once, from wherever they still are: with the hint 520 x 2056 in three planes takes 23.2 us against 21.8.
 constexpr int ST_PLAIN = 0, ST_STREAM = 2;        // cache policy bits of a buffer store
-template <int TM, int TN, int EPI, bool F32_OUT, bool ACC_HALF>
+// keep: whether the pre-activation is stored too, a bool or (one way through, no branch) an integral_constant.  last(): called behind the
+// last stores.
+template <int TM, int TN, int EPI, bool F32_OUT, bool ACC_HALF, bool ADD_BIAS, class Keep, class Last>
 __device__ __forceinline__ void store_c_block(const GemmArgs& p, f32x16_t (&acc)[TM][TN], const int m_sub, const int n_sub,
-                                              const int z, const int g_out, char* const eps) {
+                                              const int z, const int g_out, const BiasBlock<TN>& bias, char* const eps, Keep keep, Last last) {
     const int l = threadIdx.x & 63, r = l & 31, ch = l >> 5;
-    const bool partial = p.split_k > 1;          // split K: raw fp32 partials, the fix-up kernel runs the epilogue
+    const bool partial = !ADD_BIAS && !std::is_same_v<Keep, std::true_type> && p.split_k > 1;    // split K: raw fp32 partials, the fix-up kernel runs the epilogue
     constexpr bool use_gelu = EPI == EPI_BIAS_GELU;
     constexpr bool use_dg = EPI == EPI_MUL_DGELU;
-    const bool use_pre = !use_dg && p.pre != nullptr;
+    const bool use_pre = !use_dg && keep;
+    constexpr bool one_pass = !F32_OUT && std::is_same_v<Keep, std::true_type>;
     const int rows_left = p.M - m_sub;
     // rows m_sub .. M - 1 of a matrix with leading dimension ld (elements of es bytes), N columns
     auto block_rsrc = [&](const void* base, int64_t ld, int es) __attribute__((always_inline)) {
@@ -118,6 +135,19 @@ __device__ __forceinline__ void store_c_block(const GemmArgs& p, f32x16_t (&acc)
             else                    v[e] = acc[i][j][4 * g + e];
         }
     };
+    auto preact4 = [&](int i, int j, int g, float (&v)[4]) __attribute__((always_inline)) {
+        raw4(i, j, g, v);
+        if constexpr (ADD_BIAS) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                uint32_t w = bias.v[j][g][h];
+                // (with fp32 outputs unpacked where it is used: the unpacked block is another 64 registers)
+                if constexpr (F32_OUT) asm volatile("" : "+v"(w));
+                v[2 * h] += bf16_lo(w);
+                v[2 * h + 1] += bf16_hi(w);
+            }
+        }
+    };
     u32x2_t dg_v[TN][4];                         // (asked for one slab ahead the pass is 2 % slower)
     auto load_dg = [&](int i) __attribute__((always_inline)) {
         if constexpr (use_dg) {
@@ -129,7 +159,7 @@ __device__ __forceinline__ void store_c_block(const GemmArgs& p, f32x16_t (&acc)
         }
     };
     auto final4 = [&](int i, int j, int g, float (&v)[4]) __attribute__((always_inline)) {
-        raw4(i, j, g, v);
+        preact4(i, j, g, v);
         if constexpr (use_gelu) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) v[e] = gelu_f(v[e]);
@@ -146,24 +176,57 @@ __device__ __forceinline__ void store_c_block(const GemmArgs& p, f32x16_t (&acc)
     constexpr int CPR = 4 * TN, RPI = 64 / CPR;        // 16-byte chunks of a row; rows a wave instruction covers
     static_assert(TN == 2 || TN == 4);
     auto swz = [](int row) __attribute__((always_inline)) { return TN == 4 ? row & 15 : (row >> 1) & 7; };
-    auto slab_bf16 = [&](int i, auto value4, __amdgpu_buffer_rsrc_t rs, int ld) __attribute__((always_inline)) {
+    auto lane_bf16 = [&](int ld) __attribute__((always_inline)) {
+        return (n_sub + 8 * (l % CPR)) < p.N ? (uint32_t)(((l / CPR) * ld + n_sub + 8 * (l % CPR)) * 2) : OOB_OFFSET;
+    };
+    auto put_bf16 = [&](int j, int g, const u32x2_t v) __attribute__((always_inline)) {
+        *reinterpret_cast<u32x2_t*>(eps + r * (16 * CPR) + (((4 * j + g) ^ swz(r)) << 4) + 8 * ch) = v;
+    };
+    auto store_bf16 = [&](int i, __amdgpu_buffer_rsrc_t rs, int ld, uint32_t lane) __attribute__((always_inline)) {
         const int cc = l % CPR;
-        const uint32_t lane = (n_sub + 8 * cc) < p.N ? (uint32_t)(((l / CPR) * ld + n_sub + 8 * cc) * 2) : OOB_OFFSET;
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                float x[4];
-                value4(i, j, g, x);
-                const u32x2_t v = {pack_bf16(x[0], x[1]), pack_bf16(x[2], x[3])};
-                *reinterpret_cast<u32x2_t*>(eps + r * (16 * CPR) + (((4 * j + g) ^ swz(r)) << 4) + 8 * ch) = v;
-            }
 #pragma unroll
         for (int it = 0; it < 32 / RPI; ++it) {
             const int rr = it * RPI + l / CPR;
             const u32x4_t v = *reinterpret_cast<const u32x4_t*>(eps + rr * (16 * CPR) + ((cc ^ swz(rr)) << 4));
             __builtin_amdgcn_raw_buffer_store_b128(v, rs, (int)(lane + (uint32_t)((32 * i + RPI * it) * ld * 2)), 0, ST_STREAM);
         }
+    };
+    auto slab_bf16 = [&](int i, auto value4, __amdgpu_buffer_rsrc_t rs, int ld) __attribute__((always_inline)) {
+        const uint32_t lane = lane_bf16(ld);
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                float x[4];
+                value4(i, j, g, x);
+                put_bf16(j, g, u32x2_t{pack_bf16(x[0], x[1]), pack_bf16(x[2], x[3])});
+            }
+        store_bf16(i, rs, ld, lane);
+    };
+    // The pre-activation and the bf16 output: the accumulators are read and the bias added once.  (The output's stores follow its own
+    // arithmetic: right behind those of the pre-activation they take 5 % longer where rows are off cache lines.)
+    auto slab_pre_out = [&](int i, __amdgpu_buffer_rsrc_t rs_p, int ldp, __amdgpu_buffer_rsrc_t rs_o, int ldo) __attribute__((always_inline)) {
+        float x[TN][4][4];
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                preact4(i, j, g, x[j][g]);
+                put_bf16(j, g, u32x2_t{pack_bf16(x[j][g][0], x[j][g][1]), pack_bf16(x[j][g][2], x[j][g][3])});
+            }
+        store_bf16(i, rs_p, ldp, lane_bf16(ldp));
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                if constexpr (use_gelu) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) x[j][g][e] = gelu_f(x[j][g][e]);
+                }
+                put_bf16(j, g, u32x2_t{pack_bf16(x[j][g][0], x[j][g][1]), pack_bf16(x[j][g][2], x[j][g][3])});
+            }
+        store_bf16(i, rs_o, ldo, lane_bf16(ldo));
     };
     // fp32 slab, one 32-column block at a time: rows of 128 bytes; lane l stores columns
     // 4 (l % 8) .. + 3 of rows l / 8 + 8 it
@@ -196,6 +259,7 @@ __device__ __forceinline__ void store_c_block(const GemmArgs& p, f32x16_t (&acc)
             slab_f32(i, raw4, std::integral_constant<int, ST_PLAIN>{}, rs_ws, p.N);
             __builtin_amdgcn_sched_barrier(0);
         }
+        last();
     } else {
         const int ldo = (int)p.ldos[g_out];
         const __amdgpu_buffer_rsrc_t rs_out = block_rsrc(p.outs[g_out], ldo, F32_OUT ? 4 : 2);
@@ -204,11 +268,16 @@ __device__ __forceinline__ void store_c_block(const GemmArgs& p, f32x16_t (&acc)
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
             load_dg(i);
-            if constexpr (!use_dg) {
-                if (use_pre) slab_bf16(i, raw4, rs_pre, (int)p.ldp);
+            if constexpr (one_pass) {
+                slab_pre_out(i, rs_pre, (int)p.ldp, rs_out, ldo);
+            } else {
+                if constexpr (!use_dg) {
+                    if (use_pre) slab_bf16(i, preact4, rs_pre, (int)p.ldp);
+                }
+                if constexpr (F32_OUT) slab_f32(i, final4, std::integral_constant<int, ST_STREAM>{}, rs_out, ldo);
+                else                   slab_bf16(i, final4, rs_out, ldo);
             }
-            if constexpr (F32_OUT) slab_f32(i, final4, std::integral_constant<int, ST_STREAM>{}, rs_out, ldo);
-            else                   slab_bf16(i, final4, rs_out, ldo);
+            if (i == TM - 1) last();
             __builtin_amdgcn_sched_barrier(0);
         }
     }

@@ -966,3 +966,30 @@ def test_few_rows_and_long_contractions(m, k, n):
     chunk a wave and several, ragged strips, two steps, every kind of output."""
     for steps, y, dx in ((1, "f32", "bf16"), (2, "bf16", "f32")):
         run_share(T.Grid(T.MODE_2D, q=steps), (steps * m, steps * k, steps * n), y_dtype=y, dx_dtype=dx, use_own_slot=False, label=f"{m}x{k}x{n} steps {steps}")
+
+
+@pytest.mark.parametrize("tile,split", [(0, 0), (1, 1), (1, 3), (2, 1), (3, 1), (4, 1), (4, 3), (5, 1)])
+@pytest.mark.parametrize("m,n", [(300, 1032), (24, 520), (16, 264), (300, 33032)])
+def test_a_large_bias_costs_one_rounding(m, n, tile, split):
+    """Products far below the bias: it is added to the finished sum, once, whatever kernel runs the product (a sum that starts from the
+    bias is rounded at its size with every step of K: 1e-5 here).  The widest shape has more 256 x 256 tiles than workgroups."""
+    k = 4096
+    gen = torch.Generator(device="cuda").manual_seed(m + n)
+    rnd = lambda *shape: torch.randn(shape, generator=gen, device="cuda")
+    x, w = rnd(m, k).to(torch.bfloat16), (1e-5 * rnd(k, n)).to(torch.bfloat16)
+    bias = (8 + 7.5 * torch.rand(n, generator=gen, device="cuda")).to(torch.bfloat16)
+    ref = x.double() @ w.double()
+    assert float(ref.abs().max()) < 0.01
+    ref += bias.double()
+    grid, dims = T.Grid(T.MODE_2D), (m, k, n)
+    y, pre = torch.empty((m, n), device="cuda"), torch.empty((m, n), dtype=torch.bfloat16, device="cuda")
+    # half an ulp of a value below 16, and K / 8 roundings of sums below 0.01 to 24 bits
+    bound = 2.0 ** -21 + k / 8 * 2.0 ** -24 * 0.01
+    with T.plan_opts(tile=tile, split_k=split):
+        ws = workspace_for(grid, dims)
+        for epi in (T.EPI_BIAS, T.EPI_BIAS_GELU):                 # (GeLU(a) is a for a > 7.9 in fp32)
+            T.tp_linear_fwd(grid, dims, 1, [x], [w], bias, epi, y, pre, ws)
+            err = float((y.double() - ref).abs().max())
+            say(f"  {m} x {n} tile {tile} split {split} epilogue {epi}: max err {err:.3g}, bound {bound:.3g}")
+            assert err <= bound
+            assert torch.equal(pre, y.to(torch.bfloat16))
