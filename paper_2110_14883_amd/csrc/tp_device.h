@@ -69,12 +69,14 @@ __device__ __forceinline__ float half_erfc_poly(float t) {           // q / t
 }
 __device__ __forceinline__ float erfc_t(float x) { return __builtin_amdgcn_rcpf(fmaf(0.3275911f * 0.70710678118654752f, x, 1.0f)); }
 __device__ __forceinline__ float exp_half_square(float a) { return __builtin_amdgcn_exp2f(a * a * -0.72134752044448170f); }   // exp(-a^2/2)
-// max(a, 0) - |a| Phi(-|a|).  (|a| is held below infinity, so that +inf gives +inf and not inf - inf x 0; a NaN stays one.
-// The maximum is written out: fmaxf() takes a second instruction to quieten a NaN that the fma carries on anyway.)
+// max(a, 0) - |a| Phi(-|a|).  At infinity it is a (1 + erf(a / sqrt 2)) / 2 as written: +inf stays (a is held below it, so that the second
+// term is not inf x 0), -inf is inf x 0, a NaN, and a NaN stays one.  (Minimum and maximum are written out: fminf() and fmaxf() take a
+// second instruction to quieten a NaN that the fma carries on anyway.)
 __device__ __forceinline__ float gelu_f(float a) {
-    const float x = __builtin_amdgcn_fmed3f(fabsf(a), 0.0f, 1e30f), t = erfc_t(x);
-    float relu;
+    float held, relu;
+    asm("v_min_f32 %0, 0x7149f2ca, %1" : "=v"(held) : "v"(a));       // 1e30
     asm("v_max_f32 %0, 0, %1" : "=v"(relu) : "v"(a));
+    const float x = fabsf(held), t = erfc_t(x);
     return fmaf(-x, half_erfc_poly(t) * t * exp_half_square(a), relu);
 }
 // g GeLU'(a).  GeLU'(a) = Phi(a) + a phi(a) = 1 + h for a >= 0 and -h for a < 0 with h = |a| phi(a) - Phi(-|a|)

@@ -892,14 +892,34 @@ def test_fix_up_of_every_number_of_planes(split):
 
 
 def test_gelu_of_the_ends_of_the_range():
-    """Infinities, a NaN and values whose square overflows: +inf stays, -inf gives its limit 0, a NaN stays one."""
+    """Infinities, a NaN and values whose square overflows, as the oracle's a (1 + erf(a / sqrt 2)) / 2 has them: +inf stays, -inf is a NaN
+    (an overflow upstream does not turn into a 0), a NaN stays one.  On its own, and in the epilogue of a product on every kernel."""
     inf, nan = float("inf"), float("nan")
     c = torch.tensor([[inf, -inf, nan, 3e38, -3e38, 1e20, -1e20, 0.0]], device="cuda")
+    with np.errstate(invalid="ignore", over="ignore"):
+        ref = torch.from_numpy(O.gelu(host64(c))).float()[0].tolist()
+
+    def same(got):
+        for x, g, r in zip(c[0].tolist(), got, ref):
+            assert g == r or (g != g and r != r), (x, g, r)
+
+    zeros = torch.zeros(8, dtype=torch.bfloat16, device="cuda")
     y = torch.empty_like(c)
-    T.tp_bias_act(c, torch.zeros(8, dtype=torch.bfloat16, device="cuda"), T.EPI_BIAS_GELU, y)
-    got, big = y[0].tolist(), c[0].tolist()
-    assert got[0] == inf and got[2] != got[2] and [got[3], got[5]] == [big[3], big[5]]
-    assert got[1] == 0.0 and got[4] == 0.0 and got[6] == 0.0 and got[7] == 0.0
+    T.tp_bias_act(c, zeros, T.EPI_BIAS_GELU, y)
+    same(y[0].tolist())
+    # the same values as products: an 8 x 8 identity times them, in a tile of every kind
+    w = torch.zeros((8, 8), dtype=torch.bfloat16, device="cuda")
+    w[0] = c[0].to(torch.bfloat16)
+    x = torch.zeros((1, 8), dtype=torch.bfloat16, device="cuda")
+    x[0, 0] = 1.0
+    c = w[:1].float()
+    with np.errstate(invalid="ignore", over="ignore"):
+        ref = torch.from_numpy(O.gelu(host64(c))).float()[0].tolist()
+    y = torch.empty((1, 8), device="cuda")
+    for tile in range(6):
+        with T.plan_opts(tile=tile):
+            T.tp_linear_fwd(T.Grid(T.MODE_2D), (1, 8, 8), 1, [x], [w], zeros, T.EPI_BIAS_GELU, y, None, workspace_for(T.Grid(T.MODE_2D), (1, 8, 8)))
+        same(y[0].tolist())
 
 
 @pytest.mark.parametrize("k_tiles", [1, 2, 3, 4])
