@@ -202,7 +202,9 @@ def _stream(stream):
     if stream is None:
         as_object, forked, device, raw = _current_stream_calls()
         return as_object().cuda_stream if forked() else raw(device())
-    return getattr(stream, "cuda_stream", stream)
+    handle = getattr(stream, "cuda_stream", stream)
+    # anything else that ctypes takes for a void*: a c_void_p, an object with _as_parameter_ (and nothing that it refuses)
+    return handle if type(handle) is int else C.cast(handle, C.c_void_p).value
 
 
 def _check(status: int, where: str) -> None:

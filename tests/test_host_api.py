@@ -354,3 +354,43 @@ def test_marshalling_hands_over_what_it_was_given():
     finally:
         m.bind(*own, torch.float32, torch.bfloat16)
     assert _st(lambda: T.tp_linear_fwd(grid, (4, 8, 16), 1, None, [a], None, 0, a, stream=0)) == 1
+
+
+def _recorded_forward(seen):
+    """The forward's C function replaced by one that appends what it is handed to `seen`; a function that puts the own ones back."""
+    import torch
+    m, L = B._call(), B.lib()
+    names = ("tp_linear_fwd_ex", "tp_linear_fwd_static", "tp_linear_bwd_ex", "tp_linear_bwd_partials_ex", "tp_bias_act", "tp_dgelu", "tp_bias_grad")
+    own = [C.cast(getattr(L, n), C.c_void_p).value for n in names]
+    keep = C.CFUNCTYPE(C.c_int, C.c_void_p, C.c_void_p, C.c_int, C.POINTER(B._CBlk), C.POINTER(B._CBlk), C.c_void_p, C.c_int, B._OBlk, B._OBlk, C.c_void_p,
+                       C.c_size_t, C.c_void_p, C.c_void_p)(lambda *a: seen.append(a) or 0)
+    m.bind(C.cast(keep, C.c_void_p).value, *own[1:], torch.float32, torch.bfloat16)
+
+    def restore():
+        assert keep is not None
+        m.bind(*own, torch.float32, torch.bfloat16)
+    return restore
+
+
+def test_a_stream_is_whatever_ctypes_takes_for_a_pointer():
+    """None is torch's current stream; an int, a torch stream, a c_void_p or an object with _as_parameter_ is a handle; what
+    ctypes refuses as a pointer is refused."""
+    class Wrapper:
+        _as_parameter_ = C.c_void_p(0x5678)
+
+    class TorchLike:
+        cuda_stream = 0x9abc
+
+    seen = []
+    restore = _recorded_forward(seen)
+    try:
+        for given, handle in ((0x1234, 0x1234), (C.c_void_p(0x1234), 0x1234), (C.c_void_p(None), None), (0, None), (Wrapper(), 0x5678), (TorchLike(), 0x9abc),
+                              (True, 1)):
+            T.tp_linear_fwd(T.Grid(T.MODE_2D), (8, 8, 8), 1, [(0x40, 8)], [(0x40, 8)], None, 0, (0x40, 8, 0), stream=given)
+            assert seen.pop()[11] == handle, given
+        for refused in (1.0, object(), (1, 2)):
+            with pytest.raises((TypeError, C.ArgumentError)):
+                T.tp_linear_fwd(T.Grid(T.MODE_2D), (8, 8, 8), 1, [(0x40, 8)], [(0x40, 8)], None, 0, (0x40, 8, 0), stream=refused)
+        assert not seen
+    finally:
+        restore()
