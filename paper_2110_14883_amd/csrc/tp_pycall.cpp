@@ -172,6 +172,7 @@ template <class B, bool (*CONVERT)(PyObject*, B*)> struct Blocks {
     const B* ptr = nullptr;
     bool fill(PyObject* o) {
         if (o == Py_None) return true;
+        if (PyObject_Size(o) < 0) return false;    // (an iterator's blocks may be gone before the call)
         Ref s(PySequence_Fast(o, "blocks must be a sequence"));
         if (!s) return false;
         const Py_ssize_t n = PySequence_Fast_GET_SIZE(s.p);

@@ -394,3 +394,21 @@ def test_a_stream_is_whatever_ctypes_takes_for_a_pointer():
         assert not seen
     finally:
         restore()
+
+
+def test_blocks_that_live_only_while_they_are_iterated_over_are_refused():
+    """A list of blocks has a length; a generator could hand out tensors that are freed before the launch."""
+    import torch
+    seen = []
+    restore = _recorded_forward(seen)
+    try:
+        one = [torch.zeros(8, 8, dtype=torch.bfloat16)]
+        for x, w in ((iter(one), one), (one, (t for t in one))):
+            with pytest.raises(TypeError):
+                T.tp_linear_fwd(T.Grid(T.MODE_2D), (8, 8, 8), 1, x, w, None, 0, (0x40, 8, 0), stream=0)
+        assert not seen
+        for x in (one, tuple(one), torch.zeros(1, 8, 8, dtype=torch.bfloat16)):
+            T.tp_linear_fwd(T.Grid(T.MODE_2D), (8, 8, 8), 1, x, one, None, 0, (0x40, 8, 0), stream=0)
+            assert (seen[-1][3][0].ptr, seen[-1][3][0].ld) == ((x if torch.is_tensor(x) else x[0]).data_ptr(), 8)
+    finally:
+        restore()
