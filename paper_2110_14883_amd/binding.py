@@ -190,18 +190,23 @@ def _rows_cols(t, rows, cols):
 
 
 @functools.lru_cache(maxsize=1)
-def _current_stream_calls():
+def _raw_stream_calls():
+    """torch's functions for the current stream's handle, or None where this torch does not have them under these names."""
     import torch
     torch.cuda.current_stream()              # (initialises the device, or says why it cannot)
-    return torch.cuda.current_stream, torch._C._cuda_isInBadFork, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
+    calls = [getattr(torch._C, n, None) for n in ("_cuda_isInBadFork", "_cuda_getDevice", "_cuda_getCurrentRawStream")]
+    return calls if all(calls) else None
 
 
 def _stream(stream):
     """A stream's handle; None is torch's current stream on the current device (asked for by its handle: making the stream
     object as well takes 2.9 us, a third of a small call)."""
     if stream is None:
-        as_object, forked, device, raw = _current_stream_calls()
-        return as_object().cuda_stream if forked() else raw(device())
+        calls = _raw_stream_calls()
+        if calls is None or calls[0]():      # (a forked child: current_stream() says so)
+            import torch
+            return torch.cuda.current_stream().cuda_stream
+        return calls[2](calls[1]())
     handle = getattr(stream, "cuda_stream", stream)
     # anything else that ctypes takes for a void*: a c_void_p, an object with _as_parameter_ (and nothing that it refuses)
     return handle if type(handle) is int else C.cast(handle, C.c_void_p).value

@@ -412,3 +412,26 @@ def test_blocks_that_live_only_while_they_are_iterated_over_are_refused():
             assert (seen[-1][3][0].ptr, seen[-1][3][0].ld) == ((x if torch.is_tensor(x) else x[0]).data_ptr(), 8)
     finally:
         restore()
+
+
+def test_the_current_stream_with_and_without_the_raw_calls(monkeypatch):
+    """Where torch has no function for the handle alone, or the process is a forked child, the stream object is asked."""
+    import torch
+
+    class Stream:
+        cuda_stream = 0x77
+
+    monkeypatch.setattr(torch.cuda, "current_stream", Stream)
+    for n, f in (("_cuda_isInBadFork", lambda: False), ("_cuda_getDevice", lambda: 3), ("_cuda_getCurrentRawStream", lambda d: 0x1000 + d)):
+        monkeypatch.setattr(torch._C, n, f, raising=False)
+    B._raw_stream_calls.cache_clear()
+    try:
+        assert B._stream(None) == 0x1003
+        monkeypatch.setattr(torch._C, "_cuda_isInBadFork", lambda: True)
+        B._raw_stream_calls.cache_clear()
+        assert B._stream(None) == 0x77
+        monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream")
+        B._raw_stream_calls.cache_clear()
+        assert B._stream(None) == 0x77
+    finally:
+        B._raw_stream_calls.cache_clear()
