@@ -8,8 +8,10 @@ import contextlib
 import contextvars
 import ctypes as C
 import functools
+import importlib.machinery
 import importlib.util
 import os
+import sys
 from dataclasses import dataclass
 
 MODE_1D_COL, MODE_1D_ROW, MODE_2D, MODE_2P5D, MODE_3D, MODE_3D_GATHERED = 10, 11, 2, 25, 3, 33
@@ -19,7 +21,7 @@ DT_BF16, DT_F32 = 0, 1
 MAX_STEPS = 16
 
 _LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libtplinear.so")
-_CALL_PATH = os.path.join(os.path.dirname(_LIB_PATH), "_tpcall.so")
+_CALL_PATH = os.path.join(os.path.dirname(_LIB_PATH), "_tpcall" + importlib.machinery.EXTENSION_SUFFIXES[0])   # of this interpreter
 _lib = None
 
 
@@ -158,7 +160,7 @@ def _call():
     """The extension module that makes the calls, given the loaded library's functions."""
     L = lib()
     if not os.path.exists(_CALL_PATH):
-        raise RuntimeError(f"{_CALL_PATH} is not built; run `python -m paper_2110_14883_amd.build`")
+        raise RuntimeError(f"{_CALL_PATH} is not built; run `{sys.executable or 'python'} -m paper_2110_14883_amd.build` with this interpreter")
     spec = importlib.util.spec_from_file_location("_tpcall", _CALL_PATH)
     m = importlib.util.module_from_spec(spec)
     spec.loader.exec_module(m)

@@ -1,10 +1,11 @@
-"""Builds libtplinear.so (gfx950) in-tree with hipcc, and the binding's extension module _tpcall.so (host code)
-with the C++ compiler.  `python -m paper_2110_14883_amd.build`.
+"""Builds libtplinear.so (gfx950) in-tree with hipcc, and the binding's extension module _tpcall (host code, for the
+interpreter that builds it and named after it) with the C++ compiler.  `python -m paper_2110_14883_amd.build`.
 
 Every source is compiled to its own object (in parallel) and the objects are linked into the shared
 library; objects are kept under csrc/_build/ and reused while their source and the headers are older."""
 from __future__ import annotations
 
+import importlib.machinery
 import os
 import subprocess
 import sys
@@ -17,7 +18,7 @@ CSRC = os.path.join(PKG_DIR, "csrc")
 OBJ_DIR = os.path.join(CSRC, "_build")
 LIB_PATH = os.path.join(PKG_DIR, "libtplinear.so")
 PROBE_LIB_PATH = os.path.join(PKG_DIR, "libtpprobe.so")      # bench-only measurement aid (tp_probe.hip)
-CALL_LIB_PATH = os.path.join(PKG_DIR, "_tpcall.so")
+CALL_LIB_PATH = os.path.join(PKG_DIR, "_tpcall" + importlib.machinery.EXTENSION_SUFFIXES[0])
 CALL_SOURCE = "tp_pycall.cpp"
 SOURCES = ["tp_kernels.hip", "tp_gemm4.hip", "tp_gemm_ms.hip", "tp_small.hip", "tp_api.cpp"]
 PROBE_SOURCE = "tp_probe.hip"

@@ -435,3 +435,11 @@ def test_the_current_stream_with_and_without_the_raw_calls(monkeypatch):
         assert B._stream(None) == 0x77
     finally:
         B._raw_stream_calls.cache_clear()
+
+
+def test_the_extension_module_carries_the_interpreter_in_its_name():
+    """Another interpreter finds no module and is told to build one; it does not load this one's."""
+    import sysconfig
+    from paper_2110_14883_amd import build
+    path = B._call().__file__
+    assert path == build.CALL_LIB_PATH == B._CALL_PATH and path.endswith(sysconfig.get_config_var("EXT_SUFFIX"))
