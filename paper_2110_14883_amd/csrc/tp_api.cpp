@@ -292,11 +292,12 @@ double small_cost(int form, int bm, int64_t wgs, int64_t T, double bytes) {
 
 // The same kernel for a forward of at most 32 rows, with tiles of 64 columns (whole cache lines of weight rows) and K split
 // over z workgroups too where there are few of them: z > 1 writes planes and takes the fix-up launch.  A wave then has one or
-// two chunks, all on their way at once, instead of a chain of them.  Fitted to 16 rows, in us, mean of operands from memory
+// two chunks, with 16 rows all on their way at once, instead of a chain of them.  Fitted to 16 rows, in us, mean of operands from memory
 // and cached (1900 cycles); from memory, against the better of 32 columns and 128 x 128 tiles: 4096 x 4096 19.9 -> 13.6 (z = 4), 4096 x
 // 1024 18.9 -> 9.7 (8), 8192 x 2048 17.1 -> 13.4 (8), 1024 x 16384 16.0 -> 11.1 (1), 4096 x 8192 21.0 -> 19.5 (2); 3 steps of
 // 392 x 5568 stay with 32 columns (7.9 against 9.1), 4 of 6144 x 6144 with 128 x 128 tiles (58 / 71).
-// 32 rows leave a wave one slot, so its chunks do not overlap.
+// 32 rows leave a wave one slot, so its chunks do not overlap: 1.15 x a chunk of 16 rows where a wave has nine or more (1.50 us against 1.31,
+// medians of 370 and 290 draws; both below the constants, which were fitted on another box: the line is on the safe side).
 double wide_cost(int bm, int64_t strips, int z, int64_t T) {
     const int64_t chunks = (T + 8 * z - 1) / (8 * z), rounds = (strips * z + kCUs - 1) / kCUs;
     const double wgs = (double)(strips * z) / (double)rounds, chunk = bm == 16 ? 1.95 : 2.2;
@@ -339,6 +340,12 @@ Plan make_plan(const Opts& o, int form, int64_t m, int64_t n, int64_t k, int n_s
             for (int z = 1; z <= 8 && z * strips <= (z > 1 ? kCUs : 4 * kCUs); ++z) {
                 Plan c{bm == 16 ? TILE_16x64_SMALL : TILE_32x64_SMALL, bm, 64, 1, (int)strips, z, group_m, 1, 0, 0, 0, 0, 0, 0};
                 const double wide = wide_cost(bm, strips, z, T);
+                // Whole K in one workgroup: its chain of chunks is in the open where the strips do not fit one round of workgroups, and
+                // is long beyond eight chunks a wave.  Time of the best other plan over this one's, from memory and cached, 280 drawn products:
+                // strips in one round, up to 8 chunks a wave 0.86 - 1.63 and 1.12 - 1.79, more chunks 0.58 - 1.16 and 0.59 - 1.22; strips in
+                // several, up to 2 chunks 0.88 - 1.02 and 0.97 - 1.41, more 0.59 - 1.01 and 0.59 - 1.10.  (30 x 16992, K = 2360: 31.1 and 24.2 us with,
+                // 23.0 and 21.0 without; 32 x 10896, K = 3 x 1624: 33.6 and 23.4, 26.7 and 24.5.)
+                if (z == 1 && T > (strips > kCUs ? 16 : 64)) continue;
                 if (ws_bytes_for(c, m, n) > need || wide >= cost) continue;
                 p = c;
                 cost = wide;
