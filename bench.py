@@ -38,9 +38,9 @@ NSETS = int(os.environ.get("TPL_BENCH_NSETS", "3"))   # buffer sets rotated thro
 # of the headline workload.  (Its dX is planned with K split in two: the launch is the fp32-partials
 # instantiation, followed by the fix-up kernel's 252 MB.)
 MEASURED_TRAFFIC_BYTES = {
-    "tpl::tp_gemm4_kernel<true, false, 2, false, true>": 2274000000,     # forward NN + bias + GeLU: 1872 MB read, 403 MB written
-    "tpl::tp_gemm4_kernel<false, false, 0, true, false>": 2959000000,     # dW TN: 2355 MB read, 604 MB written
-    "tpl::tp_gemm4_kernel<true, true, 0, true, false>": 2134000000,       # dX NT: 1932 MB read, 201 MB written
+    "tpl::tp_gemm4_kernel<true, false, 2, false, true, true>": 2274000000,     # forward NN + bias + GeLU: 1872 MB read, 403 MB written
+    "tpl::tp_gemm4_kernel<false, false, 0, true, false, true>": 2959000000,     # dW TN: 2355 MB read, 604 MB written
+    "tpl::tp_gemm4_kernel<true, true, 0, true, false, true>": 2134000000,       # dX NT: 1932 MB read, 201 MB written
 }
 
 
@@ -51,9 +51,9 @@ def log(*a):
 def gemm_symbol(form: str, epi: int, f32_out: bool, pre: bool = False) -> str:
     """Name of the 256x256 GEMM instantiation a call launches when K is not split (as rocprofv3 prints it, without
     'void' and the argument list).  form: NN / NT / TN; epi: 0 none, 1 bias, 2 bias+GeLU, 3 *GeLU'; pre: the
-    pre-activation is stored too."""
+    pre-activation is stored too (every output here has rows on 64-byte boundaries: streamed, the last argument)."""
     kc = {"NN": "true, false", "NT": "true, true", "TN": "false, false"}[form]
-    return f"tpl::tp_gemm4_kernel<{kc}, {epi}, {'true' if f32_out else 'false'}, {'true' if pre else 'false'}>"
+    return f"tpl::tp_gemm4_kernel<{kc}, {epi}, {'true' if f32_out else 'false'}, {'true' if pre else 'false'}, true>"
 
 
 # Calls of these workloads whose main kernel the kernel traces under profiles/ show to be another: K split into fp32

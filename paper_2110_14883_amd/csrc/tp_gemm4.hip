@@ -36,9 +36,10 @@ constexpr int W4_EPI_BYTES_PER_WAVE = 8192;                  // 32 rows x 256 by
 
 }  // namespace
 
-// PRE: the pre-activation is stored too.  (Compiled in: with both ways through the epilogue in one kernel the one without it took 143 us
-// for 16384 x 1024, K = 4096 with GeLU, alone 134.5.)
-template <bool A_KC, bool B_KC, int EPI, bool F32_OUT, bool PRE>
+// PRE: the pre-activation is stored too; STREAM: stores carry the streaming hint.  (Compiled in: with both ways through the epilogue in one
+// kernel, the one without the pre-activation took 143 us for 16384 x 1024, K = 4096 with GeLU, alone 134.5; and a branch around the
+// stores cost the one with it 2 %, 32896 x 2560, K = 2 x 640 230.5 -> 235.4.)
+template <bool A_KC, bool B_KC, int EPI, bool F32_OUT, bool PRE, bool STREAM>
 __global__ __launch_bounds__(W4_THREADS) __attribute__((amdgpu_waves_per_eu(1, 1)))
 void tp_gemm4_kernel(const GemmArgs p) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
@@ -343,7 +344,7 @@ void tp_gemm4_kernel(const GemmArgs p) {
         BiasBlock<TN> bias;
         if constexpr (USE_BIAS) spread_bias(bias, own_bias, eps);
         store_c_block<TM, TN, EPI, F32_OUT, true, USE_BIAS>(p, acc, done.m0 + wm * 128, done.n0 + wn * 128, done.z, done.g, bias, eps,
-                                                            std::bool_constant<PRE>{}, take_bias);
+                                                            std::bool_constant<PRE>{}, std::bool_constant<STREAM>{}, take_bias);
         if (c.left == 0) break;
         barrier();                                    // every wave is done with its patch
     }
@@ -352,21 +353,27 @@ void tp_gemm4_kernel(const GemmArgs p) {
 // ---------------------------------------------------------------------------------------------
 // host launcher
 // ---------------------------------------------------------------------------------------------
-template <bool A_KC, bool B_KC, int EPI, bool F32_OUT, bool PRE = false>
-static hipError_t launch4_one(const GemmArgs& a, hipStream_t stream) {
+template <bool A_KC, bool B_KC, int EPI, bool F32_OUT, bool PRE, bool STREAM>
+static hipError_t launch4_as(const GemmArgs& a, hipStream_t stream) {
     static std::atomic<uint64_t> attr_done{0};
     int dev = 0;
     if (hipError_t e = hipGetDevice(&dev); e != hipSuccess) return e;
     const uint64_t bit = 1ull << (dev & 63);
     if (!(attr_done.load(std::memory_order_relaxed) & bit)) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&tp_gemm4_kernel<A_KC, B_KC, EPI, F32_OUT, PRE>),
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&tp_gemm4_kernel<A_KC, B_KC, EPI, F32_OUT, PRE, STREAM>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, W4_LDS_BYTES);
         if (e != hipSuccess) return e;
         attr_done.fetch_or(bit, std::memory_order_relaxed);
     }
     const int total = a.tiles_m * a.tiles_n * a.split_k;
     const unsigned grid = (unsigned)(total < a.max_workgroups ? total : a.max_workgroups);
-    return launch_kernel(tp_gemm4_kernel<A_KC, B_KC, EPI, F32_OUT, PRE>, dim3(grid), dim3(W4_THREADS), W4_LDS_BYTES, stream, a);
+    return launch_kernel(tp_gemm4_kernel<A_KC, B_KC, EPI, F32_OUT, PRE, STREAM>, dim3(grid), dim3(W4_THREADS), W4_LDS_BYTES, stream, a);
+}
+
+template <bool A_KC, bool B_KC, int EPI, bool F32_OUT, bool PRE = false>
+static hipError_t launch4_one(const GemmArgs& a, hipStream_t s) {
+    // (planes never carry the hint: either kernel stores them)
+    return a.stream ? launch4_as<A_KC, B_KC, EPI, F32_OUT, PRE, true>(a, s) : launch4_as<A_KC, B_KC, EPI, F32_OUT, PRE, false>(a, s);
 }
 
 // (the pre-activation of a split product is the fix-up's to store)

@@ -258,7 +258,7 @@ void tp_gemm_ms_kernel(const GemmArgs p) {
                 for (int i = 0; i < TM; ++i) acc[i][j][e] += b;
             }
     }
-    store_c_block<TM, TN, EPI, F32_OUT, false, false>(p, acc, m0 + wm * WM, n0 + wn * WN, z, g, bias, lds + w * 8192, p.pre != nullptr, [] {});
+    store_c_block<TM, TN, EPI, F32_OUT, false, false>(p, acc, m0 + wm * WM, n0 + wn * WN, z, g, bias, lds + w * 8192, p.pre != nullptr, p.stream != 0, [] {});
 }
 
 // ---------------------------------------------------------------------------------------------

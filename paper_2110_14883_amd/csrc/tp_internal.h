@@ -46,6 +46,7 @@ struct GemmArgs {
     float* ws;                          // [split_k][M][N] fp32 partials
     int32_t rotate;                     // rotate the K-tile order inside a step per C tile
     int32_t max_workgroups;             // persistent grid size cap (workgroups resident at once)
+    int32_t stream;                     // stores of the outputs carry the streaming hint
     // Grouped launch (n_groups > 1): n_groups independent single-step products of the same extents
     // in one grid, product g = a[g] x b[g] -> outs[g] (no epilogue).  The groups are laid side by
     // side along N (group_along_n) or along M in the tile grid: tiles_m / tiles_n then count the

@@ -540,6 +540,16 @@ static hipError_t launch_tile(int form, const GemmArgs& a, hipStream_t s) {
     }
 }
 
+// Whether stores of an output, one of `total` bytes in this launch, carry the streaming hint (why: store_c_block).  A streamed piece of a 64-byte
+// sector goes to memory as it is, and a row off those boundaries has one at both ends of every tile's segment: over a product's time more than
+// memory takes.  Nothing else of an output that size stays in the 32 MB of the L2s either; a small one is better off leaving early all the same.
+// Rows off the boundaries, with the hint / without, us: 24777 x 5640 fp32, K = 216 300 / 182; 17425 x 3432 fp32, K = 200 132 / 78; two of
+// 11015 x 3000 fp32, K = 64 146 / 82; 6144 x 5256 bf16 twice, K = 768 86 / 72.  Means over 413 drawn products from memory / cached, by outputs:
+// below 16 MB 1.02 / 0.99 x, 16 to 35 MB 0.98 / 0.91, 35 to 90 0.91 / 0.87, beyond 0.81 / 0.76.
+static bool streams(const void* p, int64_t ld, int es, int64_t total) {
+    return total <= (16 << 20) || (((uint64_t)(uintptr_t)p | (uint64_t)(ld * es)) & 63) == 0;
+}
+
 // A plain launch is one group whose output is `out`; false: a grouped one that does not hold together.
 static bool normalise(GemmArgs& a) {
     if (a.tiles_m < 1 || a.tiles_n < 1 || a.group_m < 1) return false;
@@ -550,10 +560,15 @@ static bool normalise(GemmArgs& a) {
     if (a.n_groups <= 1) {
         a.n_groups = 1; a.group_along_n = 1; a.group_tiles = a.tiles_n;
         a.outs[0] = a.out; a.ldos[0] = a.ldo;
-        return true;
+    } else if (a.n_steps != 1 || a.n_groups > TP_MAX_STEPS || a.group_tiles < 1 || a.bias || a.dg || a.pre ||
+               (a.group_along_n ? a.tiles_n : a.tiles_m) != a.n_groups * a.group_tiles) {
+        return false;
     }
-    return a.n_steps == 1 && a.n_groups <= TP_MAX_STEPS && a.group_tiles >= 1 && !a.bias && !a.dg && !a.pre &&
-           (a.group_along_n ? a.tiles_n : a.tiles_m) == a.n_groups * a.group_tiles;
+    const int es = a.out_f32 ? 4 : 2;
+    const int64_t total = (int64_t)a.M * a.N * (es * a.n_groups + (a.pre ? 2 : 0));
+    a.stream = !a.pre || streams(a.pre, a.ldp, 2, total);
+    for (int g = 0; g < a.n_groups; ++g) a.stream &= streams(a.outs[g], a.ldos[g], es, total);
+    return true;
 }
 
 hipError_t launch_gemm_pair(int tile_x, const GemmArgs& x, int tile_w, const GemmArgs& w, hipStream_t s) {

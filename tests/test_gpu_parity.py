@@ -1013,3 +1013,45 @@ def test_a_large_bias_costs_one_rounding(m, n, tile, split):
             say(f"  {m} x {n} tile {tile} split {split} epilogue {epi}: max err {err:.3g}, bound {bound:.3g}")
             assert err <= bound
             assert torch.equal(pre, y.to(torch.bfloat16))
+
+
+@pytest.mark.parametrize("tile", [1, 2, 3, 4])
+@pytest.mark.parametrize("kind", ["Y fp32", "Y", "Y fp32 and A", "Y and A", "Y and A in wide rows", "dX fp32", "dX", "dX GeLU'", "dW", "dX partials"])
+def test_outputs_with_and_without_the_streaming_hint(kind, tile):
+    """More than 16 MB of outputs whose rows start off 64-byte boundaries are stored without the hint, in rows on them with it: the same
+    bits, and nothing beside the block.  One group's odd rows, or the pre-activation's, decide for the launch."""
+    m, k, n = 4136, 72, 2056
+    gen = torch.Generator(device="cuda").manual_seed(tile)
+    rnd = lambda *shape: torch.randn(shape, generator=gen, device="cuda").to(torch.bfloat16)
+    f32 = "fp32" in kind or kind in ("dW", "dX partials")
+    a, b, bias, dg = (rnd(k, m) if kind == "dW" else rnd(m, k)), (rnd(k, n) if kind[0] == "Y" or kind == "dW" else rnd(n, k)), rnd(n), rnd(m, n)
+    ws = torch.empty(256, dtype=torch.uint8, device="cuda")
+
+    def out(ld, dtype):
+        whole = torch.full((m, ld), 7.0, dtype=dtype, device="cuda")
+        return whole, whole[:, :n]
+
+    def run(ld, ld_pre):
+        whole, y = out(ld, torch.float32 if f32 else torch.bfloat16)
+        whole_pre, pre = out(ld_pre, torch.bfloat16) if "A" in kind else (whole, None)
+        with T.plan_opts(tile=tile, split_k=1, trim=2):
+            if kind[0] == "Y":
+                T.tp_linear_fwd(T.Grid(T.MODE_2D), (m, k, n), 1, [a], [b], bias, T.EPI_BIAS_GELU, y, pre, ws)
+            elif kind == "dW":
+                T.tp_linear_bwd(T.Grid(T.MODE_2D), (k, m, n), 0, 1, x_blocks_dw=[a], da_col_blocks=[b], dw=y, workspace=ws)
+            elif kind == "dX partials":
+                other = torch.empty((m, n), device="cuda")
+                T.tp_linear_bwd_partials(T.Grid(T.MODE_2D, q=2), (2 * m, 2 * n, 2 * k), a, [b, b], [other, y], workspace=ws)
+                assert torch.equal(other, y)
+            else:
+                T.tp_linear_bwd(T.Grid(T.MODE_2D), (m, n, k), 1, 0, da_row_blocks=[a], w_blocks_dx=[b], dx=y, workspace=ws, dgelu_preact=dg if "GeLU" in kind else None)
+        assert bool((whole[:, n:] == 7.0).all()) and bool((whole_pre[:, n:] == 7.0).all())
+        return y, pre
+
+    off, on = n, 2112
+    y0, pre0 = run(on, off if "wide" in kind else on)
+    y1, pre1 = run(off, off)
+    assert torch.equal(y0, y1) and (pre0 is None or torch.equal(pre0, pre1))
+    if kind in ("Y fp32", "dX fp32", "dW"):
+        ref = (a.double().T if kind == "dW" else a.double()) @ (b.double() if kind[0] == "Y" or kind == "dW" else b.double().T)
+        check(host64(y1), O.gelu(host64(ref) + host64(bias)) if kind[0] == "Y" else host64(ref), "f32", kind)
