@@ -21,7 +21,9 @@
  * Ownership / errors.  The caller owns every buffer; the library never allocates, frees or
  * synchronises.  Work is enqueued on the HIP stream passed in (a hipStream_t cast to void*, NULL =
  * the default stream) and the call returns immediately.  Inputs are read-only and may alias each
- * other but not outputs.  Every failure is a return code found before anything is launched; nothing
+ * other but not the output of a product that reads them.  A backward call finishes its outputs in the
+ * order dA, db, dX, dW as far as that can be seen: dW may be written over what only dX reads, and dW
+ * reads what dX left where dX is written over blocks of dW's.  Every failure is a return code found before anything is launched; nothing
  * is written on error.  Row counts may be any value >= 1 (ragged tails are masked); column extents
  * of every block and every `ld` must be multiples of 8 elements and every pointer, the workspace
  * included, 16-byte aligned (128-bit loads and stores), else TP_ERR_ALIGN (TP_ERR_WORKSPACE for the

@@ -478,7 +478,7 @@ bool writes_into(const GemmArgs& w, int form, const GemmArgs& r) {
 }
 
 // The two products of a backward call, dX first.  Where both run on the workgroup-split kernel they share one launch, unless one
-// writes what the other reads: then the order is what the caller counts on.
+// writes what the other reads or writes: there the order shows, and the header promises it.
 int run_backward(const Opts& o, const Product& px, const Product& pw, void* workspace, hipStream_t stream) {
     auto small = [](const Product& p) { return p.active && p.plan.tile_id >= TILE_32x32_SMALL; };
     if (small(px) && small(pw) && !writes_into(px.args, pw.form, pw.args) && !writes_into(pw.args, px.form, px.args))
