@@ -255,7 +255,7 @@ void tp_gemm4_kernel(const GemmArgs p) {
     //     every fourth when 12, every slot when 16); those of step 0 of the NEXT K tile during step 3,
     //     from the next stages, after the barrier before slot 48;
     //   loads: those of K tile u + 2.  A has three stages: its loads come from slot 9 on, every fourth slot, into the stage of
-    //     tile u - 1, free since the last barrier; they have 70 - 100 slots to land.  B has two: its loads come after the barrier, every other
+    //     tile u - 1, free since the last barrier; they have 75 - 103 slots to land.  B has two: its loads come after the barrier, every other
     //     slot, into the stage that tile u has just been read from, and have 49 - 63.  (All four waves run the same schedule, so a slot
     //     with a load asks the CU's one address path for 4 KB, two slots at 64 B/clk; four where rows are off cache lines.)
     //   With two stages of each and the epilogue's patches beside them one operand had 17 - 47 slots, less than a load from beyond the

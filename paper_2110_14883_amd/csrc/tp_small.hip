@@ -8,7 +8,7 @@
 //     rows) may split K over workgroups too, with planes and a fix-up: 33.5 MB of weights from memory 19.9 -> 13.6 us;
 //   * waves take the chunks of 64 k in turn (wave w of part z of Z: 8 z + w, 8 (z + Z) + w, ...), across the steps of the sum, and work alone until
 //     the end: each has its own ring of LDS slots, filled by direct-to-LDS loads (16 bytes a lane: 8 lines or 16
-//     half lines an instruction) one or two chunks ahead, with no barrier in the K loop.  An operand that is not
+//     half lines an instruction) one to three chunks ahead (slots - 1; a tile of 32 x 64 has one slot and none ahead), with no barrier in the K loop.  An operand that is not
 //     contraction-contiguous is transposed on the way out, by ds_read_b64_tr_b16.
 //     (Fragments loaded straight into registers, 16 bytes of a row or 4 bytes of 8 rows a lane, kept the address path
 //     busy four times as long: 16 x 4096 x 4096 dX 13.9 us against 8.0, 512 x 1024 x 1024 dX 12.5 against 7.5, forward

@@ -858,9 +858,9 @@ def test_long_k_and_few_large_tiles_are_split_over_workgroups(kind, m, k, n, cou
 
 @pytest.mark.parametrize("m,n", [(300, 1416), (1300, 264)])
 @pytest.mark.parametrize("k", [64, 128, 192, 200])
-def test_either_operand_of_the_stream_kernel_forward_late(m, n, k):
-    """The forward on 256 x 256 tiles with operand B late (rows of A on cache lines, C wider than tall) and with operand A
-    late (rows off the lines, or C as tall as wide): one K tile a step to four, two steps, K whole and split."""
+def test_stream_kernel_forward_of_short_steps(m, n, k):
+    """The forward on 256 x 256 tiles, C wider than tall and taller than wide: one K tile a step to four (the last one ragged), two steps, K
+    whole and split, the ring of A's three stages entered and left at every position."""
     for split in (1, 3):
         with overrides(tile=1, split=split if 2 * ((k + 63) // 64) >= split else 2):
             run_share(T.Grid(T.MODE_2D, q=2, ri=0, rj=1), (2 * m, 2 * k, 2 * n), backward=False, y_dtype="f32" if split == 1 else "bf16",
@@ -949,7 +949,8 @@ def test_stream_kernel_with_few_k_tiles_a_tile(form, k_tiles):
 @pytest.mark.parametrize("overlap", ["none", "dW over W", "dX over X"])
 def test_both_backward_products_in_one_launch(m, h, f, overlap):
     """dX and dW of one call are those of two calls, bit for bit; also where one is written over what the other reads, which the
-    order of the two (dX, then dW) makes well defined for dW over W and for dX over an X that dW reads as dX left it."""
+    order of the two (dX, then dW) makes well defined for dW over W and for dX over an X that dW reads as dX left it.
+    (That they share a launch, and where they do not, is shown in test_launch_routes.py.)"""
     gen = torch.Generator(device="cuda").manual_seed(m)
     rand = lambda r, c: torch.randn((r, c), generator=gen, device="cuda", dtype=torch.bfloat16)
     grid, dims = T.Grid(T.MODE_2D), (m, h, f)
