@@ -38,9 +38,9 @@ NSETS = int(os.environ.get("TPL_BENCH_NSETS", "3"))   # buffer sets rotated thro
 # of the headline workload.  (Its dX is planned with K split in two: the launch is the fp32-partials
 # instantiation, followed by the fix-up kernel's 252 MB.)
 MEASURED_TRAFFIC_BYTES = {
-    "tpl::tp_gemm4_kernel<true, false, 2, false, true, true>": 2274000000,     # forward NN + bias + GeLU: 1872 MB read, 403 MB written
-    "tpl::tp_gemm4_kernel<false, false, 0, true, false, true>": 2959000000,     # dW TN: 2355 MB read, 604 MB written
-    "tpl::tp_gemm4_kernel<true, true, 0, true, false, true>": 2134000000,       # dX NT: 1932 MB read, 201 MB written
+    "tpl::tp_gemm4_kernel<true, false, 2, false, true, true>": 2229000000,     # forward NN + bias + GeLU: 1826 MB read, 403 MB written
+    "tpl::tp_gemm4_kernel<false, false, 0, true, false, true>": 2528000000,     # dW TN: 1924 MB read, 604 MB written
+    "tpl::tp_gemm4_kernel<true, true, 0, true, false, true>": 2172000000,       # dX NT: 1971 MB read, 201 MB written
 }
 
 
