@@ -309,14 +309,18 @@ PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n) {
 PyMethodDef methods[] = {{"fwd", FAST(fwd)}, {"fwd_static", FAST(fwd_static)}, {"bwd", FAST(bwd)}, {"bwd_partials", FAST(bwd_partials)},
                          {"bias_act", FAST(bias_act)}, {"dgelu", FAST(dgelu)}, {"bias_grad", FAST(bias_grad)}, {"bind", FAST(bind)},
                          {nullptr, nullptr, 0, nullptr}};
-PyModuleDef module = {PyModuleDef_HEAD_INIT, "_tpcall", "argument marshalling of the libtplinear binding", -1, methods, nullptr, nullptr, nullptr, nullptr};
-
-}  // namespace
-
-PyMODINIT_FUNC PyInit__tpcall(void) {
+// (Set up in its exec slot: a second load of the file makes a module of its own.  A module set up in one go would fill the one that stands under
+// this name in sys.modules, which may be another copy's.)
+int exec(PyObject*) {
     struct { PyObject** to; const char* name; } names[] = {{&s_data_ptr, "data_ptr"}, {&s_stride, "stride"}, {&s_shape, "shape"},
                                                            {&s_dtype, "dtype"}, {&s_numel, "numel"}, {&s_element_size, "element_size"}};
     for (auto& x : names)
-        if (!(*x.to = PyUnicode_InternFromString(x.name))) return nullptr;
-    return PyModule_Create(&module);
+        if (!*x.to && !(*x.to = PyUnicode_InternFromString(x.name))) return -1;
+    return 0;
 }
+PyModuleDef_Slot slots[] = {{Py_mod_exec, reinterpret_cast<void*>(exec)}, {0, nullptr}};
+PyModuleDef module = {PyModuleDef_HEAD_INIT, "_tpcall", "argument marshalling of the libtplinear binding", 0, methods, slots, nullptr, nullptr, nullptr};
+
+}  // namespace
+
+PyMODINIT_FUNC PyInit__tpcall(void) { return PyModuleDef_Init(&module); }

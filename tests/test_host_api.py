@@ -443,3 +443,33 @@ def test_the_extension_module_carries_the_interpreter_in_its_name():
     from paper_2110_14883_amd import build
     path = B._call().__file__
     assert path == build.CALL_LIB_PATH == B._CALL_PATH and path.endswith(sysconfig.get_config_var("EXT_SUFFIX"))
+
+
+def test_two_copies_of_the_extension_module_stay_apart(tmp_path):
+    """A second copy of the package in the process has functions of its own, also after the first one's module is loaded again."""
+    import importlib.util
+    import shutil
+    import torch
+
+    def load(path):
+        spec = importlib.util.spec_from_file_location("_tpcall", path)
+        m = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(m)
+        return m
+
+    names = ("tp_linear_fwd_ex", "tp_linear_fwd_static", "tp_linear_bwd_ex", "tp_linear_bwd_partials_ex", "tp_bias_act", "tp_dgelu", "tp_bias_grad")
+    own = [C.cast(getattr(B.lib(), n), C.c_void_p).value for n in names]
+    sig = C.CFUNCTYPE(C.c_int, C.c_void_p, C.c_int64, C.c_void_p, C.c_int64, C.c_void_p, C.c_int64, C.c_int64, C.c_int64, C.c_void_p)
+    here, there = sig(lambda *a: 101), sig(lambda *a: 102)
+    put = lambda f: own[:5] + [C.cast(f, C.c_void_p).value] + own[6:]
+    other = shutil.copy(B._CALL_PATH, tmp_path / os.path.basename(B._CALL_PATH))
+    first = load(B._CALL_PATH)
+    try:
+        first.bind(*put(here), torch.float32, torch.bfloat16)
+        second = load(other)
+        second.bind(*put(there), torch.float32, torch.bfloat16)
+        again = load(B._CALL_PATH)
+        call = lambda m: m.dgelu((0x40, 8), (0x40, 8), (0x40, 8), 1, 8, 0)
+        assert [call(m) for m in (first, second, again, second, first)] == [101, 102, 101, 102, 101]
+    finally:
+        first.bind(*own, torch.float32, torch.bfloat16)
