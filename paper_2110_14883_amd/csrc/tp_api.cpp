@@ -297,7 +297,7 @@ double small_cost(int form, int bm, int64_t wgs, int64_t T, double bytes) {
 // 1024 18.9 -> 9.7 (8), 8192 x 2048 17.1 -> 13.4 (8), 1024 x 16384 16.0 -> 11.1 (1), 4096 x 8192 21.0 -> 19.5 (2); 3 steps of
 // 392 x 5568 stay with 32 columns (7.9 against 9.1), 4 of 6144 x 6144 with 128 x 128 tiles (58 / 71).
 // 32 rows leave a wave one slot, so its chunks do not overlap: 1.15 x a chunk of 16 rows where a wave has nine or more (1.50 us against 1.31,
-// medians of 370 and 290 draws; both below the constants, which were fitted on another box: the line is on the safe side).
+// medians of 370 and 290 draws; both below the constants, which were fitted on another card: the line is on the safe side).
 double wide_cost(int bm, int64_t strips, int z, int64_t T) {
     const int64_t chunks = (T + 8 * z - 1) / (8 * z), rounds = (strips * z + kCUs - 1) / kCUs;
     const double wgs = (double)(strips * z) / (double)rounds, chunk = bm == 16 ? 1.95 : 2.2;
