@@ -343,8 +343,8 @@ void tp_gemm4_kernel(const GemmArgs p) {
         char* const eps = lds + (fill_a - s_wbase) + w * W4_EPI_BYTES_PER_WAVE;
         BiasBlock<TN> bias;
         if constexpr (USE_BIAS) spread_bias(bias, own_bias, eps);
-        store_c_block<TM, TN, EPI, F32_OUT, true, USE_BIAS>(p, acc, done.m0 + wm * 128, done.n0 + wn * 128, done.z, done.g, bias, eps,
-                                                            std::bool_constant<PRE>{}, std::bool_constant<STREAM>{}, take_bias);
+        store_c_block<TM, TN, EPI, F32_OUT, true, USE_BIAS, STREAM>(p, acc, done.m0 + wm * 128, done.n0 + wn * 128, done.z, done.g, bias, eps,
+                                                            std::bool_constant<PRE>{}, take_bias);
         if (c.left == 0) break;
         barrier();                                    // every wave is done with its patch
     }

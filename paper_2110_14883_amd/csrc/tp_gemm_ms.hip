@@ -29,7 +29,8 @@ template <int BM, int BN> struct MsShape {
 };
 }  // namespace
 
-template <int BM, int BN, bool A_KC, bool B_KC, int EPI, bool F32_OUT>
+// STREAM: stores carry the streaming hint
+template <int BM, int BN, bool A_KC, bool B_KC, int EPI, bool F32_OUT, bool STREAM>
 __global__ __launch_bounds__(MS_THREADS) __attribute__((amdgpu_waves_per_eu(1, 1)))
 void tp_gemm_ms_kernel(const GemmArgs p) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
@@ -258,27 +259,32 @@ void tp_gemm_ms_kernel(const GemmArgs p) {
                 for (int i = 0; i < TM; ++i) acc[i][j][e] += b;
             }
     }
-    store_c_block<TM, TN, EPI, F32_OUT, false, false>(p, acc, m0 + wm * WM, n0 + wn * WN, z, g, bias, lds + w * 8192, p.pre != nullptr, p.stream != 0, [] {});
+    store_c_block<TM, TN, EPI, F32_OUT, false, false, STREAM>(p, acc, m0 + wm * WM, n0 + wn * WN, z, g, bias, lds + w * 8192, p.pre != nullptr, [] {});
 }
 
 // ---------------------------------------------------------------------------------------------
 // host launcher
 // ---------------------------------------------------------------------------------------------
-template <int BM, int BN, bool A_KC, bool B_KC, int EPI, bool F32_OUT>
-static hipError_t launch_ms_one(const GemmArgs& a, hipStream_t stream) {
+template <int BM, int BN, bool A_KC, bool B_KC, int EPI, bool F32_OUT, bool STREAM>
+static hipError_t launch_ms_as(const GemmArgs& a, hipStream_t stream) {
     static std::atomic<uint64_t> attr_done{0};
     constexpr int lds_bytes = MsShape<BM, BN>::LDS_BYTES;
     int dev = 0;
     if (hipError_t e = hipGetDevice(&dev); e != hipSuccess) return e;
     const uint64_t bit = 1ull << (dev & 63);
     if (!(attr_done.load(std::memory_order_relaxed) & bit)) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&tp_gemm_ms_kernel<BM, BN, A_KC, B_KC, EPI, F32_OUT>),
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&tp_gemm_ms_kernel<BM, BN, A_KC, B_KC, EPI, F32_OUT, STREAM>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
         if (e != hipSuccess) return e;
         attr_done.fetch_or(bit, std::memory_order_relaxed);
     }
     const unsigned grid = (unsigned)(a.tiles_m * a.tiles_n * a.split_k);
-    return launch_kernel(tp_gemm_ms_kernel<BM, BN, A_KC, B_KC, EPI, F32_OUT>, dim3(grid), dim3(MS_THREADS), lds_bytes, stream, a);
+    return launch_kernel(tp_gemm_ms_kernel<BM, BN, A_KC, B_KC, EPI, F32_OUT, STREAM>, dim3(grid), dim3(MS_THREADS), lds_bytes, stream, a);
+}
+
+template <int BM, int BN, bool A_KC, bool B_KC, int EPI, bool F32_OUT>
+static hipError_t launch_ms_one(const GemmArgs& a, hipStream_t s) {
+    return a.stream ? launch_ms_as<BM, BN, A_KC, B_KC, EPI, F32_OUT, true>(a, s) : launch_ms_as<BM, BN, A_KC, B_KC, EPI, F32_OUT, false>(a, s);
 }
 
 template <int BM, int BN>

@@ -100,13 +100,13 @@ __device__ __forceinline__ void spread_bias(BiasBlock<4>& b, const uint32_t word
 // Outputs leave with the streaming hint, K-split planes without: an output is not read again by this launch, and as ordinary lines
 // of the L2 it drives out the operand panels that the XCD's other workgroups are about to read (6144 x 24576 fp32, K = 4096: 991 ->
 // 905 us; 32896 x 2560 bf16 twice, K = 2 x 640: 287 -> 272; 8192 x 1024 bf16, K = 2 x 1024: 43 -> 40).  Whether they do is the host's to say
-// (p.stream).  The planes are read by the fix-up at once, from wherever they still are: with the hint 520 x 2056 in three planes takes 23.2 us against 21.8.
+// (GemmArgs::stream).  The planes are read by the fix-up at once, from wherever they still are: with the hint 520 x 2056 in three planes takes 23.2 us against 21.8.
 constexpr int ST_PLAIN = 0, ST_STREAM = 2;        // cache policy bits of a buffer store
-// keep, stream: whether the pre-activation is stored too, whether stores carry the hint; bools or (one way through, no branch)
-// integral_constants.  last(): called behind the last stores.
-template <int TM, int TN, int EPI, bool F32_OUT, bool ACC_HALF, bool ADD_BIAS, class Keep, class Stream, class Last>
+// STREAM: the outputs' stores carry the hint.  keep: whether the pre-activation is stored too, a bool or (one way through, no branch) an
+// integral_constant.  last(): called behind the last stores.
+template <int TM, int TN, int EPI, bool F32_OUT, bool ACC_HALF, bool ADD_BIAS, bool STREAM, class Keep, class Last>
 __device__ __forceinline__ void store_c_block(const GemmArgs& p, f32x16_t (&acc)[TM][TN], const int m_sub, const int n_sub,
-                                              const int z, const int g_out, const BiasBlock<TN>& bias, char* const eps, Keep keep, Stream stream, Last last) {
+                                              const int z, const int g_out, const BiasBlock<TN>& bias, char* const eps, Keep keep, Last last) {
     const int l = threadIdx.x & 63, r = l & 31, ch = l >> 5;
     const bool partial = !ADD_BIAS && !std::is_same_v<Keep, std::true_type> && p.split_k > 1;    // split K: raw fp32 partials, the fix-up kernel runs the epilogue
     constexpr bool use_gelu = EPI == EPI_BIAS_GELU;
@@ -182,31 +182,15 @@ __device__ __forceinline__ void store_c_block(const GemmArgs& p, f32x16_t (&acc)
     auto put_bf16 = [&](int j, int g, const u32x2_t v) __attribute__((always_inline)) {
         *reinterpret_cast<u32x2_t*>(eps + r * (16 * CPR) + (((4 * j + g) ^ swz(r)) << 4) + 8 * ch) = v;
     };
-    // (The policy is part of the instruction: one branch a slab where it is not compiled in.  The fences keep the patch's reads behind it,
-    // where their registers are those of the stores; in front of it the compiler holds a whole slab.)
-    auto with_policy = [&](auto yes, auto f) __attribute__((always_inline)) {
-        if constexpr (std::is_same_v<decltype(yes), bool>) {
-            if (yes) {
-                asm volatile("; streaming" ::: "memory");
-                f(std::integral_constant<int, ST_STREAM>{});
-            } else {
-                asm volatile("; plain" ::: "memory");
-                f(std::integral_constant<int, ST_PLAIN>{});
-            }
-        } else {
-            f(std::integral_constant<int, decltype(yes)::value ? ST_STREAM : ST_PLAIN>{});
-        }
-    };
+    constexpr int out_policy = STREAM ? ST_STREAM : ST_PLAIN;
     auto store_bf16 = [&](int i, __amdgpu_buffer_rsrc_t rs, int ld, uint32_t lane) __attribute__((always_inline)) {
         const int cc = l % CPR;
-        with_policy(stream, [&](auto policy) __attribute__((always_inline)) {
 #pragma unroll
-            for (int it = 0; it < 32 / RPI; ++it) {
-                const int rr = it * RPI + l / CPR;
-                const u32x4_t v = *reinterpret_cast<const u32x4_t*>(eps + rr * (16 * CPR) + ((cc ^ swz(rr)) << 4));
-                __builtin_amdgcn_raw_buffer_store_b128(v, rs, (int)(lane + (uint32_t)((32 * i + RPI * it) * ld * 2)), 0, decltype(policy)::value);
-            }
-        });
+        for (int it = 0; it < 32 / RPI; ++it) {
+            const int rr = it * RPI + l / CPR;
+            const u32x4_t v = *reinterpret_cast<const u32x4_t*>(eps + rr * (16 * CPR) + ((cc ^ swz(rr)) << 4));
+            __builtin_amdgcn_raw_buffer_store_b128(v, rs, (int)(lane + (uint32_t)((32 * i + RPI * it) * ld * 2)), 0, out_policy);
+        }
     };
     auto slab_bf16 = [&](int i, auto value4, __amdgpu_buffer_rsrc_t rs, int ld) __attribute__((always_inline)) {
         const uint32_t lane = lane_bf16(ld);
@@ -247,7 +231,7 @@ __device__ __forceinline__ void store_c_block(const GemmArgs& p, f32x16_t (&acc)
     };
     // fp32 slab, one 32-column block at a time: rows of 128 bytes; lane l stores columns
     // 4 (l % 8) .. + 3 of rows l / 8 + 8 it
-    auto slab_f32 = [&](int i, auto value4, auto yes, __amdgpu_buffer_rsrc_t rs, int ld) __attribute__((always_inline)) {
+    auto slab_f32 = [&](int i, auto value4, auto policy, __amdgpu_buffer_rsrc_t rs, int ld) __attribute__((always_inline)) {
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
             const int n = n_sub + 32 * j + 4 * (l & 7);
@@ -259,14 +243,12 @@ __device__ __forceinline__ void store_c_block(const GemmArgs& p, f32x16_t (&acc)
                 const f32x4_t v = {x[0], x[1], x[2], x[3]};
                 *reinterpret_cast<f32x4_t*>(eps + r * 128 + (((2 * g + ch) ^ ((r >> 1) & 7)) << 4)) = v;
             }
-            with_policy(yes, [&](auto policy) __attribute__((always_inline)) {
 #pragma unroll
-                for (int it = 0; it < 4; ++it) {
-                    const int rr = it * 8 + (l >> 3), cc = l & 7;
-                    const u32x4_t v = *reinterpret_cast<const u32x4_t*>(eps + rr * 128 + ((cc ^ ((rr >> 1) & 7)) << 4));
-                    __builtin_amdgcn_raw_buffer_store_b128(v, rs, (int)(lane + (uint32_t)((32 * i + 8 * it) * ld * 4)), 0, decltype(policy)::value);
-                }
-            });
+            for (int it = 0; it < 4; ++it) {
+                const int rr = it * 8 + (l >> 3), cc = l & 7;
+                const u32x4_t v = *reinterpret_cast<const u32x4_t*>(eps + rr * 128 + ((cc ^ ((rr >> 1) & 7)) << 4));
+                __builtin_amdgcn_raw_buffer_store_b128(v, rs, (int)(lane + (uint32_t)((32 * i + 8 * it) * ld * 4)), 0, decltype(policy)::value);
+            }
         }
     };
     // (with ACC_HALF the last MFMA's result is read by hand-placed instructions: give it the 19 cycles it needs)
@@ -275,7 +257,7 @@ __device__ __forceinline__ void store_c_block(const GemmArgs& p, f32x16_t (&acc)
         const __amdgpu_buffer_rsrc_t rs_ws = block_rsrc(p.ws + ((int64_t)z * p.n_groups + g_out) * p.M * p.N, (int64_t)p.N, 4);
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
-            slab_f32(i, raw4, std::false_type{}, rs_ws, p.N);
+            slab_f32(i, raw4, std::integral_constant<int, ST_PLAIN>{}, rs_ws, p.N);
             __builtin_amdgcn_sched_barrier(0);
         }
         last();
@@ -293,7 +275,7 @@ __device__ __forceinline__ void store_c_block(const GemmArgs& p, f32x16_t (&acc)
                 if constexpr (!use_dg) {
                     if (use_pre) slab_bf16(i, preact4, rs_pre, (int)p.ldp);
                 }
-                if constexpr (F32_OUT) slab_f32(i, final4, stream, rs_out, ldo);
+                if constexpr (F32_OUT) slab_f32(i, final4, std::integral_constant<int, out_policy>{}, rs_out, ldo);
                 else                   slab_bf16(i, final4, rs_out, ldo);
             }
             if (i == TM - 1) last();
